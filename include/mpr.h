@@ -59,9 +59,9 @@ enum {
 #define MPR_TILE_COMPACT 0x100
 #define MPR_TILE_FUSED 0x200
 /* With MPR_TILE_FUSED (8, 12, 16, 24 or 32 rows): the fused sweeps of a chain
- * set whose tiles the GPU holds at once run many per cooperative launch, with
- * a grid barrier between sweeps (small fills; a set too large for that, or a
- * call that records states, runs the same rows one launch per sweep). */
+ * set whose tiles the GPU holds at once run many per cooperative launch, the
+ * tiles kept on the chip (a set that does not fit takes tiles of up to 64
+ * rows, or else the same rows one launch per sweep). */
 #define MPR_TILE_PERSIST 0x400
 
 typedef struct mpr_ctx mpr_ctx;
@@ -148,9 +148,9 @@ typedef struct {
                                 ignored.  Results equal those of an uninterrupted run bit for
                                 bit (random numbers are keyed by sweep, not by call). */
     int32_t barrier_timeout_us; /* > 0: the longest a block of the persistent sweep
-                                (MPR_TILE_PERSIST) waits at its grid barrier, in microseconds,
+                                (MPR_TILE_PERSIST) waits for other blocks, in microseconds,
                                 before the call gives up with MPR_ERR_HIP (every block then
-                                leaves at its next barrier; the workspace contents are lost);
+                                leaves at its next wait; the workspace contents are lost);
                                 0: 2 seconds.  Results do not depend on it. */
 } mpr_params;
 

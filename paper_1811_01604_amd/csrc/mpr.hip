@@ -43,15 +43,16 @@ constexpr int kBlock = 256;
 constexpr int kMapBlocks = 512;          // partial-result blocks per image at most (map, e_s)
 constexpr int kHoldoutBlocks = 64;       // partial-result blocks of the hold-out error
 constexpr size_t kScratchBytes = 8u << 20;
+constexpr size_t kHaloBytes = 8u << 20;  // halo words of the resident sweeps, after the scratch
 constexpr uint32_t kTableStream = 0x80000000u;
 constexpr uint32_t kInitSweep = 0xFFFFFFFFu;
 // Layout of the context's device scratch: fixed slots, then a region for
 // per-call partial results.
 constexpr int64_t kDoneOffset = 0;       // done-chain counter
 constexpr int64_t kTicketOffset = 256;   // last-block ticket of the redo kernel with the control fused
-constexpr int64_t kGenOffset = 512;      // barrier generation of the persistent sweep
-constexpr int64_t kAbortOffset = 768;    // barrier time-out word of the persistent sweep
-constexpr int64_t kSlotsOffset = 16384;  // per-chain sweep sums of the persistent sweep (32 bytes a chain)
+constexpr int64_t kGenOffset = 512;      // sweeps a resident launch has run
+constexpr int64_t kAbortOffset = 768;    // time-out word of the resident sweeps
+constexpr int64_t kSlotsOffset = 16384;  // the blocks' sums of the resident sweeps
 constexpr int64_t kWorkOffset = 1024;    // three work counters (profiling)
 constexpr int64_t kEnergyOffset = 2048;  // diag energy accumulator
 constexpr int64_t kSlopeOffset = 4096;   // diag slope input / output
@@ -639,9 +640,11 @@ __device__ void set_derived(ChainState &st, double q)
 // Algorithm 2 steps 5.2-5.5 (relaxation), 6 (equilibrium states) and the
 // e(T, L) runs for a chain not done, after both colours of a sweep, on its
 // state `st` (in place) with its sums e_fx and acc of that sweep.  The done
-// counter (and the work counters) are skipped where null.
+// counter (and the work counters) are skipped where null; `slope` gives the
+// energy slope at sweep t once the ring buffer holds its energy.
+template <class Slope>
 __device__ __forceinline__ void control_core(ChainState &st, const ChainDesc &d, const CtlParams &cp,
-                                             unsigned int *done_count, unsigned long long *work)
+                                             unsigned int *done_count, unsigned long long *work, Slope slope)
 {
     if (work) {
         // work counters: chain-sweeps, gap-site updates, useful bytes
@@ -659,7 +662,7 @@ __device__ __forceinline__ void control_core(ChainState &st, const ChainDesc &d,
         const double A = (double)acc / (double)d.P;
         if (A < cp.a_targ) st.a_relax = 1.0 + (double)(t + 1u) / cp.k_a;
         st.ring[t % (uint32_t)cp.n_fit] = ope;
-        if (t >= (uint32_t)cp.n_fit && t % (uint32_t)cp.n_f == 0u) st.k = ring_slope(st.ring, t, cp.n_fit, cp.w);
+        if (t >= (uint32_t)cp.n_fit && t % (uint32_t)cp.n_f == 0u) st.k = slope(t);
         st.A_last = A;
         const uint32_t tn = t + 1u;
         st.sweep = tn;
@@ -710,7 +713,7 @@ __device__ __forceinline__ void control_chain(const ChainDesc *__restrict__ desc
     ChainState &st = states[c];
     if (st.phase == PH_DONE) return;
     const ChainDesc d = descs[c];
-    control_core(st, d, cp, done_count, work);
+    control_core(st, d, cp, done_count, work, [&](uint32_t t) { return ring_slope(st.ring, t, cp.n_fit, cp.w); });
 }
 
 // The deferred double-precision updates of one half-sweep (block shape
@@ -923,9 +926,9 @@ __device__ __forceinline__ SweepState sweep_state_of(const ChainState *stp)
     return s;
 }
 
-template <int TH, int NW = kTileNW>
+template <int TH>
 struct TileShared {
-    static constexpr int NT = NW * 64;  // threads per block
+    static constexpr int NW = kTileNW;
     // list entries per wave: its rows of the colour-0 pass with the ring
     // (TH + 2 rows of kTileH columns, a row per wave in turn) and its share
     // of the ring's two side columns (at most 64 per wave)
@@ -940,22 +943,13 @@ struct TileShared {
     int any_redo[2];
 };
 
-// Equilibrium sums and squared deviations of a tile's own sites (both
-// colours), staged with the angles when the sweep is known to need them.
-template <int TH>
-struct TilePre {
-    alignas(16) float acc[2][TH][kTileH];
-    alignas(16) float m2[2][TH][kTileH];
-};
-
 // Stages the tile and its halo (both colours, 18 float4 per row and colour;
 // the colour loop outside, so that the base pointer of every load is
-// uniform) from h into LDS, and with `P` the tile's own equilibrium sums
-// (and squared deviations, where kept).  No barrier at the end.
-template <int TH, int NW>
-__device__ __forceinline__ void tile_stage(TileShared<TH, NW> &L, TilePre<TH> *P, const ChainDesc &d, int y0, int hx0)
+// uniform) from h into LDS.  No barrier at the end.
+template <int TH>
+__device__ __forceinline__ void tile_stage(TileShared<TH> &L, const ChainDesc &d, int y0, int hx0)
 {
-    constexpr int NT = TileShared<TH, NW>::NT;
+    constexpr int NT = kBlock;
     const int tid = (int)threadIdx.x;
     constexpr int NQ = kTileLS / 4;
     constexpr int NLOAD = (TH + 4) * NQ;
@@ -976,29 +970,6 @@ __device__ __forceinline__ void tile_stage(TileShared<TH, NW> &L, TilePre<TH> *P
             if (!in) v[cc][it] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
         }
     }
-    if (P) {
-        // the tile's rows y0 .. y0 + TH - 1, half-columns hx0 .. hx0 + kTileH - 1
-        constexpr int PQ = kTileH / 4;
-        constexpr int PLOAD = TH * PQ;
-        constexpr int PIT = (PLOAD + NT - 1) / NT;
-        const bool with_m2 = d.m2[0] != nullptr;
-#pragma unroll
-        for (int cc = 0; cc < 2; ++cc) {
-            const float *ap = cc ? d.acc[1] : d.acc[0];
-            const float *mp = cc ? d.m2[1] : d.m2[0];
-#pragma unroll
-            for (int it = 0; it < PIT; ++it) {
-                const int k = tid + it * NT;
-                const int r = k / PQ, q = k - r * PQ;
-                const int y = y0 + r;
-                if (k < PLOAD && y < d.ny) {
-                    const uint32_t idx = (uint32_t)(y * d.S + hx0 + 4 * q);
-                    *(v4f *)&P->acc[cc][r][4 * q] = gldi4(ap, idx);
-                    if (with_m2) *(v4f *)&P->m2[cc][r][4 * q] = gldi4(mp, idx);
-                }
-            }
-        }
-    }
 #pragma unroll
     for (int cc = 0; cc < 2; ++cc)
 #pragma unroll
@@ -1010,15 +981,13 @@ __device__ __forceinline__ void tile_stage(TileShared<TH, NW> &L, TilePre<TH> *P
 }
 
 // The sweep (mode 0) or one colour (modes 1, 2) of a staged tile, and the
-// write-back of its gap sites and equilibrium sums (those from `P` when
-// given: staged by tile_stage for this sweep).
-template <bool DIAG, int TH, bool EDGE, int NW>
-__device__ __forceinline__ void tile_update(TileShared<TH, NW> &L, const TilePre<TH> *P, const ChainDesc &d,
-                                            const SweepState &ss, int y0, int hx0, int mode, const SweepConsts &sc,
-                                            int or_only, uint8_t *__restrict__ flags, uint64_t &e_thread,
-                                            uint32_t &acc_thread)
+// write-back of its gap sites and equilibrium sums.
+template <bool DIAG, int TH, bool EDGE>
+__device__ __forceinline__ void tile_update(TileShared<TH> &L, const ChainDesc &d, const SweepState &ss, int y0, int hx0,
+                                            int mode, const SweepConsts &sc, int or_only, uint8_t *__restrict__ flags,
+                                            uint64_t &e_thread, uint32_t &acc_thread)
 {
-    constexpr int NT = TileShared<TH, NW>::NT;
+    constexpr int NT = kBlock, NW = kTileNW;
     // the wave index through readfirstlane: the compiler then knows it is
     // uniform, and keeps the row loops of the list building and their
     // counters on the scalar unit
@@ -1055,10 +1024,9 @@ __device__ __forceinline__ void tile_update(TileShared<TH, NW> &L, const TilePre
                 // their values
                 const int W = (d.nx - ((y + cc) & 1) + 1) >> 1;
                 const bool gg[4] = {g0, g1, g2, g3};
-                const v4f s0 = P ? *(const v4f *)&P->acc[cc][rr][4 * q] : gldi4(ap, idx);
+                const v4f s0 = gldi4(ap, idx);
                 v4f s1 = s0;
-                v4f m = mp ? (P ? *(const v4f *)&P->m2[cc][rr][4 * q] : gldi4(mp, idx))
-                           : v4f{0.0f, 0.0f, 0.0f, 0.0f};
+                v4f m = mp ? gldi4(mp, idx) : v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (gg[e] && h + e < W) {
@@ -1108,7 +1076,7 @@ __device__ __forceinline__ void tile_update(TileShared<TH, NW> &L, const TilePre
             if (energy) {
                 const uint64_t bi = full ? ~0ull : __ballot(in);
                 const int rs = (full ? lane : rank_below(bi)) - rg;
-                if (in && !gap) lst[TileShared<TH, NW>::CAP - 1 - (ns + rs)] = ent;
+                if (in && !gap) lst[TileShared<TH>::CAP - 1 - (ns + rs)] = ent;
                 ns += (full ? 64 : __popcll(bi)) - cg;
             }
         };
@@ -1161,7 +1129,7 @@ __device__ __forceinline__ void tile_update(TileShared<TH, NW> &L, const TilePre
         }
         // bond energies of the tile's sampled colour-1 sites
         for (int e = lane; e < ns; e += 64) {
-            const uint32_t ent = lst[TileShared<TH, NW>::CAP - 1 - e];
+            const uint32_t ent = lst[TileShared<TH>::CAP - 1 - e];
             const int r = (int)(ent >> 7), j = (int)(ent & 127u);
             const int s = (r + c) & 1;
             const float *oth = &L.a[c ^ 1][r][j];
@@ -1179,7 +1147,7 @@ __device__ __forceinline__ void tile_update(TileShared<TH, NW> &L, const TilePre
         __syncthreads();
         // the deferred decisions, in double precision from the same inputs
         if (L.any_redo[pass]) {
-            for (int wd = tid; wd < TileShared<TH, NW>::RW; wd += NT) {
+            for (int wd = tid; wd < TileShared<TH>::RW; wd += NT) {
                 uint32_t m = L.redo[wd];
                 if (!m) continue;
                 L.redo[wd] = 0u;
@@ -1216,16 +1184,16 @@ __device__ __forceinline__ void tile_sweep_body(TileShared<TH> &L, const ChainDe
                                                 uint8_t *__restrict__ flags, uint64_t &e_thread,
                                                 uint32_t &acc_thread)
 {
-    tile_stage<TH, kTileNW>(L, nullptr, d, y0, hx0);
+    tile_stage(L, d, y0, hx0);
     __syncthreads();
-    tile_update<DIAG, TH, EDGE, kTileNW>(L, nullptr, d, ss, y0, hx0, mode, sc, or_only, flags, e_thread, acc_thread);
+    tile_update<DIAG, TH, EDGE>(L, d, ss, y0, hx0, mode, sc, or_only, flags, e_thread, acc_thread);
 }
 
 // The block's bond energy and accepted count added to its chain (energy in
 // 16-bit halves, so that the 32-bit lane sums cannot carry out).  Called by
 // every thread of the block.
-template <int TH, int NW>
-__device__ __forceinline__ void tile_block_sums(TileShared<TH, NW> &L, uint64_t e_thread, uint32_t acc_thread,
+template <int TH>
+__device__ __forceinline__ void tile_block_sums(TileShared<TH> &L, uint64_t e_thread, uint32_t acc_thread,
                                                 unsigned long long *e_sum, unsigned long long *acc_sum)
 {
     const int tid = (int)threadIdx.x;
@@ -1236,6 +1204,7 @@ __device__ __forceinline__ void tile_block_sums(TileShared<TH, NW> &L, uint64_t 
         hi += __shfl_xor(hi, off);
         ac += __shfl_xor(ac, off);
     }
+    constexpr int NW = kTileNW;
     const int wid = tid >> 6;
     if ((tid & 63) == 0) {
         L.red[0][wid] = lo;
@@ -1331,39 +1300,74 @@ __global__ __launch_bounds__(kBlock) void sweep_tile_kernel(ChainDesc *__restric
     if (tid == 0) *ctl.ticket = 0u;
 }
 
-// Persistent fused sweeps, for chain sets whose tiles all fit on the GPU at
-// once (small fills: a 1024 x 1024 chain is 256 tiles of 32 rows).  One
-// cooperative launch (which guarantees that every block is resident) runs up
-// to `count` sweeps of 512-thread blocks, with a grid barrier between two
-// sweeps in place of a kernel launch and its gap.  Every block keeps its
-// chain's descriptor and state and runs the chain's per-sweep control itself
-// (the same inputs give every block of a chain the same result), from the
-// sweep's bond energy and accepted count, which the blocks add into one of
-// two per-chain slots (alternating sweeps), so that nothing waits for one
-// block's control; the chain's first block counts it done and writes its
-// state and descriptor back at the end.  The arithmetic is that of
-// sweep_tile_kernel, so the results are the same bit for bit.
+// Many fused sweeps per cooperative launch (which guarantees that every block
+// is resident), for chain sets whose tiles the GPU holds at once: a
+// 1024 x 1024 chain is 256 tiles of 32 rows.  A block keeps its tile (TH rows
+// x 2 kTileH columns, both colours) in LDS from the launch's first sweep to
+// its last, and exchanges only the sites around it with the tiles beside it.
 //
-// Barrier: every wave waits for its own stores (they then sit in its XCD's
-// L2), one thread per block writes that L2 back (release) and takes a
-// ticket; the last ticket-holder clears the slots read in this sweep, resets
-// the ticket and publishes the sweep count (bit 31: stop) in `gen`; the
-// others poll `gen` and then invalidate their caches (acquire).  A block
-// that waits longer than its bound (2 s unless the call sets another) sets
-// `abort` and every block leaves at its next barrier; the host then reports
-// an error.
-struct PersistCtl {
-    unsigned int *gen;    // sweeps completed in this launch, | 1 << 31 to stop; zero at launch
-    unsigned int *abort;  // nonzero: a block timed out at a barrier
-    unsigned long long *slots;  // per chain: [sweep parity][energy, accepted]; zero at launch
-    uint64_t wait_ticks;  // the longest wait at a barrier, in ticks of the 100 MHz constant clock
-    int32_t count;        // sweeps to run at most
-    uint32_t need;        // done-counter value at which every chain has finished
+// What bounds a small fill is the latency of a sweep's dependent steps, not
+// its arithmetic (a 1024 x 1024 sweep is 5 us of VALU work on 256 CUs).  So:
+//  - A halo value travels as one 64-bit word holding the angle and a tag
+//    (launch epoch and sweep), stored and polled with relaxed device-scope
+//    atomics: the word is its own flag, no fence, cache write-back or
+//    invalidation stands between two sweeps, and the data arrives with the
+//    poll that finds it.  Only colour 1 is exchanged: the ring's colour-0
+//    sites are updated by every tile that reads them, to the same bits.
+//  - The chain's per-sweep control needs its energy and accepted count:
+//    every block stores its own sums in a word of its own and wave 0 of
+//    every block reads those of the whole chain while the other waves poll
+//    the halo (no atomic adds on one address).  Chains never wait for other
+//    chains, and a block leaves when its chain is done.
+//  - Equilibrium sweeps need no control: a tile waits for its neighbours'
+//    halo only, after it has updated the colour-0 sites that do not need it,
+//    so that a tile delayed by a double-precision decision delays its
+//    neighbours and not the whole chain.
+//  - The gap sites do not change: they are listed once per launch, and the
+//    waves take the lists 64 entries at a time in turn.
+// Two halo buffers alternate.  A tile that publishes sweep t + 2 has read
+// its neighbours' sweep t + 1, which they published after reading its
+// sweep t: the buffer it overwrites has been read.  The sums alternate
+// between two words by the same argument over the whole chain.
+// Measured, one chain with 100 states, whole fills, against the kernel this
+// replaced (tiles written to memory and a device-wide barrier between
+// sweeps): 64^2 4.4 us per sweep (8.5), 1024^2 8.4 us (18.9); 2048^2 28.7 us,
+// against 41.3 us with one launch per sweep; four double-precision chains of
+// 512^2 17.3 us, against two half-sweep launches of 12 us; 32 table chains of
+// 256^2 17 us, against 38 us of half-sweeps and deferred redos.
+//
+// A block that waits longer than its bound (2 s unless the call sets another)
+// sets `abort` and every block leaves at its next wait; the host then reports
+// an error.  The update of a site is that of sweep_tile_kernel (or, for
+// double-precision chains, of half_sweep_fp64_kernel), so the results are the
+// same bit for bit.
+struct ResidentCtl {
+    unsigned int *gen;             // most sweeps any chain ran in this launch; zero at launch
+    unsigned int *abort;           // nonzero: a block timed out
+    unsigned long long *sums;      // [sweep parity][block]: energy | accepted << 46 | tag << 60, then
+                                   // [block]: 1 once it has read its chain's state; zero at launch
+    unsigned long long *halo;      // per block: colour 1 of even and odd sweeps, colour 0 at the start
+    unsigned int *done_count;
+    unsigned long long *work;
+    float *states_out;             // recorded equilibrium states (nullable), their stride and K
+    const int64_t *offsets;
+    int64_t states_n_total;
+    uint64_t wait_ticks;           // the longest wait, in ticks of the 100 MHz constant clock
+    uint32_t epoch;                // launch tag of the halo words, << kResSweepBits
+    int32_t count;                 // sweeps to run at most
+    int32_t K;
 };
 constexpr uint64_t kPersistWaitTicks = 200000000ull;  // default wait bound: 2 s
-constexpr int kPersistThreads = 512;
-constexpr int64_t kPersistMaxChains = 1024;  // chains of a set that can take the persistent shapes
-static_assert(kSlotsOffset + 32 * kPersistMaxChains <= kVarOffset, "persistent sweep slots overlap the partials");
+constexpr int kResThreads = 512;
+constexpr int kResWaves = kResThreads / 64;
+constexpr int kResMaxBlocks = 512;  // blocks of a launch at most (8 sums words per lane of the reading wave)
+constexpr int kResSweepBits = 13;   // sweeps_per_launch is at most 4096
+constexpr uint32_t kResEpochs = 1u << (32 - kResSweepBits);
+constexpr int kResMaxRows = 64;
+// 64-bit words of a halo value and of one block's three halo buffers
+template <typename RT> constexpr int res_words() { return (int)sizeof(RT) / 4; }
+template <typename RT, int TH> constexpr int res_halo_len() { return 4 * kTileH + 2 * TH; }
+template <typename RT, int TH> constexpr int res_halo_words() { return 3 * res_halo_len<RT, TH>() * res_words<RT>(); }
 
 __device__ __forceinline__ uint32_t ld_agent(const unsigned int *p)
 {
@@ -1375,155 +1379,596 @@ __device__ __forceinline__ unsigned long long ld_agent64(const unsigned long lon
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int TH>
-__global__ __launch_bounds__(kPersistThreads) __attribute__((amdgpu_waves_per_eu(4))) void sweep_tile_persist_kernel(ChainDesc *descs, ChainState *states,
-                                                                             BlockMap bm, SweepConsts sc,
-                                                                             FusedControl ctl, PersistCtl pc)
+__device__ __forceinline__ void st_agent64(unsigned long long *p, unsigned long long v)
 {
-    constexpr int NW = kPersistThreads / 64;
-    __shared__ TileShared<TH, NW> L;
-    __shared__ TilePre<TH> P;
-    __shared__ ChainState sst;  // this block's copy of its chain's state
-    __shared__ int sh_last, sh_stop;
-    const int tid = (int)threadIdx.x;
-    for (int w = tid; w < TileShared<TH, NW>::RW; w += kPersistThreads) L.redo[w] = 0u;
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ bool fixed_rt(float v) { return is_fixed(v); }
+__device__ __forceinline__ bool fixed_rt(double v) { return is_fixed_d(v); }
+
+template <typename RT, int TH>
+struct ResidentShared {
+    static constexpr int N0 = TH * kTileH + 2 * kTileH + TH;  // colour-0 sites of the tile and its ring
+    static constexpr int C0 = (N0 + 63) / 64;                 // 64-entry chunks of that list
+    static constexpr int RCAP = (C0 + kResWaves - 1) / kResWaves * 64;
+    // the equilibrium sums live in LDS where two blocks per CU leave room
+    static constexpr bool ACC = TH * sizeof(RT) <= 128;
+    alignas(16) RT a[2][TH + 4][kTileLS];
+    alignas(16) RT acc[ACC ? 2 * TH : 1][kTileH];
+    alignas(16) RT m2[ACC ? 2 * TH : 1][kTileH];
+    uint16_t list0[C0 * 64];          // colour-0 gap sites: those that need no halo first; row << 7 | half-column
+    uint16_t list1[TH * kTileH];      // colour 1: gap sites from the front, sampled sites from the back
+    uint16_t redo[kResWaves][RCAP];   // sites of a wave's pass to be redone in double precision
+    ChainState st;                    // this block's copy of its chain's state
+    double w[kMaxFit];
+    unsigned long long red_e[kResWaves];
+    uint32_t red_a[kResWaves];
+    int n0_inner, n0, n1, ns;
+    int fail;
+};
+
+// One poll loop's bookkeeping: true when the wait must be given up.
+__device__ __forceinline__ bool res_give_up(const ResidentCtl &rc, uint64_t t0, int n)
+{
+    __builtin_amdgcn_s_sleep(1);
+    if ((n & 7) == 7 && ld_agent(rc.abort) != 0u) return true;
+    if ((uint64_t)(wall_clock64() - t0) > rc.wait_ticks) {
+        __hip_atomic_store(rc.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return true;
+    }
+    return false;
+}
+
+// Waits for the halo value at p (res_words words tagged `tag`) and returns
+// it in *out; false when the wait was given up.
+__device__ __forceinline__ bool res_wait(const ResidentCtl &rc, const unsigned long long *p, uint32_t tag, float *out)
+{
+    unsigned long long v = ld_agent64(p);
+    if ((uint32_t)(v >> 32) != tag) {
+        const uint64_t t0 = wall_clock64();
+        for (int n = 0;; ++n) {
+            if (res_give_up(rc, t0, n)) return false;
+            v = ld_agent64(p);
+            if ((uint32_t)(v >> 32) == tag) break;
+        }
+    }
+    *out = __uint_as_float((uint32_t)v);
+    return true;
+}
+
+__device__ __forceinline__ bool res_wait(const ResidentCtl &rc, const unsigned long long *p, uint32_t tag, double *out)
+{
+    unsigned long long v = ld_agent64(p), w = ld_agent64(p + 1);
+    if ((uint32_t)(v >> 32) != tag || (uint32_t)(w >> 32) != tag) {
+        const uint64_t t0 = wall_clock64();
+        for (int n = 0;; ++n) {
+            if (res_give_up(rc, t0, n)) return false;
+            v = ld_agent64(p);
+            w = ld_agent64(p + 1);
+            if ((uint32_t)(v >> 32) == tag && (uint32_t)(w >> 32) == tag) break;
+        }
+    }
+    *out = __hiloint2double((int)(uint32_t)w, (int)(uint32_t)v);
+    return true;
+}
+
+__device__ __forceinline__ void res_publish(unsigned long long *p, uint32_t tag, float v)
+{
+    st_agent64(p, ((unsigned long long)tag << 32) | __float_as_uint(v));
+}
+
+__device__ __forceinline__ void res_publish(unsigned long long *p, uint32_t tag, double v)
+{
+    st_agent64(p, ((unsigned long long)tag << 32) | (uint32_t)__double2loint(v));
+    st_agent64(p + 1, ((unsigned long long)tag << 32) | (uint32_t)__double2hiint(v));
+}
+
+// ring_slope by a whole wave: lane j loads the j-th value (the newest is
+// `newest`, not yet in the ring), the sum runs in the same order.
+__device__ __forceinline__ double ring_slope_wave(const double *ring, double newest, uint32_t t, int n_fit,
+                                                  const double *w, int lane)
+{
+    const int j0 = lane < n_fit ? lane : 0;
+    const double r = j0 == n_fit - 1 ? newest : ring[(t + 1u + (uint32_t)j0) % (uint32_t)n_fit];
+    const double wl = w[j0];
+    const int rl = __double2loint(r), rh = __double2hiint(r), wlo = __double2loint(wl), whi = __double2hiint(wl);
+    double s = 0.0;
+    for (int j = 0; j < n_fit; ++j) {
+        const double rj = __hiloint2double(__builtin_amdgcn_readlane(rh, j), __builtin_amdgcn_readlane(rl, j));
+        const double wj = __hiloint2double(__builtin_amdgcn_readlane(whi, j), __builtin_amdgcn_readlane(wlo, j));
+        s += wj * rj;
+    }
+    return s;
+}
+
+// The launch of one tile: block `slot` of the launch, block lb of the nblk
+// blocks of chain cid.
+template <typename RT, int TH, bool EDGE>
+__device__ __forceinline__ void resident_tile(ResidentShared<RT, TH> &L, ChainState *states, const ChainDesc &d, int cid,
+                                              int slot, int lb, int nblk, const SweepConsts &sc, const CtlParams &cp,
+                                              const ResidentCtl &rc)
+{
+    using RS = ResidentShared<RT, TH>;
+    typedef RT v4 __attribute__((ext_vector_type(4)));
+    constexpr bool F64 = sizeof(RT) == 8;
+    constexpr int W = res_words<RT>();
+    constexpr int HL = res_halo_len<RT, TH>() * W;  // words of one halo buffer
+    constexpr int NQ = kTileH / 4;
+    static_assert(4 * kTileH + 2 * TH + 4 <= kResThreads - 64, "one halo value per polling thread");
+    const int tid = (int)threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nbx = d.S / kTileH, nby = nblk / nbx;
+    const int ty = lb / nbx, tx = lb - ty * nbx;
+    const int y0 = ty * TH, hx0 = tx * kTileH;
+    const bool lead = lb == 0;  // the chain's first block
+    RT *const h0p = (RT *)d.h[0], *const h1p = (RT *)d.h[1];
+    RT *const acc0p = (RT *)d.acc[0], *const acc1p = (RT *)d.acc[1];
+    RT *const m20p = (RT *)d.m2[0], *const m21p = (RT *)d.m2[1];
+
+    // ---- the tile, its sums and its chain's state into LDS; the halo zero
+    // (outside the grid: never a candidate nor a valid neighbour)
+    for (int k = tid; k < 2 * (TH + 4) * kTileLS; k += kResThreads) {
+        const int j = k % kTileLS, r = (k / kTileLS) % (TH + 4);
+        if (r < 2 || r >= TH + 2 || j < 4 || j >= kTileH + 4) (&L.a[0][0][0])[k] = (RT)0;
+    }
+    for (int k = tid; k < 2 * TH * NQ; k += kResThreads) {
+        const int cc = k / (TH * NQ), rr = (k / NQ) % TH, q = k % NQ, y = y0 + rr;
+        v4 v = {(RT)0, (RT)0, (RT)0, (RT)0}, s = v, m = v;
+        if (y < d.ny) {
+            const int64_t idx = (int64_t)y * d.S + hx0 + 4 * q;
+            v = *(const v4 *)((cc ? h1p : h0p) + idx);
+            if (RS::ACC && acc0p) s = *(const v4 *)((cc ? acc1p : acc0p) + idx);
+            if (RS::ACC && m20p) m = *(const v4 *)((cc ? m21p : m20p) + idx);
+        }
+        *(v4 *)&L.a[cc][rr + 2][4 + 4 * q] = v;
+        if (RS::ACC) {
+            *(v4 *)&L.acc[cc * TH + rr][4 * q] = s;
+            *(v4 *)&L.m2[cc * TH + rr][4 * q] = m;
+        }
+    }
+    {
+        const unsigned long long *src = reinterpret_cast<const unsigned long long *>(states + cid);
+        unsigned long long *dst = reinterpret_cast<unsigned long long *>(&L.st);
+        for (int k = tid; k < (int)(sizeof(ChainState) / 8); k += kResThreads) dst[k] = src[k];
+        for (int k = tid; k < kMaxFit; k += kResThreads) L.w[k] = cp.w[k];
+    }
+    if (tid == 0) {
+        L.n0_inner = L.n0 = L.n1 = L.ns = 0;
+        L.fail = 0;
+    }
+    __syncthreads();
+
+    unsigned long long *const started = rc.sums + 2 * kResMaxBlocks + (slot - lb);
+    if (tid == 0 && nblk > 1) st_agent64(started + lb, 1ull);
+
+    // ---- halo exchange: a block's colour-1 buffer holds its rows 0, 1,
+    // TH - 2 and TH - 1, then its first and last half-column; the colour-0
+    // one rows 0 and TH - 1, then the columns
+    unsigned long long *const mine = rc.halo + (int64_t)slot * 3 * HL;
+    auto publish1 = [&](int buf, uint32_t tag) {
+        for (int k = tid; k < 4 * kTileH + 2 * TH; k += kResThreads) {
+            RT v;
+            if (k < 4 * kTileH) {
+                const int b = k / kTileH;
+                v = L.a[1][b < 2 ? 2 + b : TH + b - 2][4 + k % kTileH];
+            } else {
+                const int b = k - 4 * kTileH;
+                v = L.a[1][2 + (b < TH ? b : b - TH)][b < TH ? 4 : kTileH + 3];
+            }
+            res_publish(mine + buf * HL + k * W, tag, v);
+        }
+    };
+    // the halo value this thread polls (threads of wave 0 poll none):
+    // offset in the halo of the block that holds it, or -1, and its place
+    int64_t src1 = -1, src0 = -1;
+    int dst1 = 0, dst0 = 0;
+    {
+        const int up = ty > 0 ? slot - nbx : -1, dn = ty + 1 < nby ? slot + nbx : -1;
+        const int w = tid - 64;
+        int s = -1, o = 0, r = 0, j = 0;
+        if (w < 0) {
+        } else if (w < 2 * kTileH) {  // rows y0 - 1 and y0 - 2
+            s = up, o = (w < kTileH ? 3 : 2) * kTileH + w % kTileH, r = w < kTileH ? 1 : 0, j = 4 + w % kTileH;
+        } else if (w < 4 * kTileH) {  // rows y0 + TH and y0 + TH + 1
+            s = dn, o = w - 2 * kTileH, r = w < 3 * kTileH ? TH + 2 : TH + 3, j = 4 + w % kTileH;
+        } else if (w < 4 * kTileH + TH) {
+            s = tx > 0 ? slot - 1 : -1, o = w + TH, r = 2 + w - 4 * kTileH, j = 3;
+        } else if (w < 4 * kTileH + 2 * TH) {
+            s = tx + 1 < nbx ? slot + 1 : -1, o = w - TH, r = 2 + w - 4 * kTileH - TH, j = kTileH + 4;
+        } else if (w < 4 * kTileH + 2 * TH + 4) {  // corners
+            const int k = w - 4 * kTileH - 2 * TH, b = k < 2 ? up : dn;
+            const bool left = (k & 1) == 0;
+            s = b >= 0 && (left ? tx > 0 : tx + 1 < nbx) ? b + (left ? -1 : 1) : -1;
+            o = (k < 2 ? 3 : 0) * kTileH + (left ? kTileH - 1 : 0), r = k < 2 ? 1 : TH + 2, j = left ? 3 : kTileH + 4;
+        }
+        if (s >= 0) src1 = (int64_t)s * 3 * HL + o * W;
+        dst1 = r * kTileLS + j;
+        s = -1;
+        if (w < 0) {
+        } else if (w < kTileH) {
+            s = up, o = kTileH + w, r = 1, j = 4 + w;
+        } else if (w < 2 * kTileH) {
+            s = dn, o = w - kTileH, r = TH + 2, j = 4 + w - kTileH;
+        } else if (w < 2 * kTileH + TH) {
+            s = tx > 0 ? slot - 1 : -1, o = w + TH, r = 2 + w - 2 * kTileH, j = 3;
+        } else if (w < 2 * kTileH + 2 * TH) {
+            s = tx + 1 < nbx ? slot + 1 : -1, o = w - TH, r = 2 + w - 2 * kTileH - TH, j = kTileH + 4;
+        }
+        if (s >= 0) src0 = (int64_t)s * 3 * HL + 2 * HL + o * W;
+        dst0 = r * kTileLS + j;
+    }
+    auto wait1 = [&](int buf, uint32_t tag) {
+        if (src1 < 0) return;
+        RT v;
+        if (res_wait(rc, rc.halo + src1 + buf * HL, tag, &v)) (&L.a[1][0][0])[dst1] = v;
+        else L.fail = 1;
+    };
+    if (nblk > 1) {
+        publish1(0, rc.epoch | 1u);
+        for (int k = tid; k < 2 * kTileH + 2 * TH; k += kResThreads) {
+            RT v;
+            if (k < 2 * kTileH) {
+                v = L.a[0][k < kTileH ? 2 : TH + 1][4 + k % kTileH];
+            } else {
+                const int b = k - 2 * kTileH;
+                v = L.a[0][2 + (b < TH ? b : b - TH)][b < TH ? 4 : kTileH + 3];
+            }
+            res_publish(mine + 2 * HL + k * W, rc.epoch | 1u, v);
+        }
+        wait1(0, rc.epoch | 1u);
+        if (src0 >= 0) {
+            RT v;
+            if (res_wait(rc, rc.halo + src0, rc.epoch | 1u, &v)) (&L.a[0][0][0])[dst0] = v;
+            else L.fail = 1;
+        }
+        __syncthreads();
+    }
+
+    // ---- the lists: colour 0 in two rounds, first the gap sites whose
+    // neighbours are all in the tile, then the others and the ring; colour 1
+    // (a list's order does not matter: sites of a colour do not depend on
+    // each other and the sums are integers)
+    auto in_grid = [&](int c, int r, int j) {
+        const int y = y0 - 2 + r, h = hx0 - 4 + j, s = (r + c) & 1;
+        return !EDGE || (y >= 0 && y < d.ny && h >= 0 && h < ((d.nx - s + 1) >> 1));
+    };
+    auto append = [&](bool want, uint16_t *lst, int *n, int dir, uint16_t ent) {
+        const uint64_t b = __ballot(want);
+        int base = 0;
+        if (lane == 0 && b) base = atomicAdd(n, (int)__popcll(b));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (want) lst[dir * (base + rank_below(b))] = ent;
+    };
+    for (int round = 0; round < 2; ++round) {
+        for (int r = 2 + wid; r < TH + 2; r += kResWaves) {
+            const int j = 4 + lane, s = r & 1;
+            const bool inner = r > 2 && r < TH + 1 && (s ? j < kTileH + 3 : j > 4);
+            append(inner == (round == 0) && in_grid(0, r, j) && !fixed_rt(L.a[0][r][j]), L.list0, &L.n0, 1,
+                   (uint16_t)((r << 7) | j));
+        }
+        if (round == 0) {
+            __syncthreads();
+            if (tid == 0) L.n0_inner = L.n0;
+            __syncthreads();
+        } else {
+            // the ring: the rows above and below, and in each row the one
+            // colour-0 site beside the tile
+            if (wid < 2) {
+                const int r = wid ? TH + 2 : 1, j = 4 + lane;
+                append(in_grid(0, r, j) && !fixed_rt(L.a[0][r][j]), L.list0, &L.n0, 1, (uint16_t)((r << 7) | j));
+            }
+            for (int k = wid; k * 64 < TH; k += kResWaves) {
+                const int rr = k * 64 + lane, r = 2 + (rr < TH ? rr : 0), j = (r & 1) ? 3 : kTileH + 4;
+                append(rr < TH && in_grid(0, r, j) && !fixed_rt(L.a[0][r][j]), L.list0, &L.n0, 1,
+                       (uint16_t)((r << 7) | j));
+            }
+        }
+    }
+    for (int r = 2 + wid; r < TH + 2; r += kResWaves) {
+        const int j = 4 + lane;
+        const bool in = in_grid(1, r, j), gap = in && !fixed_rt(L.a[1][r][j]);
+        append(gap, L.list1, &L.n1, 1, (uint16_t)((r << 7) | j));
+        append(in && !gap, L.list1 + TH * kTileH - 1, &L.ns, -1, (uint16_t)((r << 7) | j));
+    }
+    __syncthreads();
+    const int n0 = L.n0, n1 = L.n1, ns = L.ns, inner_chunks = L.n0_inner / 64;
+
+    // ---- the sweeps
+    int32_t phase = L.st.phase;
+    bool due = false;  // a sweep was made whose control has not run
+    int i = 0;
+    for (;; ++i) {
+        bool have = true;  // the halo of this sweep is in LDS
+        if (due) {
+            if (phase == PH_EQ) {
+                have = nblk == 1;
+                if (tid == 0) {
+                    L.st.e_fx = L.st.acc = 0ull;
+                    control_core(L.st, d, cp, lead ? rc.done_count : nullptr, lead ? rc.work : nullptr,
+                                 [](uint32_t) { return 0.0; });
+                }
+            } else if (wid == 0) {
+                // the chain's sums of the last sweep
+                unsigned long long e = 0ull;
+                uint32_t ac = 0u;
+                if (nblk == 1) {
+                    e = lane < kResWaves ? L.red_e[lane & (kResWaves - 1)] : 0ull;
+                    ac = lane < kResWaves ? L.red_a[lane & (kResWaves - 1)] : 0u;
+                } else {
+                    const unsigned long long *p = rc.sums + (int64_t)((i - 1) & 1) * kResMaxBlocks + (slot - lb);
+                    const uint32_t tag = (((uint32_t)(i - 1) >> 1) & 7u) + 1u;
+                    unsigned long long v[kResMaxBlocks / 64];
+#pragma unroll
+                    for (int k = 0; k < kResMaxBlocks / 64; ++k)
+                        v[k] = lane + 64 * k < nblk ? ld_agent64(p + lane + 64 * k) : (unsigned long long)tag << 60;
+                    const uint64_t t0 = wall_clock64();
+                    for (int n = 0;; ++n) {
+                        bool ok = true;
+#pragma unroll
+                        for (int k = 0; k < kResMaxBlocks / 64; ++k) ok = ok && (uint32_t)(v[k] >> 60) == tag;
+                        if (ok) break;
+                        if (res_give_up(rc, t0, n)) {
+                            L.fail = 1;
+                            break;
+                        }
+#pragma unroll
+                        for (int k = 0; k < kResMaxBlocks / 64; ++k)
+                            if ((uint32_t)(v[k] >> 60) != tag) v[k] = ld_agent64(p + lane + 64 * k);
+                    }
+#pragma unroll
+                    for (int k = 0; k < kResMaxBlocks / 64; ++k) {
+                        e += v[k] & ((1ull << 46) - 1ull);
+                        ac += (uint32_t)(v[k] >> 46) & 0x3FFFu;
+                    }
+                }
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) {
+                    e += __shfl_xor(e, off);
+                    ac += __shfl_xor(ac, off);
+                }
+                const uint32_t t = L.st.sweep;
+                double slope = 0.0;
+                if (phase == PH_RELAX && t >= (uint32_t)cp.n_fit && t % (uint32_t)cp.n_f == 0u)
+                    slope = ring_slope_wave(L.st.ring, (double)e * cp.e_unit / (double)d.ngp, t, cp.n_fit, L.w, lane);
+                if (lane == 0) {
+                    L.st.e_fx = e;
+                    L.st.acc = ac;
+                    control_core(L.st, d, cp, lead ? rc.done_count : nullptr, lead ? rc.work : nullptr,
+                                 [&](uint32_t) { return slope; });
+                }
+            } else if (i < rc.count) {
+                wait1(i & 1, rc.epoch | (uint32_t)(i + 1));
+            }
+            __syncthreads();
+        }
+        if (L.fail) break;
+        phase = L.st.phase;
+        if (phase == PH_DONE || i >= rc.count) break;
+        const bool eq = phase == PH_EQ;
+        const uint32_t sweep = L.st.sweep;
+        unsigned long long e_thread = 0ull;
+        uint32_t acc_thread = 0u;
+        int n_redo = 0;
+        // segment 0: the colour-0 chunks that need no halo; 1: the others; 2: colour 1
+        for (int seg = 0; seg < 3; ++seg) {
+            const int c = seg == 2 ? 1 : 0;
+            if (seg == 1 && !have) {
+                wait1(i & 1, rc.epoch | (uint32_t)(i + 1));
+                __syncthreads();
+                if (L.fail) break;
+            }
+            const uint16_t *lst = c ? L.list1 : L.list0;
+            const int n = c ? n1 : n0;
+            const int k_end = seg == 0 ? inner_chunks : (n + 63) / 64;
+            // wave w takes chunks w, w + kResWaves, ...; segment 1 goes on where 0 stopped
+            int k = wid;
+            if (seg == 1) k += (inner_chunks > wid ? (inner_chunks - wid + kResWaves - 1) / kResWaves : 0) * kResWaves;
+            for (; k < k_end; k += kResWaves) {
+                const int e = k * 64 + lane;
+                bool n64 = false;
+                uint32_t ent = 0u;
+                if (e < n) {
+                    ent = lst[e];
+                    const int r = (int)(ent >> 7), j = (int)(ent & 127u);
+                    const int s = (r + c) & 1;  // y0 is even
+                    const RT *oth = &L.a[c ^ 1][r][j];
+                    const RT a0 = L.a[c][r][j];
+                    const RT nL = fabs(oth[s - 1]), nR = fabs(oth[s]), nU = fabs(oth[-kTileLS]), nD = fabs(oth[kTileLS]);
+                    const int y = y0 - 2 + r, h = hx0 - 4 + j;
+                    uint32_t valid = 15u;
+                    if (EDGE) {
+                        const int Wo = (d.nx + s) >> 1;
+                        valid = (h + s - 1 >= 0 ? 1u : 0u) | (h + s < Wo ? 2u : 0u) | (y > 0 ? 4u : 0u) |
+                                (y + 1 < d.ny ? 8u : 0u);
+                    }
+                    const U4 ctr = {(uint32_t)y * (uint32_t)d.nx + (uint32_t)(2 * (h & ~1) + s), sweep, d.chain,
+                                    d.image_id};
+                    const U4 w = philox4x32_10(ctr, sc.seed_lo, sc.seed_hi);
+                    const bool second = (h & 1) != 0;
+                    const float u = unit24(second ? w.z : w.x), rr = unit24(second ? w.w : w.y);
+                    const bool own = c == 1 || (r >= 2 && r < TH + 2 && j >= 4 && j < kTileH + 4);
+                    if constexpr (F64) {
+                        const SiteOutD o = update_site_d(a0, nL, nR, nU, nD, valid, (double)u, (double)rr, L.st.a_cur,
+                                                         L.st.T, sc.q64, false);
+                        L.a[c][r][j] = o.phi;
+                        if (own) {
+                            acc_thread += o.accepted ? 1u : 0u;
+                            if (c == 1 && !eq) e_thread += energy_fx_d(o.e_bonds);
+                        }
+                    } else {
+                        n64 = true;
+                        const SiteOut o = update_site(a0, nL, nR, nU, nD, valid, u, rr, L.st.inv_T, L.st.dscale, false,
+                                                      &n64);
+                        if (!n64) {
+                            L.a[c][r][j] = o.phi;
+                            if (own) {
+                                acc_thread += o.accepted ? 1u : 0u;
+                                if (c == 1 && !eq) e_thread += energy_fx(o.e_bonds);
+                            }
+                        }
+                    }
+                }
+                if constexpr (!F64) {  // too close to call: redone below
+                    const uint64_t b = __ballot(n64);
+                    if (b) {
+                        if (n64) L.redo[wid][n_redo + rank_below(b)] = (uint16_t)ent;
+                        n_redo += (int)__popcll(b);
+                    }
+                }
+            }
+            if (seg == 0) continue;
+            // the wave's deferred decisions, in double precision from the same inputs
+            if constexpr (!F64) {
+                for (int e = lane; e < n_redo; e += 64) {
+                    const uint32_t ent = L.redo[wid][e];
+                    const int r = (int)(ent >> 7), j = (int)(ent & 127u);
+                    const SiteOutD o = tile_redo_site(&L.a[0][0][0], TH + 4, c, r, j, y0, hx0, d.nx, d.ny, sweep, d.chain,
+                                                      d.image_id, sc, 0, L.st.a_cur, L.st.T);
+                    L.a[c][r][j] = (float)o.phi;
+                    if (c == 1 || (r >= 2 && r < TH + 2 && j >= 4 && j < kTileH + 4)) {
+                        acc_thread += o.accepted ? 1u : 0u;
+                        if (c == 1 && !eq) e_thread += energy_fx((float)o.e_bonds);
+                    }
+                }
+                n_redo = 0;
+            }
+            if (c == 1 && !eq) {
+                // bond energies of the tile's sampled colour-1 sites
+                for (int e = tid; e < ns; e += kResThreads) {
+                    const uint32_t ent = L.list1[TH * kTileH - 1 - e];
+                    const int r = (int)(ent >> 7), j = (int)(ent & 127u);
+                    const int s = (r + 1) & 1;
+                    const RT *oth = &L.a[0][r][j];
+                    const RT nL = fabs(oth[s - 1]), nR = fabs(oth[s]), nU = fabs(oth[-kTileLS]), nD = fabs(oth[kTileLS]);
+                    uint32_t valid = 15u;
+                    if (EDGE) {
+                        const int y = y0 - 2 + r, h = hx0 - 4 + j;
+                        const int Wo = (d.nx + s) >> 1;
+                        valid = (h + s - 1 >= 0 ? 1u : 0u) | (h + s < Wo ? 2u : 0u) | (y > 0 ? 4u : 0u) |
+                                (y + 1 < d.ny ? 8u : 0u);
+                    }
+                    if constexpr (F64) e_thread += energy_fx_d(bond_energy_d(fabs(L.a[1][r][j]), nL, nR, nU, nD, valid, sc.q64));
+                    else e_thread += energy_fx(bond_energy_half(0.5f * fabsf(L.a[1][r][j]), nL, nR, nU, nD, valid));
+                }
+                unsigned long long es = e_thread;
+                uint32_t as = acc_thread;
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) {
+                    es += __shfl_xor(es, off);
+                    as += __shfl_xor(as, off);
+                }
+                if (lane == 0) {
+                    L.red_e[wid] = es;
+                    L.red_a[wid] = as;
+                }
+            }
+            __syncthreads();
+        }
+        if (L.fail) break;
+        due = true;
+        if (nblk > 1) {
+            if (tid == 0 && !eq) {
+                unsigned long long e = 0ull, a = 0ull;
+                for (int w = 0; w < kResWaves; ++w) {
+                    e += L.red_e[w];
+                    a += L.red_a[w];
+                }
+                const unsigned long long tag = (((uint32_t)i >> 1) & 7u) + 1u;
+                st_agent64(rc.sums + (int64_t)(i & 1) * kResMaxBlocks + slot, e | (a << 46) | (tag << 60));
+            }
+            publish1((i + 1) & 1, rc.epoch | (uint32_t)(i + 2));
+        }
+        if (eq) {
+            // the sweep's states into the equilibrium sums (the arithmetic of
+            // accumulate_state), and recorded, while the halo is under way
+            if (acc0p) {
+                for (int k = tid; k < 2 * TH * NQ; k += kResThreads) {
+                    const int cc = k / (TH * NQ), rr = (k / NQ) % TH, q = k % NQ, y = y0 + rr;
+                    if (y >= d.ny) continue;
+                    const int h = hx0 + 4 * q;
+                    const int Wc = (d.nx - ((y + cc) & 1) + 1) >> 1;
+                    const v4 v = *(const v4 *)&L.a[cc][rr + 2][4 + 4 * q];
+                    const int64_t idx = (int64_t)y * d.S + h;
+                    v4 *ap = RS::ACC ? (v4 *)&L.acc[RS::ACC ? cc * TH + rr : 0][4 * q] : (v4 *)((cc ? acc1p : acc0p) + idx);
+                    v4 *mp = RS::ACC ? (v4 *)&L.m2[RS::ACC ? cc * TH + rr : 0][4 * q] : (v4 *)((cc ? m21p : m20p) + idx);
+                    const v4 s0 = *ap;
+                    v4 s1 = s0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (!fixed_rt(v[e]) && h + e < Wc) s1[e] = s0[e] + v[e];
+                    *ap = s1;
+                    if (m20p) {
+                        v4 m = *mp;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (!fixed_rt(v[e]) && h + e < Wc) {
+                                if constexpr (F64)
+                                    m[e] = fma(v[e] - s0[e] * L.st.inv_km1_d, v[e] - s1[e] * L.st.inv_k_d, m[e]);
+                                else m[e] = fmaf(v[e] - s0[e] * L.st.inv_km1, v[e] - s1[e] * L.st.inv_k, m[e]);
+                            }
+                        *mp = m;
+                    }
+                }
+            }
+            if (rc.states_out) {
+                const int64_t m = (int64_t)d.chain * rc.K + (rc.K - L.st.eq_left);
+                float *o = rc.states_out + m * rc.states_n_total + rc.offsets[cid];
+                for (int k = tid; k < TH * 2 * kTileH; k += kResThreads) {
+                    const int rr = k / (2 * kTileH), xx = k % (2 * kTileH), y = y0 + rr, x = 2 * hx0 + xx;
+                    if (y < d.ny && x < d.nx)
+                        o[(int64_t)y * d.nx + x] = (float)fabs(L.a[(rr + xx) & 1][rr + 2][4 + (xx >> 1)]);
+                }
+            }
+            __syncthreads();  // the state is read above, the control changes it
+        }
+    }
+    // ---- the tile, its sums and the chain's state back to memory
+    __syncthreads();
+    if (L.fail) return;
+    for (int k = tid; k < 2 * TH * NQ; k += kResThreads) {
+        const int cc = k / (TH * NQ), rr = (k / NQ) % TH, q = k % NQ, y = y0 + rr;
+        if (y >= d.ny) continue;
+        const int64_t idx = (int64_t)y * d.S + hx0 + 4 * q;
+        *(v4 *)((cc ? h1p : h0p) + idx) = *(const v4 *)&L.a[cc][rr + 2][4 + 4 * q];
+        if (RS::ACC && acc0p) *(v4 *)((cc ? acc1p : acc0p) + idx) = *(const v4 *)&L.acc[RS::ACC ? cc * TH + rr : 0][4 * q];
+        if (RS::ACC && m20p) *(v4 *)((cc ? m21p : m20p) + idx) = *(const v4 *)&L.m2[RS::ACC ? cc * TH + rr : 0][4 * q];
+    }
+    if (lead) {
+        // once every block of the chain has read its state at the start
+        // (equilibrium sweeps wait for the neighbours only)
+        if (tid < nblk && nblk > 1) {
+            const uint64_t t0 = wall_clock64();
+            for (int n = 0; ld_agent64(started + tid) == 0ull; ++n)
+                if (res_give_up(rc, t0, n)) break;
+        }
+        __syncthreads();
+        const unsigned long long *src = reinterpret_cast<const unsigned long long *>(&L.st);
+        unsigned long long *dst = reinterpret_cast<unsigned long long *>(states + cid);
+        for (int k = tid; k < (int)(sizeof(ChainState) / 8); k += kResThreads) dst[k] = src[k];
+        if (tid == 0) atomicMax(rc.gen, (unsigned int)i);
+    }
+}
+
+template <typename RT, int TH>
+__global__ __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(4))) void sweep_resident_kernel(
+    const ChainDesc *descs, ChainState *states, BlockMap bm, SweepConsts sc, CtlParams cp, ResidentCtl rc)
+{
+    __shared__ ResidentShared<RT, TH> L;
     // the tile of this block (the XCD-aware order of sweep_tile_kernel)
     const uint32_t G = gridDim.x, b = blockIdx.x;
     const uint32_t per = G >> 3, rem = G & 7u, xcd = b & 7u;
-    const int64_t lbk = (int64_t)xcd * per + (int64_t)min(xcd, rem) + (int64_t)(b >> 3);
-    int lb;
-    const int cid = chain_of_block(bm, lbk, &lb);
-    const bool lead = lb == 0;  // the chain's first block
-    unsigned long long *const slot = pc.slots + 4 * cid;
-    // descriptor and state as of the launch (earlier kernels wrote them)
-    ChainDesc d = descs[cid];
-    {
-        const unsigned long long *src = reinterpret_cast<const unsigned long long *>(states + cid);
-        unsigned long long *dst = reinterpret_cast<unsigned long long *>(&sst);
-        for (int k = tid; k < (int)(sizeof(ChainState) / 8); k += kPersistThreads) dst[k] = src[k];
-    }
+    const int64_t slot = (int64_t)xcd * per + (int64_t)min(xcd, rem) + (int64_t)(b >> 3);
+    const int k = find_chain(bm.start, bm.n, slot);
+    const int lb = (int)(slot - bm.start[k]), nblk = (int)(bm.start[k + 1] - bm.start[k]);
+    const int cid = bm.id[k];
+    const ChainDesc d = descs[cid];
+    if (states[cid].phase == PH_DONE) return;  // before this launch: no block of the chain starts
     const int nbx = d.S / kTileH;
     const int ty = lb / nbx, tx = lb - ty * nbx;
     const int y0 = ty * TH, hx0 = tx * kTileH;
     const bool edge = !(ty >= 1 && y0 + TH + 2 <= d.ny && tx >= 1 && hx0 + kTileH + 2 <= (d.nx >> 1));
-    const bool sums = d.acc[0] != nullptr;
-    __syncthreads();
-    int phase = sst.phase;  // the chain's phase as of the last control
-    bool swept = false;     // the previous loop pass swept the chain (its control is due)
-    for (int i = 0; i < pc.count; ++i) {
-        // the control of the previous sweep: its sums (coherent loads) are
-        // read while the tile is staged
-        unsigned long long te = 0ull, ta = 0ull;
-        const bool due = swept;
-        if (tid == 0 && due) {
-            te = ld_agent64(slot + 2 * ((i - 1) & 1));
-            ta = ld_agent64(slot + 2 * ((i - 1) & 1) + 1);
-        }
-        // the equilibrium sums are staged too when the last sweep was an
-        // equilibrium one (the next is then one as well, or none)
-        const bool pre = sums && phase == PH_EQ;
-        if (phase != PH_DONE) tile_stage<TH, NW>(L, pre ? &P : nullptr, d, y0, hx0);
-        if (tid == 0 && due) {
-            sst.e_fx = te;
-            sst.acc = ta;
-            control_core(sst, d, ctl.cp, lead ? ctl.done_count : nullptr, lead ? ctl.work : nullptr);
-        }
-        if (tid < 2) L.any_redo[tid] = 0;
-        __syncthreads();
-        const SweepState ss = sweep_state_of(&sst);
-        phase = ss.phase;
-        swept = phase != PH_DONE;
-        if (swept) {
-            uint64_t e_thread = 0u;
-            uint32_t acc_thread = 0u;
-            const TilePre<TH> *pp = pre ? &P : nullptr;
-            if (edge)
-                tile_update<false, TH, true, NW>(L, pp, d, ss, y0, hx0, 0, sc, 0, nullptr, e_thread, acc_thread);
-            else
-                tile_update<false, TH, false, NW>(L, pp, d, ss, y0, hx0, 0, sc, 0, nullptr, e_thread, acc_thread);
-            if (ss.phase != PH_EQ) tile_block_sums(L, e_thread, acc_thread, slot + 2 * (i & 1), slot + 2 * (i & 1) + 1);
-            // the sweep wrote h2: exchange the buffers (as sweep_tile_kernel's last block does in memory)
-            float *t0 = d.h[0], *t1 = d.h[1];
-            d.h[0] = d.h2[0];
-            d.h[1] = d.h2[1];
-            d.h2[0] = t0;
-            d.h2[1] = t1;
-            if (tid == 0) sst.swapped ^= 1;
-        }
-        // arrive: this wave's stores are in L2, then one write-back per block
-        __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (tid == 0) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            sh_last = atomicAdd(ctl.ticket, 1u) == G - 1u;
-        }
-        __syncthreads();
-        if (sh_last) {
-            // every block has read the sums of the previous sweep: clear
-            // their slots for the sweep after next
-            for (int k = tid; k < bm.n; k += kPersistThreads) {
-                unsigned long long *sk = pc.slots + 4 * bm.id[k] + 2 * ((i + 1) & 1);
-                __hip_atomic_store(sk, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(sk + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-            __syncthreads();
-            if (tid == 0) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                const bool stop = i + 1 >= pc.count || ld_agent(ctl.done_count) >= pc.need || ld_agent(pc.abort) != 0u;
-                __hip_atomic_store(ctl.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-                __hip_atomic_store(pc.gen, (uint32_t)(i + 1) | (stop ? 0x80000000u : 0u), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-                sh_stop = stop ? 1 : 0;
-            }
-        } else if (tid == 0) {
-            const uint64_t t0 = wall_clock64();
-            int stop = 0;
-            for (;;) {
-                const uint32_t g = ld_agent(pc.gen);
-                if ((g & 0x7FFFFFFFu) >= (uint32_t)(i + 1)) {
-                    stop = (g >> 31) ? 1 : 0;
-                    break;
-                }
-                if (ld_agent(pc.abort) != 0u) {
-                    stop = 1;
-                    break;
-                }
-                if ((uint64_t)(wall_clock64() - t0) > pc.wait_ticks) {
-                    __hip_atomic_store(pc.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    stop = 1;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(4);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            sh_stop = stop;
-        }
-        __syncthreads();
-        if (sh_stop) {
-            // the control of the last sweep updated
-            if (tid == 0 && swept) {
-                sst.e_fx = ld_agent64(slot + 2 * (i & 1));
-                sst.acc = ld_agent64(slot + 2 * (i & 1) + 1);
-                control_core(sst, d, ctl.cp, lead ? ctl.done_count : nullptr, lead ? ctl.work : nullptr);
-            }
-            break;
-        }
-    }
-    // the chain's first block writes its state and descriptor back
-    __syncthreads();
-    if (lead) {
-        const unsigned long long *src = reinterpret_cast<const unsigned long long *>(&sst);
-        unsigned long long *dst = reinterpret_cast<unsigned long long *>(states + cid);
-        for (int k = tid; k < (int)(sizeof(ChainState) / 8); k += kPersistThreads) dst[k] = src[k];
-        if (tid == 0) {
-            descs[cid].h[0] = d.h[0];
-            descs[cid].h[1] = d.h[1];
-            descs[cid].h2[0] = d.h2[0];
-            descs[cid].h2[1] = d.h2[1];
-        }
-    }
+    if (edge) resident_tile<RT, TH, true>(L, states, d, cid, (int)slot, lb, nblk, sc, cp, rc);
+    else resident_tile<RT, TH, false>(L, states, d, cid, (int)slot, lb, nblk, sc, cp, rc);
 }
 
 // The double-precision sweep: the layout of half_sweep_body (a thread per
@@ -1874,6 +2319,13 @@ __global__ void clear_words_kernel(unsigned int *w0, unsigned int *w1, unsigned 
         if (w2) *w2 = 0u;
     }
     for (int k = t; k < n64; k += (int)blockDim.x) wide[k] = 0ull;
+}
+
+// Zeroes the halo words of the resident sweeps.
+__global__ void clear_halo_kernel(unsigned long long *w, int64_t n)
+{
+    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
+        w[k] = 0ull;
 }
 
 // 1 for every chain that is done, else 0 (for rebuilding the launch list).
@@ -2402,15 +2854,22 @@ struct mpr_ctx {
     // rest stages small read-backs (the per-block partials of the map and
     // of the sample energies) in one copy each
     unsigned int *done_host = nullptr;
-    // resident blocks of the persistent sweep kernel by tile rows (0: no
-    // cooperative launch on this device)
-    std::map<int, int64_t> persist_cap;
+    // blocks of the resident sweep kernel that the device holds at once, by
+    // tile rows and angle bytes (0: no cooperative launch on this device)
+    std::map<std::pair<int, int>, int64_t> persist_cap;
+    uint32_t halo_epoch = 0;          // resident launches since the halo words were cleared; 0: not cleared yet
     // sweeps run on a context-owned stream (captured into HIP graphs),
     // ordered after and before the caller's stream with two events
     hipStream_t gstream = nullptr;
     hipEvent_t ev_in = nullptr, ev_out = nullptr, ev_t0 = nullptr, ev_t1 = nullptr;
-    // tuned block shape (tile rows) by batch shape
-    std::map<std::tuple<int, int, int, int>, int> tuned_rows;
+    // tuned block shape by batch shape
+    // (shapes before `next` are timed; a run too short to time them all goes
+    // on in the next call)
+    struct Tuned {
+        int next = 0, best = -1;
+        float ms = 0.0f;
+    };
+    std::map<std::tuple<int, int, int, int>, Tuned> tuned_rows;
     // profiling
     bool profile = false;
     double prof_ms = 0.0;
@@ -2512,9 +2971,12 @@ struct Shape {
     int rows;
     bool compact;
     bool fused;
-    bool persist;  // fused sweeps, many per cooperative launch (sweep_tile_persist_kernel)
+    bool persist;  // fused sweeps, many per cooperative launch (sweep_resident_kernel)
 };
-constexpr int kNumShapes = 18;
+// The last two are not values of mpr_params.tile_rows: they are the resident
+// shapes of chains whose 32-row tiles the GPU does not hold at once.
+constexpr int kNumShapes = 20;
+constexpr int kNumParamShapes = 18;
 constexpr int kNumPlainShapes = 4;
 constexpr int kNumUnfusedShapes = 7;   // the shapes of double-precision chains
 constexpr Shape kShapes[kNumShapes] = {{1, false, false}, {2, false, false}, {4, false, false}, {8, false, false},
@@ -2522,12 +2984,22 @@ constexpr Shape kShapes[kNumShapes] = {{1, false, false}, {2, false, false}, {4,
                                        {16, false, true}, {24, false, true}, {32, false, true},
                                        {48, false, true}, {8, false, true},  {12, false, true},
                                        {8, false, true, true},  {12, false, true, true}, {16, false, true, true},
-                                       {24, false, true, true}, {32, false, true, true}};
+                                       {24, false, true, true}, {32, false, true, true},
+                                       {48, false, true, true}, {kResMaxRows, false, true, true}};
+// Block prefix sums are kept once for every number of tile rows: the
+// resident shapes of 8 to 48 rows share those of the fused shapes, and the
+// 64-row one takes the place of the 8-row one.
+constexpr int kNumStarts = 18;
+constexpr int start_of(int k)
+{
+    constexpr int same[kNumShapes] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 11, 12, 7, 8, 9, 10, 13};
+    return same[k];
+}
 constexpr int kDefaultShape = 2;  // plain, 4 half-rows
 
 int tile_code(const Shape &sh)
 {
-    return sh.rows | (sh.compact ? MPR_TILE_COMPACT : 0) | (sh.fused ? MPR_TILE_FUSED : 0) |
+    return (sh.persist ? std::min(sh.rows, 32) : sh.rows) | (sh.compact ? MPR_TILE_COMPACT : 0) | (sh.fused ? MPR_TILE_FUSED : 0) |
            (sh.persist ? MPR_TILE_PERSIST : 0);
 }
 
@@ -2535,7 +3007,7 @@ int tile_code(const Shape &sh)
 // MPR_TILE_FUSED | MPR_TILE_PERSIST), or -1.
 int shape_of(int tile)
 {
-    for (int k = 0; k < kNumShapes; ++k)
+    for (int k = 0; k < kNumParamShapes; ++k)
         if (tile == tile_code(kShapes[k])) return k;
     return -1;
 }
@@ -2620,7 +3092,7 @@ int64_t sim_bytes(const mpr_image *imgs, int n, const mpr_params *p)
     const int64_t chains = (int64_t)n * p->R;
     b += round_up(chains * (int64_t)sizeof(ChainDesc), 256) + round_up(chains * (int64_t)sizeof(ChainState), 256);
     b += round_up(chains * 8, 256) + round_up((int64_t)n * sizeof(ImgDev), 256) + 4096;
-    b += round_up(kNumShapes * (chains + 1) * 8, 256) + round_up(chains * 4 + 4, 256);
+    b += round_up(kNumStarts * (chains + 1) * 8, 256) + round_up(chains * 4 + 4, 256);
     for (int i = 0; i < n; ++i) b += redo_bytes(imgs[i].nx, imgs[i].ny, p->R);
     return b;
 }
@@ -2680,7 +3152,7 @@ int64_t table_bytes(const mpr_image *imgs, int n, const mpr_params *p)
     best += round_up(chains * (int64_t)sizeof(ChainDesc), 256) + round_up(chains * (int64_t)sizeof(ChainState), 256);
     best += round_up(chains * 8, 256) + round_up((int64_t)n * sizeof(ImgDev), 256) + 4096;
     best += round_up((int64_t)n * kMapBlocks * 16, 256);
-    best += round_up(kNumShapes * (chains + 1) * 8, 256) + round_up(chains * 4 + 4, 256);
+    best += round_up(kNumStarts * (chains + 1) * 8, 256) + round_up(chains * 4 + 4, 256);
     int64_t rb = 0;
     for (int i = 0; i < n; ++i) {
         const TableGrid t = table_grid(imgs[i], p);
@@ -2776,7 +3248,7 @@ struct ChainSet {
     int64_t *d_offset = nullptr;
     // the chains a sweep launch covers (those not done when the launch list
     // was last built): block prefix sums per shape and chain ids
-    int64_t *d_start[kNumShapes] = {};
+    int64_t *d_start[kNumStarts] = {};
     int32_t *d_ids = nullptr;
     int n_active = 0;
     int64_t total_blocks[kNumShapes] = {};
@@ -2789,7 +3261,7 @@ struct ChainSet {
     int K = 0;
 };
 
-BlockMap block_map(const ChainSet &cs, int v) { return BlockMap{cs.d_start[v], cs.d_ids, cs.n_active, 0}; }
+BlockMap block_map(const ChainSet &cs, int v) { return BlockMap{cs.d_start[start_of(v)], cs.d_ids, cs.n_active, 0}; }
 
 template <int ROWS>
 void launch_half_rows(hipStream_t st, const ChainSet &cs, int v, bool table, int colour, const SweepConsts &sc)
@@ -2929,63 +3401,71 @@ void launch_tile(hipStream_t st, const ChainSet &cs, int v, int mode, const Swee
     }
 }
 
-template <int TH>
-const void *persist_kernel() { return reinterpret_cast<const void *>(&sweep_tile_persist_kernel<TH>); }
+template <typename RT, int TH>
+const void *resident_kernel()
+{
+    static_assert((int64_t)kResMaxBlocks * res_halo_words<RT, TH>() * 8 <= (int64_t)kHaloBytes, "halo words");
+    return reinterpret_cast<const void *>(&sweep_resident_kernel<RT, TH>);
+}
 
-const void *persist_kernel_of(int rows)
+// The resident kernel of a number of tile rows, null where there is none
+// (tall tiles of doubles would leave no room for a second block on a CU).
+const void *resident_kernel_of(int rows, bool fp64)
 {
     switch (rows) {
-        case 8: return persist_kernel<8>();
-        case 12: return persist_kernel<12>();
-        case 16: return persist_kernel<16>();
-        case 24: return persist_kernel<24>();
-        default: return persist_kernel<32>();
+        case 8: return fp64 ? resident_kernel<double, 8>() : resident_kernel<float, 8>();
+        case 12: return fp64 ? resident_kernel<double, 12>() : resident_kernel<float, 12>();
+        case 16: return fp64 ? resident_kernel<double, 16>() : resident_kernel<float, 16>();
+        case 24: return fp64 ? resident_kernel<double, 24>() : resident_kernel<float, 24>();
+        case 32: return fp64 ? resident_kernel<double, 32>() : resident_kernel<float, 32>();
+        case 48: return fp64 ? nullptr : resident_kernel<float, 48>();
+        case kResMaxRows: return fp64 ? nullptr : resident_kernel<float, kResMaxRows>();
+        default: return nullptr;
     }
 }
 
-// Blocks of the persistent sweep kernel (tile rows `rows`) that the device
-// holds at once, 0 without cooperative launches; cached on the context.
-int64_t persist_capacity(mpr_ctx *ctx, int rows)
+// Blocks of the resident sweep kernel that the device holds at once, 0
+// without cooperative launches; cached on the context.
+int64_t persist_capacity(mpr_ctx *ctx, int rows, bool fp64)
 {
-    auto it = ctx->persist_cap.find(rows);
+    const auto key = std::make_pair(rows, fp64 ? 8 : 4);
+    auto it = ctx->persist_cap.find(key);
     if (it != ctx->persist_cap.end()) return it->second;
     int coop = 0, cus = 0, per_cu = 0;
     int64_t cap = 0;
-    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, ctx->device) == hipSuccess && coop &&
+    const void *f = resident_kernel_of(rows, fp64);
+    if (f && hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, ctx->device) == hipSuccess && coop &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persist_kernel_of(rows), kPersistThreads, 0) ==
-            hipSuccess)
-        cap = (int64_t)per_cu * cus;
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, kResThreads, 0) == hipSuccess)
+        cap = std::min<int64_t>((int64_t)per_cu * cus, kResMaxBlocks);
     (void)hipGetLastError();
-    ctx->persist_cap[rows] = cap;
+    ctx->persist_cap[key] = cap;
     return cap;
 }
 
-// Up to `count` fused sweeps of every listed chain in persistent shape v,
-// in one cooperative launch (the barrier generation cleared first).
-hipError_t launch_persist(hipStream_t st, const ChainSet &cs, int v, const SweepConsts &sc, const FusedControl &ctl,
-                          unsigned int *gen, unsigned int *abort_word, unsigned long long *slots, int count,
-                          uint32_t need, uint64_t wait_ticks)
+// Up to rc.count fused sweeps of every listed chain in resident shape v, in
+// one cooperative launch.
+hipError_t launch_resident(mpr_ctx *ctx, hipStream_t st, const ChainSet &cs, int v, const SweepConsts &sc,
+                           const CtlParams &cp, ResidentCtl rc)
 {
-    hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(kBlock), 0, st, gen, nullptr, nullptr, slots,
-                       (int)cs.desc.size() * 4);
+    if (ctx->halo_epoch == 0 || ctx->halo_epoch + 1 >= kResEpochs) {
+        // no word may hold the tag of a later launch
+        hipLaunchKernelGGL(clear_halo_kernel, dim3(512), dim3(kBlock), 0, st, rc.halo, (int64_t)kHaloBytes / 8);
+        ctx->halo_epoch = 0;
+    }
+    rc.epoch = ++ctx->halo_epoch << kResSweepBits;
+    hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(kBlock), 0, st, rc.gen, nullptr, nullptr, rc.sums,
+                       3 * kResMaxBlocks);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    ChainDesc *descs = cs.d_desc;
+    const ChainDesc *descs = cs.d_desc;
     ChainState *states = cs.d_state;
     BlockMap bm = block_map(cs, v);
     SweepConsts scc = sc;
-    FusedControl fc = ctl;
-    PersistCtl pc;
-    pc.gen = gen;
-    pc.abort = abort_word;
-    pc.slots = slots;
-    pc.wait_ticks = wait_ticks;
-    pc.count = count;
-    pc.need = need;
-    void *args[] = {&descs, &states, &bm, &scc, &fc, &pc};
-    return hipLaunchCooperativeKernel(persist_kernel_of(kShapes[v].rows), dim3((unsigned)cs.total_blocks[v]),
-                                      dim3(kPersistThreads), args, 0, st);
+    CtlParams cpp = cp;
+    void *args[] = {&descs, &states, &bm, &scc, &cpp, &rc};
+    return hipLaunchCooperativeKernel(resident_kernel_of(kShapes[v].rows, cs.fp64), dim3((unsigned)cs.total_blocks[v]),
+                                      dim3(kResThreads), args, 0, st);
 }
 
 // Builds the launch list of a chain set from the chains in `active`: block
@@ -2995,9 +3475,10 @@ int set_active(mpr_ctx *ctx, ChainSet &cs, const std::vector<int32_t> &active, h
 {
     const int n = (int)cs.desc.size();
     const int na = (int)active.size();
-    cs.h_start.assign((size_t)kNumShapes * (n + 1), 0);
+    cs.h_start.assign((size_t)kNumStarts * (n + 1), 0);
     for (int k = 0; k < kNumShapes; ++k) {
-        int64_t *sk = cs.h_start.data() + (size_t)k * (n + 1);
+        int64_t *sk = cs.h_start.data() + (size_t)start_of(k) * (n + 1);
+        sk[0] = 0;
         for (int j = 0; j < na; ++j) sk[j + 1] = sk[j] + chain_blocks(cs.desc[active[j]], k);
         cs.total_blocks[k] = sk[na];
         if (sk[na] >= ((int64_t)1 << 31)) return fail(ctx, MPR_ERR_ARG, "batch too large for one launch");
@@ -3028,7 +3509,6 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     unsigned long long *d_work = reinterpret_cast<unsigned long long *>((char *)ctx->scratch + kWorkOffset);
     unsigned int *d_gen = reinterpret_cast<unsigned int *>((char *)ctx->scratch + kGenOffset);
     unsigned int *d_abort = reinterpret_cast<unsigned int *>((char *)ctx->scratch + kAbortOffset);
-    unsigned long long *d_slots = reinterpret_cast<unsigned long long *>((char *)ctx->scratch + kSlotsOffset);
     hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(kBlock), 0, stream, d_done, d_abort, d_ticket, nullptr, 0);
     HIP_TRY(ctx, hipGetLastError());
     unsigned int already = 0;
@@ -3068,19 +3548,29 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     // control in its last block instead (unless states are recorded); or two
     // half-sweeps, the colour-1 redo kernel running the control unless the
     // states are recorded (or the chains are double precision).
-    // The persistent shapes: single-precision chains whose tiles the device
-    // holds at once, states not recorded (nothing runs between the sweep and
-    // the control).
+    // The resident shapes: chain sets whose tiles the device holds at once.
     auto persist_ok = [&](int v) {
-        return kShapes[v].persist && fuse && !table && n <= kPersistMaxChains && cs.total_blocks[v] > 0 &&
-               cs.total_blocks[v] <= persist_capacity(ctx, kShapes[v].rows);
+        return kShapes[v].persist && cs.total_blocks[v] > 0 &&
+               cs.total_blocks[v] <= persist_capacity(ctx, kShapes[v].rows, cs.fp64);
     };
-    const uint32_t need = (uint32_t)(n - (int)already);
-    const uint64_t wait_ticks = p->barrier_timeout_us > 0 ? (uint64_t)p->barrier_timeout_us * 100u : kPersistWaitTicks;
+    ResidentCtl rc0;
+    std::memset(&rc0, 0, sizeof rc0);
+    rc0.gen = d_gen;
+    rc0.abort = d_abort;
+    rc0.sums = reinterpret_cast<unsigned long long *>((char *)ctx->scratch + kSlotsOffset);
+    rc0.halo = reinterpret_cast<unsigned long long *>((char *)ctx->scratch + kScratchBytes);
+    rc0.done_count = d_done;
+    rc0.work = d_work;
+    rc0.states_out = cs.states_out;
+    rc0.offsets = cs.d_offset;
+    rc0.states_n_total = cs.states_n_total;
+    rc0.wait_ticks = p->barrier_timeout_us > 0 ? (uint64_t)p->barrier_timeout_us * 100u : kPersistWaitTicks;
+    rc0.K = cs.K;
     hipError_t perr = hipSuccess;
     auto sweeps = [&](int v, int count) {
         if (kShapes[v].persist) {
-            perr = launch_persist(st, cs, v, sc, fc, d_gen, d_abort, d_slots, count, need, wait_ticks);
+            rc0.count = count;
+            perr = launch_resident(ctx, st, cs, v, sc, cp, rc0);
             return;
         }
         for (int i = 0; i < count; ++i) {
@@ -3111,8 +3601,8 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         if (perr != hipSuccess) return fail(ctx, MPR_ERR_HIP, "persistent sweep launch: %s", hipGetErrorString(perr));
         HIP_TRY(ctx, hipGetLastError());
         HIP_TRY(ctx, hipEventRecord(ctx->ev_t1, st));
-        // the done counter; after a persistent launch the words up to the
-        // abort word, in one copy (done counter, generation, abort word)
+        // the done counter; after a resident launch the words up to the
+        // abort word, in one copy (done counter, sweeps run, abort word)
         HIP_TRY(ctx, hipMemcpyAsync(ctx->done_host, d_done,
                                     kShapes[v].persist ? (size_t)(kAbortOffset + 4) : sizeof(unsigned int),
                                     hipMemcpyDeviceToHost, st));
@@ -3121,7 +3611,7 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
             if (ctx->done_host[kAbortOffset / 4] != 0u)
                 return fail(ctx, MPR_ERR_HIP, "persistent sweep: a block timed out at the grid barrier");
             // the launch stops early once every chain is done
-            count = (int)(ctx->done_host[kGenOffset / 4] & 0x7FFFFFFFu);
+            count = (int)ctx->done_host[kGenOffset / 4];
         }
         float ms = 0.0f;
         HIP_TRY(ctx, hipEventElapsedTime(&ms, ctx->ev_t0, ctx->ev_t1));
@@ -3135,14 +3625,23 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         return MPR_OK;
     };
 
-    // block shape: fixed, cached, or tuned on the first sweeps (the table
-    // chains take the plain shapes, double-precision chains every unfused one)
+    // block shape: fixed, cached, or tuned on the first sweeps.  The one
+    // launch per sweep shapes of table chains are the plain ones, those of
+    // double-precision chains every unfused one; the resident ones follow.
     const int n_shapes = table ? kNumPlainShapes : (cs.fp64 ? kNumUnfusedShapes : kNumShapes);
     int v = p->tile_rows ? shape_of(p->tile_rows) : -1;
     if (v >= n_shapes) v = kDefaultShape;
-    // a persistent shape that does not apply here: its rows, one launch per sweep
+    // a resident shape whose tiles the device does not hold at once: the
+    // smallest taller one it does, or else its rows, one launch per sweep
     auto usable = [&](int k) { return k < 0 || !kShapes[k].persist || persist_ok(k); };
-    if (!usable(v)) v = shape_of(kShapes[v].rows | MPR_TILE_FUSED);
+    auto fallback = [&](int k) {
+        if (usable(k)) return k;
+        for (int t = k + 1; t < kNumShapes; ++t)
+            if (persist_ok(t)) return t;
+        if (table || cs.fp64) return kDefaultShape;
+        return shape_of(std::min(kShapes[k].rows, 48) | MPR_TILE_FUSED);
+    };
+    if (v >= 0) v = fallback(v);
     int maxnx = 0, maxny = 0;
     for (const auto &d : cs.desc) {
         maxnx = std::max(maxnx, d.nx);
@@ -3151,38 +3650,48 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     const auto key = std::make_tuple((table ? 1 : 0) | (cs.fp64 ? 2 : 0), n, maxnx, maxny);
     float sweep_ms = -1.0f;
     if (v < 0) {
-        auto it = ctx->tuned_rows.find(key);
-        if (it != ctx->tuned_rows.end()) v = usable(it->second) ? it->second
-                                                                 : shape_of(kShapes[it->second].rows | MPR_TILE_FUSED);
-    }
-    if (v < 0) {
+        // Where the tiles fit on the GPU only the resident shapes are timed:
+        // they take 4.4 us per 64^2 sweep, 8.4 us per 1024^2 one and 28.7 us
+        // per 2048^2 one (one chain), one launch per sweep 13.4, 27.4 and
+        // 41.3 us at best.
+        bool resident = false;
+        for (int k = 0; k < kNumShapes; ++k) resident = resident || persist_ok(k);
+        mpr_ctx::Tuned &tn = ctx->tuned_rows[key];
         const int ts = std::max(1, std::min(poll_every, 3));
-        float best = 0.0f;
-        int tried = 0;
-        for (int k = 0; k < n_shapes && !finished && done_sweeps + ts <= max_sweeps; ++k, ++tried) {
-            if (!usable(k)) continue;
-            // time per sweep; a persistent launch over more sweeps, so that
-            // its one launch does not weigh on the comparison
-            if (kShapes[k].persist) {
+        unsigned int done_before = 0;
+        for (; tn.next < kNumShapes && !finished && done_sweeps + ts <= max_sweeps; ++tn.next) {
+            const int k = tn.next;
+            if (!(resident ? persist_ok(k) : !kShapes[k].persist && k < n_shapes)) continue;
+            if (resident) {
                 // an untimed first launch (the first of a kernel costs more)
                 int rc = block(k, 1, nullptr, nullptr);
                 if (rc) return rc;
+                done_before = *ctx->done_host;
                 if (finished || done_sweeps + ts > max_sweeps) break;
             }
-            const int tk = kShapes[k].persist ? (int)std::min<int64_t>(4 * ts, max_sweeps - done_sweeps) : ts;
+            // (more sweeps in a resident launch, so that its start and end
+            // weigh less in the comparison)
+            const int tk = resident ? (int)std::min<int64_t>(2 * ts, max_sweeps - done_sweeps) : ts;
             float ms = 0.0f;
             const int64_t before = done_sweeps;
             int rc = block(k, tk, nullptr, &ms);
             if (rc) return rc;
+            // chains that finished meanwhile make the sweeps cheaper: timed again
+            if (resident && *ctx->done_host != done_before) break;
             ms /= (float)std::max<int64_t>(1, done_sweeps - before);
-            if (v < 0 || ms < best) {
-                best = ms;
-                v = k;
+            if (tn.best < 0 || ms < tn.ms) {
+                tn.ms = ms;
+                tn.best = k;
             }
         }
-        if (v < 0) v = kDefaultShape;
-        else sweep_ms = best;
-        if (tried == n_shapes) ctx->tuned_rows[key] = v;
+        if (tn.best >= 0) {
+            v = fallback(tn.best);
+            sweep_ms = tn.ms;
+        } else {
+            v = kDefaultShape;
+            for (int k = 0; k < kNumShapes; ++k)
+                if (persist_ok(k)) v = k;
+        }
     }
     if (!table) ctx->last_tile = tile_code(kShapes[v]);
     // sweeps per graph: at least about a millisecond of work per done-check
@@ -3269,10 +3778,10 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
 int upload_starts(mpr_ctx *ctx, ChainSet &cs, Carver &cv, hipStream_t stream)
 {
     const int n = (int)cs.desc.size();
-    int64_t *d = (int64_t *)cv.take((int64_t)kNumShapes * (n + 1) * 8);
+    int64_t *d = (int64_t *)cv.take((int64_t)kNumStarts * (n + 1) * 8);
     cs.d_ids = (int32_t *)cv.take((int64_t)n * 4 + 4);
     if (!d || !cs.d_ids) return fail(ctx, MPR_ERR_WORKSPACE, "workspace too small");
-    for (int k = 0; k < kNumShapes; ++k) cs.d_start[k] = d + (size_t)k * (n + 1);
+    for (int k = 0; k < kNumStarts; ++k) cs.d_start[k] = d + (size_t)k * (n + 1);
     int64_t words = 0, blocks = 0;
     for (int k = 0; k < kNumShapes; ++k) {
         int64_t b = 0;
@@ -3452,7 +3961,7 @@ int32_t mpr_create(mpr_ctx **out, int32_t device)
         ctx->static_ws = nullptr;
         (void)hipGetLastError();
     }
-    if (hipMalloc(&ctx->scratch, kScratchBytes) != hipSuccess ||
+    if (hipMalloc(&ctx->scratch, kScratchBytes + kHaloBytes) != hipSuccess ||
         hipHostMalloc((void **)&ctx->done_host, kHostStageBytes, hipHostMallocDefault) != hipSuccess ||
         hipStreamCreateWithFlags(&ctx->gstream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->ev_in, hipEventDisableTiming) != hipSuccess ||
@@ -3668,7 +4177,7 @@ int32_t mpr_estimate_temperature(mpr_ctx *ctx, const mpr_image *imgs, int32_t n,
     auto table_chain_bytes = [&](int b) {
         const int64_t hg = round_up(half_grid_bytes(tg[b].nx, tg[b].ny, teb), 256);
         return nT * 2 * hg + redo_bytes(tg[b].nx, tg[b].ny, nT) +
-               nT * (int64_t)(sizeof(ChainDesc) + sizeof(ChainState) + 8 + (kNumShapes + 1) * 8) + 4096;
+               nT * (int64_t)(sizeof(ChainDesc) + sizeof(ChainState) + 8 + (kNumStarts + 1) * 8) + 4096;
     };
     for (size_t first = 0; first < missing.size();) {
         // as many grid sizes as fit (at least one: the workspace holds the largest)

@@ -1,0 +1,87 @@
+"""GPU: sweeps that keep their tiles on the chip (many per launch) against
+one half-sweep launch at a time, bit for bit: double-precision chains, the
+e(T, L) table chains, recorded states and tiles of 48 and 64 rows, at the
+edges of the tiles (a single site wide, one tile, one row or column beyond a
+tile, several ragged tiles)."""
+import numpy as np
+import pytest
+
+import paper_1811_01604_amd as mpr
+import synth
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture()
+def ctx():
+    assert torch.cuda.is_available()
+    c = mpr.Context(0)
+    yield c
+    c.close()
+
+
+def image(ctx, ny, nx, p=0.6):
+    z = torch.from_numpy(synth.matern_field(nx, ny, 0.5, 0.2, 50.0, 10.0, 3).astype(np.float32)).cuda().flatten()
+    mk = torch.from_numpy(synth.random_mask(nx, ny, p, 4)).cuda().flatten()
+    imgs = mpr.images([(ny, nx)])
+    phi = torch.zeros_like(z)
+    ctx.map_to_angles(imgs, z, mk, phi)
+    return imgs, mk, phi
+
+
+def run(ctx, imgs, phi, mk, T, tile, record=False, **kw):
+    prm = mpr.default_params(tile_rows=tile, **kw)
+    ws = torch.empty(ctx.workspace_size(imgs, prm), dtype=torch.uint8, device="cuda")
+    ps = torch.zeros_like(phi)
+    m2 = torch.zeros_like(phi) if prm.spread else None
+    states = torch.zeros(prm.R * prm.K * phi.numel(), device="cuda") if record else None
+    st = ctx.simulate(imgs, phi, mk, np.array([T]), prm, ws, ps, phi_m2=m2, phi_states=states)
+    out = [ps, m2, states]
+    return [o.cpu().numpy().tobytes() for o in out if o is not None], st
+
+
+@pytest.mark.parametrize("fp64", [0, 1])
+@pytest.mark.parametrize("ny,nx", [(2, 1), (1, 300), (8, 128), (9, 129), (33, 127), (65, 257), (200, 131)])
+def test_resident_sweeps_equal_half_sweeps(ctx, ny, nx, fp64):
+    """The tuned shape (a resident one at these sizes) with spread and
+    recorded states, twice: the first call also tries the other shapes."""
+    imgs, mk, phi = image(ctx, ny, nx) if ny * nx > 2 else (mpr.images([(2, 1)]),
+                                                            torch.tensor([1, 0], dtype=torch.uint8, device="cuda"),
+                                                            torch.tensor([1.0, 0.0], device="cuda"))
+    for T in (2e-3, 0.05):
+        kw = dict(R=3, K=5, spread=1, fp64=fp64, record=True)
+        ref = run(ctx, imgs, phi, mk, T, 4, **kw)
+        for _ in range(2):
+            assert run(ctx, imgs, phi, mk, T, 0, **kw) == ref
+        assert ctx.profile_read()["last_tile"] & mpr.TILE_PERSIST
+
+
+@pytest.mark.parametrize("ny,nx", [(1500, 2048), (2048, 2047)])
+def test_resident_tiles_of_48_and_64_rows(ctx, ny, nx):
+    """Chains whose 32-row tiles do not fit on the GPU at once take 48 or 64 rows."""
+    imgs, mk, phi = image(ctx, ny, nx)
+    kw = dict(R=1, K=3, fixed_relax=6, spread=1)
+    ref = run(ctx, imgs, phi, mk, 0.05, 48 | mpr.TILE_FUSED, **kw)
+    assert run(ctx, imgs, phi, mk, 0.05, 32 | mpr.TILE_FUSED | mpr.TILE_PERSIST, **kw) == ref
+    assert ctx.profile_read()["last_tile"] == 32 | mpr.TILE_FUSED | mpr.TILE_PERSIST
+
+
+@pytest.mark.parametrize("q", [0.5, 0.25])
+@pytest.mark.parametrize("ny,nx", [(1, 40), (16, 16), (70, 150), (257, 255)])
+def test_resident_table_chains_equal_half_sweeps(ny, nx, q):
+    """The temperature from table chains run in the tuned shapes and in the
+    plain 4-row shape: the same energies, so the same number."""
+    assert torch.cuda.is_available()
+    got = []
+    for tile in (4, 0):
+        ctx = mpr.Context(0)
+        imgs, mk, phi = image(ctx, ny, nx, 0.3)
+        prm = mpr.default_params(tile_rows=tile, q=q, fp64=0 if q == 0.5 else 1, table_nT=8, table_T_lo=1e-4,
+                                 table_T_hi=2.0, table_burn=40, table_meas=30)
+        ws = torch.empty(ctx.workspace_size(imgs, prm), dtype=torch.uint8, device="cuda")
+        e_s, T, cl = ctx.estimate_temperature(imgs, phi, mk, prm, ws)
+        got.append((e_s[0], T[0], cl[0]))
+        ctx.close()
+    assert got[0] == got[1]
