@@ -631,39 +631,46 @@ __global__ __launch_bounds__(kBlock) void half_sweep_compact_kernel(const ChainD
     half_sweep_compact_body<DIAG, CR>(descs, states, bm, colour, sc, or_only, rd, flags);
 }
 
-__device__ void set_derived(ChainState &st, double q)
+// The quotients that the control of sweep t needs: 1 + e = (H + N_GP) / N_GP
+// with H + N_GP = sum over bonds of (1 - cos), the acceptance ratio and
+// (t + 1) / k_a.
+struct ControlRatios {
+    double ope, A, ta;
+};
+__device__ __forceinline__ ControlRatios control_ratios(const ChainState &st, const ChainDesc &d, const CtlParams &cp)
 {
-    st.inv_T = (float)(1.0 / st.T);
-    st.dscale = (float)(kTwoPi * q / st.a_cur);
+    return {(double)st.e_fx * cp.e_unit / (double)d.ngp, (double)st.acc / (double)d.P,
+            (double)(st.sweep + 1u) / cp.k_a};
+}
+
+// Work counters: chain-sweeps, gap-site updates, useful bytes.
+__device__ __forceinline__ void count_work(const ChainDesc &d, const CtlParams &cp, unsigned long long *work)
+{
+    atomicAdd(&work[0], 1ull);
+    atomicAdd(&work[1], (unsigned long long)d.P);
+    atomicAdd(&work[2], (unsigned long long)(cp.angle_bytes * ((int64_t)d.nx * d.ny + d.P)));
 }
 
 // Algorithm 2 steps 5.2-5.5 (relaxation), 6 (equilibrium states) and the
 // e(T, L) runs for a chain not done, after both colours of a sweep, on its
 // state `st` (in place) with its sums e_fx and acc of that sweep.  The done
 // counter (and the work counters) are skipped where null; `slope` gives the
-// energy slope at sweep t once the ring buffer holds its energy.
+// energy slope at sweep t once the ring buffer holds its energy.  (1 / T stays
+// as the host set it.)
 template <class Slope>
 __device__ __forceinline__ void control_core(ChainState &st, const ChainDesc &d, const CtlParams &cp,
-                                             unsigned int *done_count, unsigned long long *work, Slope slope)
+                                             const ControlRatios &r, unsigned int *done_count,
+                                             unsigned long long *work, Slope slope)
 {
-    if (work) {
-        // work counters: chain-sweeps, gap-site updates, useful bytes
-        atomicAdd(&work[0], 1ull);
-        atomicAdd(&work[1], (unsigned long long)d.P);
-        atomicAdd(&work[2], (unsigned long long)(cp.angle_bytes * ((int64_t)d.nx * d.ny + d.P)));
-    }
+    if (work) count_work(d, cp, work);
     const uint32_t t = st.sweep;
-    const unsigned long long acc = st.acc, efx = st.e_fx;
     st.acc = 0ull;
     st.e_fx = 0ull;
-    // 1 + e = (H + N_GP) / N_GP with H + N_GP = sum over bonds of (1 - cos)
-    const double ope = (double)efx * cp.e_unit / (double)d.ngp;
     if (st.phase == PH_RELAX) {
-        const double A = (double)acc / (double)d.P;
-        if (A < cp.a_targ) st.a_relax = 1.0 + (double)(t + 1u) / cp.k_a;
-        st.ring[t % (uint32_t)cp.n_fit] = ope;
+        if (r.A < cp.a_targ) st.a_relax = 1.0 + r.ta;
+        st.ring[t % (uint32_t)cp.n_fit] = r.ope;
         if (t >= (uint32_t)cp.n_fit && t % (uint32_t)cp.n_f == 0u) st.k = slope(t);
-        st.A_last = A;
+        st.A_last = r.A;
         const uint32_t tn = t + 1u;
         st.sweep = tn;
         bool stop;
@@ -693,14 +700,13 @@ __device__ __forceinline__ void control_core(ChainState &st, const ChainDesc &d,
             st.inv_km1_d = 1.0 / (double)(k - 1);
         }
     } else {  // PH_TABLE
-        const double A = (double)acc / (double)d.P;
-        if (A < cp.a_targ) st.a_relax = 1.0 + (double)(t + 1u) / cp.k_a;
+        if (r.A < cp.a_targ) st.a_relax = 1.0 + r.ta;
         st.a_cur = st.a_relax;
-        if ((int64_t)t >= (int64_t)cp.burn) st.e_sum += ope;
+        if ((int64_t)t >= (int64_t)cp.burn) st.e_sum += r.ope;
         st.sweep = t + 1u;
         if ((int64_t)t + 1 >= (int64_t)cp.burn + cp.meas) st.phase = PH_DONE;
     }
-    set_derived(st, cp.q);
+    st.dscale = (float)(kTwoPi * cp.q / st.a_cur);
     if (st.phase == PH_DONE && done_count) atomicAdd(done_count, 1u);
 }
 
@@ -713,7 +719,7 @@ __device__ __forceinline__ void control_chain(const ChainDesc *__restrict__ desc
     ChainState &st = states[c];
     if (st.phase == PH_DONE) return;
     const ChainDesc d = descs[c];
-    control_core(st, d, cp, done_count, work, [&](uint32_t t) { return ring_slope(st.ring, t, cp.n_fit, cp.w); });
+    control_core(st, d, cp, control_ratios(st, d, cp), done_count, work, [&](uint32_t t) { return ring_slope(st.ring, t, cp.n_fit, cp.w); });
 }
 
 // The deferred double-precision updates of one half-sweep (block shape
@@ -1464,6 +1470,36 @@ __device__ __forceinline__ void res_publish(unsigned long long *p, uint32_t tag,
     st_agent64(p + 1, ((unsigned long long)tag << 32) | (uint32_t)__double2hiint(v));
 }
 
+// Sum over a wave in lane 63, by row shifts and row broadcasts on the vector
+// unit (a butterfly through LDS takes 6 round trips of some 100 cycles).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_get(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void dpp_step(unsigned long long &e, uint32_t &a)
+{
+    const uint32_t lo = dpp_get<CTRL, ROWS>((uint32_t)e), hi = dpp_get<CTRL, ROWS>((uint32_t)(e >> 32));
+    e += ((unsigned long long)hi << 32) | lo;
+    a += dpp_get<CTRL, ROWS>(a);
+}
+__device__ __forceinline__ void wave_sum_63(unsigned long long &e, uint32_t &a)
+{
+    dpp_step<0x111, 0xF>(e, a);  // row_shr:1
+    dpp_step<0x112, 0xF>(e, a);  // row_shr:2
+    dpp_step<0x114, 0xF>(e, a);  // row_shr:4
+    dpp_step<0x118, 0xF>(e, a);  // row_shr:8
+    dpp_step<0x142, 0xA>(e, a);  // row_bcast:15 into rows 1 and 3
+    dpp_step<0x143, 0xC>(e, a);  // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ unsigned long long readlane64(unsigned long long v, int lane)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
 // ring_slope by a whole wave: lane j loads the j-th value (the newest is
 // `newest`, not yet in the ring), the sum runs in the same order.
 __device__ __forceinline__ double ring_slope_wave(const double *ring, double newest, uint32_t t, int n_fit,
@@ -1681,11 +1717,20 @@ __device__ __forceinline__ void resident_tile(ResidentShared<RT, TH> &L, ChainSt
         bool have = true;  // the halo of this sweep is in LDS
         if (due) {
             if (phase == PH_EQ) {
+                // temperature and a stay as they are: the control's
+                // divisions (1 us on one lane) wait until the chain is left,
+                // unless the squared deviations need its 1 / k
                 have = nblk == 1;
                 if (tid == 0) {
-                    L.st.e_fx = L.st.acc = 0ull;
-                    control_core(L.st, d, cp, lead ? rc.done_count : nullptr, lead ? rc.work : nullptr,
-                                 [](uint32_t) { return 0.0; });
+                    if (L.st.eq_left > 1 && i < rc.count && !m20p) {
+                        L.st.sweep += 1u;
+                        L.st.eq_left -= 1;
+                        if (lead) count_work(d, cp, rc.work);
+                    } else {
+                        L.st.e_fx = L.st.acc = 0ull;
+                        control_core(L.st, d, cp, control_ratios(L.st, d, cp), lead ? rc.done_count : nullptr, lead ? rc.work : nullptr,
+                                     [](uint32_t) { return 0.0; });
+                    }
                 }
             } else if (wid == 0) {
                 // the chain's sums of the last sweep
@@ -1721,19 +1766,23 @@ __device__ __forceinline__ void resident_tile(ResidentShared<RT, TH> &L, ChainSt
                         ac += (uint32_t)(v[k] >> 46) & 0x3FFFu;
                     }
                 }
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) {
-                    e += __shfl_xor(e, off);
-                    ac += __shfl_xor(ac, off);
-                }
+                wave_sum_63(e, ac);
+                e = readlane64(e, 63);
+                ac = (uint32_t)__builtin_amdgcn_readlane((int)ac, 63);
                 const uint32_t t = L.st.sweep;
+                // the control's three quotients by one division, a lane each
+                const double num = lane == 0 ? (double)e * cp.e_unit : lane == 1 ? (double)(unsigned long long)ac : (double)(t + 1u);
+                const double den = lane == 0 ? (double)d.ngp : lane == 1 ? (double)d.P : cp.k_a;
+                const unsigned long long quo = (unsigned long long)__double_as_longlong(num / den);
+                ControlRatios ratios;
+                ratios.ope = __longlong_as_double((long long)readlane64(quo, 0));
+                ratios.A = __longlong_as_double((long long)readlane64(quo, 1));
+                ratios.ta = __longlong_as_double((long long)readlane64(quo, 2));
                 double slope = 0.0;
                 if (phase == PH_RELAX && t >= (uint32_t)cp.n_fit && t % (uint32_t)cp.n_f == 0u)
-                    slope = ring_slope_wave(L.st.ring, (double)e * cp.e_unit / (double)d.ngp, t, cp.n_fit, L.w, lane);
+                    slope = ring_slope_wave(L.st.ring, ratios.ope, t, cp.n_fit, L.w, lane);
                 if (lane == 0) {
-                    L.st.e_fx = e;
-                    L.st.acc = ac;
-                    control_core(L.st, d, cp, lead ? rc.done_count : nullptr, lead ? rc.work : nullptr,
+                    control_core(L.st, d, cp, ratios, lead ? rc.done_count : nullptr, lead ? rc.work : nullptr,
                                  [&](uint32_t) { return slope; });
                 }
             } else if (i < rc.count) {
@@ -1852,12 +1901,8 @@ __device__ __forceinline__ void resident_tile(ResidentShared<RT, TH> &L, ChainSt
                 }
                 unsigned long long es = e_thread;
                 uint32_t as = acc_thread;
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) {
-                    es += __shfl_xor(es, off);
-                    as += __shfl_xor(as, off);
-                }
-                if (lane == 0) {
+                wave_sum_63(es, as);
+                if (lane == 63) {
                     L.red_e[wid] = es;
                     L.red_a[wid] = as;
                 }
@@ -1867,14 +1912,16 @@ __device__ __forceinline__ void resident_tile(ResidentShared<RT, TH> &L, ChainSt
         if (L.fail) break;
         due = true;
         if (nblk > 1) {
-            if (tid == 0 && !eq) {
-                unsigned long long e = 0ull, a = 0ull;
-                for (int w = 0; w < kResWaves; ++w) {
-                    e += L.red_e[w];
-                    a += L.red_a[w];
-                }
+            if (wid == 0 && !eq) {
+                unsigned long long e = lane < kResWaves ? L.red_e[lane & (kResWaves - 1)] : 0ull;
+                uint32_t a = lane < kResWaves ? L.red_a[lane & (kResWaves - 1)] : 0u;
+                dpp_step<0x111, 0xF>(e, a);  // the sum over lanes 0 to 7 in lane 7
+                dpp_step<0x112, 0xF>(e, a);
+                dpp_step<0x114, 0xF>(e, a);
                 const unsigned long long tag = (((uint32_t)i >> 1) & 7u) + 1u;
-                st_agent64(rc.sums + (int64_t)(i & 1) * kResMaxBlocks + slot, e | (a << 46) | (tag << 60));
+                if (lane == kResWaves - 1)
+                    st_agent64(rc.sums + (int64_t)(i & 1) * kResMaxBlocks + slot,
+                               e | ((unsigned long long)a << 46) | (tag << 60));
             }
             publish1((i + 1) & 1, rc.epoch | (uint32_t)(i + 2));
         }
