@@ -122,60 +122,72 @@ __device__ double ring_slope(const double *ring, uint32_t t, int n_fit, const do
 }
 
 // (fp64: the chains hold doubles; a gap starts at 2 pi u in double, as in
-// the plain definition.)
-__global__ void init_chains_kernel(const ChainDesc *__restrict__ descs, const int64_t *__restrict__ offsets,
-                                   const float *__restrict__ phi, const uint8_t *__restrict__ sampled,
-                                   const float *__restrict__ phi_init, uint32_t seed_lo, uint32_t seed_hi,
-                                   int table_mode, int fp64)
+// the plain definition.)  Every word of the half-grids is written, zeros in
+// the padding beyond a row's sites: a thread takes four half-columns of one
+// row and colour, so that its stores are whole 16-byte groups and no memset
+// goes before (two or four per chain: 768 of them took 3 ms of a 24-image,
+// 192-chain batch).  Bound by those writes; 4096^2, 16 chains: 927 us before,
+// 790 us now.
+template <typename RT>
+__global__ __launch_bounds__(kBlock) void init_chains_kernel(const ChainDesc *__restrict__ descs,
+                                                             const int64_t *__restrict__ offsets,
+                                                             const float *__restrict__ phi,
+                                                             const uint8_t *__restrict__ sampled,
+                                                             const float *__restrict__ phi_init, uint32_t seed_lo,
+                                                             uint32_t seed_hi, int table_mode)
 {
+    typedef RT v4 __attribute__((ext_vector_type(4)));
     const ChainDesc d = descs[blockIdx.y];
-    const int64_t n = (int64_t)d.nx * d.ny;
     const int64_t off = offsets[blockIdx.y];
+    const uint32_t nq = (uint32_t)d.S >> 2;
+    const int64_t n = (int64_t)d.ny * nq * 2;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int y = (int)(i / d.nx);
-        const int x = (int)(i - (int64_t)y * d.nx);
-        const int c = (x + y) & 1;
-        const int h = x >> 1;
-        double v;
-        bool fixed = false;
-        if (table_mode) {
-            v = kPi;
-        } else if (sampled[off + i]) {
-            v = (double)fabsf(phi[off + i]);
-            fixed = true;
-        } else if (phi_init) {
-            // a given start is reduced into [0, 2 pi) with its sign bit clear
-            // (a set sign bit marks a sampled site; -0.0 included)
-            v = (double)phi_init[off + i];
-            if (!(v >= 0.0 && v < kTwoPi)) {
-                v -= kTwoPi * floor(v / kTwoPi);
-                if (!(v >= 0.0 && v < kTwoPi)) v = 0.0;
+        // the two colours of a row one after the other, groups along the row
+        const uint32_t yc = (uint32_t)(i / nq);
+        const int q = (int)(i - (int64_t)yc * nq), y = (int)(yc >> 1), c = (int)(yc & 1u);
+        const int s = (y + c) & 1;
+        v4 out = {(RT)0, (RT)0, (RT)0, (RT)0};
+        U4 w = {0u, 0u, 0u, 0u};
+        for (int e = 0; e < 4; ++e) {
+            const int x = 2 * (4 * q + e) + s;
+            // two neighbouring sites of a colour share one Philox call
+            if (!table_mode && !phi_init && (e & 1) == 0) {
+                const U4 ctr = {(uint32_t)y * (uint32_t)d.nx + ((uint32_t)x & ~2u), kInitSweep, d.chain, d.image_id};
+                w = philox4x32_10(ctr, seed_lo, seed_hi);
             }
-            v = fabs(v);
-            if (!fp64 && (float)v >= 6.28318548f) v = 6.28318501;  // the largest float below 2 pi
-        } else {
-            U4 ctr = {(uint32_t)y * (uint32_t)d.nx + ((uint32_t)x & ~2u), kInitSweep, d.chain, d.image_id};
-            const U4 w = philox4x32_10(ctr, seed_lo, seed_hi);
-            const uint32_t word = ((x >> 1) & 1) ? w.z : w.x;
-            v = kTwoPi * (double)unit24(word);
+            if (x >= d.nx) continue;
+            const int64_t j = off + (int64_t)y * d.nx + x;
+            double v;
+            bool fixed = false;
+            if (table_mode) {
+                v = kPi;
+            } else if (sampled[j]) {
+                v = (double)fabsf(phi[j]);
+                fixed = true;
+            } else if (phi_init) {
+                // a given start is reduced into [0, 2 pi) with its sign bit clear
+                // (a set sign bit marks a sampled site; -0.0 included)
+                v = (double)phi_init[j];
+                if (!(v >= 0.0 && v < kTwoPi)) {
+                    v -= kTwoPi * floor(v / kTwoPi);
+                    if (!(v >= 0.0 && v < kTwoPi)) v = 0.0;
+                }
+                v = fabs(v);
+                if (sizeof(RT) == 4 && (float)v >= 6.28318548f) v = 6.28318501;  // the largest float below 2 pi
+            } else {
+                v = kTwoPi * (double)unit24((e & 1) ? w.z : w.x);
+            }
+            if constexpr (sizeof(RT) == 8) out[e] = fixed ? mark_fixed_d(v) : v;
+            else out[e] = fixed ? mark_fixed((float)v) : (float)v;
         }
-        const int64_t j = (int64_t)y * d.S + h;
+        const int64_t j = (int64_t)y * d.S + 4 * q;
+        const v4 zero = {(RT)0, (RT)0, (RT)0, (RT)0};
         // select by value: indexing the descriptor with c would put it in memory
-        float *hp = c ? d.h[1] : d.h[0];
-        float *ap = c ? d.acc[1] : d.acc[0];
-        float *mp = c ? d.m2[1] : d.m2[0];
-        if (fp64) {
-            ((double *)hp)[j] = fixed ? mark_fixed_d(v) : v;
-            if (ap) ((double *)ap)[j] = 0.0;
-            if (mp) ((double *)mp)[j] = 0.0;
-        } else {
-            const float hv = fixed ? mark_fixed((float)v) : (float)v;
-            hp[j] = hv;
-            float *h2 = c ? d.h2[1] : d.h2[0];
-            if (h2) h2[j] = hv;
-            if (ap) ap[j] = 0.0f;
-            if (mp) mp[j] = 0.0f;
-        }
+        *(v4 *)((RT *)(c ? d.h[1] : d.h[0]) + j) = out;
+        RT *h2 = (RT *)(c ? d.h2[1] : d.h2[0]), *ap = (RT *)(c ? d.acc[1] : d.acc[0]), *mp = (RT *)(c ? d.m2[1] : d.m2[0]);
+        if (h2) *(v4 *)(h2 + j) = out;
+        if (ap) *(v4 *)(ap + j) = zero;
+        if (mp) *(v4 *)(mp + j) = zero;
     }
 }
 
@@ -842,6 +854,65 @@ __global__ __launch_bounds__(kBlock) void redo_fp64_kernel(const ChainDesc *__re
     if (threadIdx.x == 0) *ctl.ticket = 0u;
 }
 
+// Relaxed device-scope loads (coherent between the XCDs).
+__device__ __forceinline__ uint32_t ld_agent(const unsigned int *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ unsigned long long ld_agent64(const unsigned long long *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Sum over a wave in lane 63, by row shifts and row broadcasts on the vector
+// unit (a butterfly through LDS takes 6 round trips of some 100 cycles).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_get(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void dpp_step(unsigned long long &e, uint32_t &a)
+{
+    const uint32_t lo = dpp_get<CTRL, ROWS>((uint32_t)e), hi = dpp_get<CTRL, ROWS>((uint32_t)(e >> 32));
+    e += ((unsigned long long)hi << 32) | lo;
+    a += dpp_get<CTRL, ROWS>(a);
+}
+__device__ __forceinline__ void wave_sum_63(unsigned long long &e, uint32_t &a)
+{
+    dpp_step<0x111, 0xF>(e, a);  // row_shr:1
+    dpp_step<0x112, 0xF>(e, a);  // row_shr:2
+    dpp_step<0x114, 0xF>(e, a);  // row_shr:4
+    dpp_step<0x118, 0xF>(e, a);  // row_shr:8
+    dpp_step<0x142, 0xA>(e, a);  // row_bcast:15 into rows 1 and 3
+    dpp_step<0x143, 0xC>(e, a);  // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ unsigned long long readlane64(unsigned long long v, int lane)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+// ring_slope by a whole wave: lane j loads the j-th value (the newest is
+// `newest`, not yet in the ring), the sum runs in the same order.
+__device__ __forceinline__ double ring_slope_wave(const double *ring, double newest, uint32_t t, int n_fit,
+                                                  const double *w, int lane)
+{
+    const int j0 = lane < n_fit ? lane : 0;
+    const double r = j0 == n_fit - 1 ? newest : ring[(t + 1u + (uint32_t)j0) % (uint32_t)n_fit];
+    const double wl = w[j0];
+    const int rl = __double2loint(r), rh = __double2hiint(r), wlo = __double2loint(wl), whi = __double2hiint(wl);
+    double s = 0.0;
+    for (int j = 0; j < n_fit; ++j) {
+        const double rj = __hiloint2double(__builtin_amdgcn_readlane(rh, j), __builtin_amdgcn_readlane(rl, j));
+        const double wj = __hiloint2double(__builtin_amdgcn_readlane(whi, j), __builtin_amdgcn_readlane(wlo, j));
+        s += wj * rj;
+    }
+    return s;
+}
+
 // ================================================================ fused tile sweep
 // A whole sweep in one launch.  A block stages one tile of both colours in
 // LDS: TH rows x 2 kTileH columns of the grid (kTileH half-columns per
@@ -871,12 +942,10 @@ __global__ __launch_bounds__(kBlock) void redo_fp64_kernel(const ChainDesc *__re
 constexpr int kTileH = 64;                // half-columns per tile and colour
 constexpr int kTileLS = kTileH + 8;       // LDS row: half-columns hx0 - 4 .. hx0 + kTileH + 3
 constexpr int kTileNW = kBlock / 64;      // waves per block
-// Fused sweeps of at most this many blocks run the control themselves: each
-// block then ends with a device-scope fence (a write-back of its XCD's L2)
-// and a ticket; measured, that saves the control kernel's node in a 1024^2
-// one-chain sweep (344 blocks: 38 -> 34 us per sweep) but costs ~37 us per
-// sweep at 2752 blocks (4096^2, one chain).
-constexpr int64_t kTileCtlMaxBlocks = 512;
+// Fused sweeps of at most this many blocks run the control themselves (a
+// chain's last block, found by a returning atomic that every block waits for
+// at its end).  
+constexpr int64_t kTileCtlMaxBlocks = 16384;
 
 // The double-precision decision of one tile site (colour c, local row r,
 // half-column j) from its LDS inputs: the steps of redo_fp64_kernel.  Kept
@@ -1196,67 +1265,93 @@ __device__ __forceinline__ void tile_sweep_body(TileShared<TH> &L, const ChainDe
 }
 
 // The block's bond energy and accepted count added to its chain (energy in
-// 16-bit halves, so that the 32-bit lane sums cannot carry out).  Called by
-// every thread of the block.
+// 16-bit halves, so that the 32-bit lane sums cannot carry out).  With
+// `arrive` the accepted counter also counts the chain's blocks in its upper
+// bits, and the value it had before this block is returned to wave 0.  Called
+// by every thread of the block.
+constexpr int kArriveShift = 40;  // a chain has at most 2^31 sites
 template <int TH>
-__device__ __forceinline__ void tile_block_sums(TileShared<TH> &L, uint64_t e_thread, uint32_t acc_thread,
-                                                unsigned long long *e_sum, unsigned long long *acc_sum)
+__device__ __forceinline__ unsigned long long tile_block_sums(TileShared<TH> &L, uint64_t e_thread, uint32_t acc_thread,
+                                                              unsigned long long *e_sum, unsigned long long *acc_sum,
+                                                              bool wanted, bool arrive)
 {
     const int tid = (int)threadIdx.x;
-    uint32_t lo = (uint32_t)(e_thread & 0xFFFFu), hi = (uint32_t)(e_thread >> 16), ac = acc_thread;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        lo += __shfl_xor(lo, off);
-        hi += __shfl_xor(hi, off);
-        ac += __shfl_xor(ac, off);
-    }
     constexpr int NW = kTileNW;
     const int wid = tid >> 6;
-    if ((tid & 63) == 0) {
-        L.red[0][wid] = lo;
-        L.red[1][wid] = hi;
-        L.red[2][wid] = ac;
+    if (wanted) {
+        uint32_t lo = (uint32_t)(e_thread & 0xFFFFu), hi = (uint32_t)(e_thread >> 16), ac = acc_thread;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            lo += __shfl_xor(lo, off);
+            hi += __shfl_xor(hi, off);
+            ac += __shfl_xor(ac, off);
+        }
+        if ((tid & 63) == 0) {
+            L.red[0][wid] = lo;
+            L.red[1][wid] = hi;
+            L.red[2][wid] = ac;
+        }
     }
     __syncthreads();
+    unsigned long long before = 0ull;
     if (tid == 0) {
         unsigned long long e = 0ull, a = 0ull;
-        for (int i = 0; i < NW; ++i) {
-            e += ((unsigned long long)L.red[1][i] << 16) + L.red[0][i];
-            a += L.red[2][i];
+        if (wanted)
+            for (int i = 0; i < NW; ++i) {
+                e += ((unsigned long long)L.red[1][i] << 16) + L.red[0][i];
+                a += L.red[2][i];
+            }
+        if (arrive) {
+            // the energy is added before the block counts as arrived: the
+            // first addition's result is waited for
+            if (e) {
+                const unsigned long long old = atomicAdd(e_sum, e);
+                __asm__ volatile("" ::"v"((uint32_t)old), "v"((uint32_t)(old >> 32)) : "memory");
+            }
+            before = atomicAdd(acc_sum, a | (1ull << kArriveShift)) + a;
+        } else {
+            if (e) atomicAdd(e_sum, e);
+            if (a) atomicAdd(acc_sum, a);
         }
-        if (e) atomicAdd(e_sum, e);
-        if (a) atomicAdd(acc_sum, a);
     }
+    return before;
 }
 
-// The work of the last block of a sweep: h and h2 of every swept chain
-// exchanged (the chain's `swapped` flag toggled), then the per-sweep control
-// of all chains.  Called by every thread of that block.
-__device__ __forceinline__ void swap_and_control(ChainDesc *descs, ChainState *states, const BlockMap &bm,
-                                                 const FusedControl &ctl)
+// The end of a chain's sweep, by wave 0 of its last block: h and h2 exchanged
+// (the chain's `swapped` flag toggled) and the per-sweep control, from the
+// chain's energy and accepted count.  Only the next launch reads h2, so no
+// fence is needed.
+__device__ __forceinline__ void chain_end(ChainDesc &dd, ChainState &st, const ChainDesc &d, unsigned long long acc,
+                                          const FusedControl &ctl)
 {
-    const int tid = (int)threadIdx.x;
-    for (int k = tid; k < bm.n; k += kBlock) {
-        const int c = bm.id[k];
-        if (states[c].phase == PH_DONE) continue;
-        ChainDesc &dd = descs[c];
-        float *t0 = dd.h[0], *t1 = dd.h[1];
-        dd.h[0] = dd.h2[0];
-        dd.h[1] = dd.h2[1];
-        dd.h2[0] = t0;
-        dd.h2[1] = t1;
-        states[c].swapped ^= 1;
+    const int lane = (int)(threadIdx.x & 63);
+    const unsigned long long e = ld_agent64(&st.e_fx);
+    const uint32_t t = st.sweep;
+    // the control's three quotients by one division, a lane each
+    const double num = lane == 0 ? (double)e * ctl.cp.e_unit : lane == 1 ? (double)acc : (double)(t + 1u);
+    const double den = lane == 0 ? (double)d.ngp : lane == 1 ? (double)d.P : ctl.cp.k_a;
+    const unsigned long long quo = (unsigned long long)__double_as_longlong(num / den);
+    ControlRatios r;
+    r.ope = __longlong_as_double((long long)readlane64(quo, 0));
+    r.A = __longlong_as_double((long long)readlane64(quo, 1));
+    r.ta = __longlong_as_double((long long)readlane64(quo, 2));
+    double slope = 0.0;
+    if (st.phase == PH_RELAX && t >= (uint32_t)ctl.cp.n_fit && t % (uint32_t)ctl.cp.n_f == 0u)
+        slope = ring_slope_wave(st.ring, r.ope, t, ctl.cp.n_fit, ctl.cp.w, lane);
+    if (lane == 0) {
+        dd.h[0] = d.h2[0];
+        dd.h[1] = d.h2[1];
+        dd.h2[0] = d.h[0];
+        dd.h2[1] = d.h[1];
+        st.swapped ^= 1;
+        control_core(st, d, ctl.cp, r, ctl.done_count, ctl.work, [&](uint32_t) { return slope; });
     }
-    __syncthreads();
-    for (int c = tid; c < ctl.n_all; c += kBlock)
-        control_chain(descs, states, c, ctl.cp, ctl.done_count, ctl.work);
 }
 
-// With `ctl.on` (launches of a few thousand blocks, where one ticket counter
-// costs little) the last block to finish also exchanges h and h2 of the
-// swept chains and runs the per-sweep control, which saves the control
-// kernel's launch in each sweep of a small fill; it finds out that it is last
-// from the ticket counter, which it resets.
+// With `ctl.on` a chain's last block to finish also ends its sweep
+// (chain_end), which saves the control kernel: the blocks of a chain count
+// themselves in the upper bits of its accepted counter, so that no counter is
+// shared between chains.
 template <bool DIAG, int TH>
 __global__ __launch_bounds__(kBlock) void sweep_tile_kernel(ChainDesc *__restrict__ descs,
                                                             ChainState *__restrict__ states, BlockMap bm,
@@ -1290,20 +1385,18 @@ __global__ __launch_bounds__(kBlock) void sweep_tile_kernel(ChainDesc *__restric
             tile_sweep_body<DIAG, TH, true>(L, d, ss, y0, hx0, mode, sc, or_only, flags, e_thread, acc_thread);
         else
             tile_sweep_body<DIAG, TH, false>(L, d, ss, y0, hx0, mode, sc, or_only, flags, e_thread, acc_thread);
-        if (phase != PH_EQ) tile_block_sums(L, e_thread, acc_thread, &stp->e_fx, &stp->acc);
+        const bool arrive = ctl.on != 0;
+        if (arrive || phase != PH_EQ) {
+            unsigned long long before = tile_block_sums(L, e_thread, acc_thread, &stp->e_fx, &stp->acc,
+                                                        phase != PH_EQ, arrive);
+            if (arrive && tid < 64) {
+                before = readlane64(before, 0);
+                const unsigned long long blocks = (unsigned long long)nbx * (unsigned long long)((d.ny + TH - 1) / TH);
+                if ((before >> kArriveShift) == blocks - 1ull)
+                    chain_end(descs[cid], states[cid], d, before & ((1ull << kArriveShift) - 1ull), ctl);
+            }
+        }
     }
-    if (!ctl.on) return;
-    __shared__ int last;
-    __syncthreads();
-    if (tid == 0) {
-        __threadfence();
-        last = atomicAdd(ctl.ticket, 1u) == gridDim.x - 1u;
-    }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();  // the other blocks' sums and stores are visible
-    swap_and_control(descs, states, bm, ctl);
-    if (tid == 0) *ctl.ticket = 0u;
 }
 
 // Many fused sweeps per cooperative launch (which guarantees that every block
@@ -1374,16 +1467,6 @@ constexpr int kResMaxRows = 64;
 template <typename RT> constexpr int res_words() { return (int)sizeof(RT) / 4; }
 template <typename RT, int TH> constexpr int res_halo_len() { return 4 * kTileH + 2 * TH; }
 template <typename RT, int TH> constexpr int res_halo_words() { return 3 * res_halo_len<RT, TH>() * res_words<RT>(); }
-
-__device__ __forceinline__ uint32_t ld_agent(const unsigned int *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ unsigned long long ld_agent64(const unsigned long long *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 __device__ __forceinline__ void st_agent64(unsigned long long *p, unsigned long long v)
 {
@@ -1468,54 +1551,6 @@ __device__ __forceinline__ void res_publish(unsigned long long *p, uint32_t tag,
 {
     st_agent64(p, ((unsigned long long)tag << 32) | (uint32_t)__double2loint(v));
     st_agent64(p + 1, ((unsigned long long)tag << 32) | (uint32_t)__double2hiint(v));
-}
-
-// Sum over a wave in lane 63, by row shifts and row broadcasts on the vector
-// unit (a butterfly through LDS takes 6 round trips of some 100 cycles).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t dpp_get(uint32_t x)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ void dpp_step(unsigned long long &e, uint32_t &a)
-{
-    const uint32_t lo = dpp_get<CTRL, ROWS>((uint32_t)e), hi = dpp_get<CTRL, ROWS>((uint32_t)(e >> 32));
-    e += ((unsigned long long)hi << 32) | lo;
-    a += dpp_get<CTRL, ROWS>(a);
-}
-__device__ __forceinline__ void wave_sum_63(unsigned long long &e, uint32_t &a)
-{
-    dpp_step<0x111, 0xF>(e, a);  // row_shr:1
-    dpp_step<0x112, 0xF>(e, a);  // row_shr:2
-    dpp_step<0x114, 0xF>(e, a);  // row_shr:4
-    dpp_step<0x118, 0xF>(e, a);  // row_shr:8
-    dpp_step<0x142, 0xA>(e, a);  // row_bcast:15 into rows 1 and 3
-    dpp_step<0x143, 0xC>(e, a);  // row_bcast:31 into rows 2 and 3
-}
-__device__ __forceinline__ unsigned long long readlane64(unsigned long long v, int lane)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
-    return ((unsigned long long)hi << 32) | lo;
-}
-
-// ring_slope by a whole wave: lane j loads the j-th value (the newest is
-// `newest`, not yet in the ring), the sum runs in the same order.
-__device__ __forceinline__ double ring_slope_wave(const double *ring, double newest, uint32_t t, int n_fit,
-                                                  const double *w, int lane)
-{
-    const int j0 = lane < n_fit ? lane : 0;
-    const double r = j0 == n_fit - 1 ? newest : ring[(t + 1u + (uint32_t)j0) % (uint32_t)n_fit];
-    const double wl = w[j0];
-    const int rl = __double2loint(r), rh = __double2hiint(r), wlo = __double2loint(wl), whi = __double2hiint(wl);
-    double s = 0.0;
-    for (int j = 0; j < n_fit; ++j) {
-        const double rj = __hiloint2double(__builtin_amdgcn_readlane(rh, j), __builtin_amdgcn_readlane(rl, j));
-        const double wj = __hiloint2double(__builtin_amdgcn_readlane(whi, j), __builtin_amdgcn_readlane(wlo, j));
-        s += wj * rj;
-    }
-    return s;
 }
 
 // The launch of one tile: block `slot` of the launch, block lb of the nblk
@@ -3592,11 +3627,11 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     // A sweep: the fused tile sweep, then control_kernel with the swap of
     // h and h2 (and the control, unless the states are recorded in between);
     // a fused sweep of at most kTileCtlMaxBlocks blocks does the swap and the
-    // control in its last block instead (unless states are recorded); or two
+    // control in each chain's last block (unless states are recorded); or two
     // half-sweeps, the colour-1 redo kernel running the control unless the
     // states are recorded (or the chains are double precision).
     // The resident shapes: chain sets whose tiles the device holds at once.
-    auto persist_ok = [&](int v) {
+    auto fits = [&](int v) {
         return kShapes[v].persist && cs.total_blocks[v] > 0 &&
                cs.total_blocks[v] <= persist_capacity(ctx, kShapes[v].rows, cs.fp64);
     };
@@ -3623,7 +3658,7 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         for (int i = 0; i < count; ++i) {
             const bool fused = kShapes[v].fused;
             if (fused && fuse && cs.total_blocks[v] <= kTileCtlMaxBlocks) {
-                launch_tile<false>(st, cs, v, 0, sc, 0, nullptr, &fc);  // swap and control in its last block
+                launch_tile<false>(st, cs, v, 0, sc, 0, nullptr, &fc);  // swap and control in each chain's last block
             } else if (fused) {
                 launch_tile<false>(st, cs, v, 0, sc, 0, nullptr);
                 control(1, cs.states_out ? 0 : 1);
@@ -3680,11 +3715,11 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     if (v >= n_shapes) v = kDefaultShape;
     // a resident shape whose tiles the device does not hold at once: the
     // smallest taller one it does, or else its rows, one launch per sweep
-    auto usable = [&](int k) { return k < 0 || !kShapes[k].persist || persist_ok(k); };
+    auto usable = [&](int k) { return k < 0 || !kShapes[k].persist || fits(k); };
     auto fallback = [&](int k) {
         if (usable(k)) return k;
         for (int t = k + 1; t < kNumShapes; ++t)
-            if (persist_ok(t)) return t;
+            if (fits(t)) return t;
         if (table || cs.fp64) return kDefaultShape;
         return shape_of(std::min(kShapes[k].rows, 48) | MPR_TILE_FUSED);
     };
@@ -3702,13 +3737,13 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         // per 2048^2 one (one chain), one launch per sweep 13.4, 27.4 and
         // 41.3 us at best.
         bool resident = false;
-        for (int k = 0; k < kNumShapes; ++k) resident = resident || persist_ok(k);
+        for (int k = 0; k < kNumShapes; ++k) resident = resident || fits(k);
         mpr_ctx::Tuned &tn = ctx->tuned_rows[key];
         const int ts = std::max(1, std::min(poll_every, 3));
         unsigned int done_before = 0;
         for (; tn.next < kNumShapes && !finished && done_sweeps + ts <= max_sweeps; ++tn.next) {
             const int k = tn.next;
-            if (!(resident ? persist_ok(k) : !kShapes[k].persist && k < n_shapes)) continue;
+            if (!(resident ? fits(k) : !kShapes[k].persist && k < n_shapes)) continue;
             if (resident) {
                 // an untimed first launch (the first of a kernel costs more)
                 int rc = block(k, 1, nullptr, nullptr);
@@ -3737,7 +3772,7 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         } else {
             v = kDefaultShape;
             for (int k = 0; k < kNumShapes; ++k)
-                if (persist_ok(k)) v = k;
+                if (fits(k)) v = k;
         }
     }
     if (!table) ctx->last_tile = tile_code(kShapes[v]);
@@ -3764,8 +3799,10 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     hipGraphExec_t &ge = cap.exec;
     auto capture = [&]() {
         cap.release();
-        // (a persistent launch runs a whole group itself and is not captured)
-        if (graphs && !kShapes[v].persist && hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) == hipSuccess) {
+        // (a resident launch runs a whole group itself; a fused sweep is one or
+        // two launches of 20 us and more, which the host keeps ahead of, and
+        // capturing its graph anew whenever the list changes took 60 to 190 us)
+        if (graphs && !kShapes[v].fused && hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) == hipSuccess) {
             sweeps(v, spl);
             if (hipStreamEndCapture(st, &cap.graph) != hipSuccess ||
                 hipGraphInstantiate(&cap.exec, cap.graph, nullptr, nullptr, 0) != hipSuccess)
@@ -3807,6 +3844,19 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         if (active.empty() || 5 * blocks > 4 * cs.total_blocks[v]) continue;
         rc = set_active(ctx, cs, active, st);
         if (rc) break;
+        if (!p->tile_rows && !kShapes[v].persist) {
+            // the last chains of a set finish in one resident launch once
+            // they fit: in the lowest tiles that leave a CU for each block
+            // (1024^2: 8.4 us per sweep in 256 blocks, 10.3 in 512), else in
+            // the tallest
+            int best = -1;
+            for (int k = 0; k < kNumShapes; ++k)
+                if (fits(k) && (best < 0 || cs.total_blocks[best] > kResMaxBlocks / 2)) best = k;
+            if (best >= 0) {
+                v = best;
+                if (p->sweeps_per_launch <= 0) spl = 256;
+            }
+        }
         capture();
     }
     cap.release();
@@ -3915,6 +3965,21 @@ bool carve_chain(Carver &cv, ChainDesc &d, int nx, int ny, bool with_acc, bool w
             return false;
     }
     return true;
+}
+
+// Starting angles of every chain of a set (table: pi everywhere).
+void launch_init(hipStream_t stream, const ChainSet &cs, const float *phi, const uint8_t *sampled,
+                 const float *phi_init, uint64_t seed, int table)
+{
+    int64_t groups = 1;
+    for (const auto &d : cs.desc) groups = std::max(groups, (int64_t)d.ny * d.S / 2);
+    const dim3 grid(blocks_for(groups, 2048), (unsigned)cs.desc.size());
+    if (cs.fp64)
+        hipLaunchKernelGGL(init_chains_kernel<double>, grid, dim3(kBlock), 0, stream, cs.d_desc, cs.d_offset, phi,
+                           sampled, phi_init, (uint32_t)seed, (uint32_t)(seed >> 32), table);
+    else
+        hipLaunchKernelGGL(init_chains_kernel<float>, grid, dim3(kBlock), 0, stream, cs.d_desc, cs.d_offset, phi,
+                           sampled, phi_init, (uint32_t)seed, (uint32_t)(seed >> 32), table);
 }
 
 // Monotone (pool-adjacent-violators) fit of y, then log T interpolated
@@ -4256,8 +4321,7 @@ int32_t mpr_estimate_temperature(mpr_ctx *ctx, const mpr_image *imgs, int32_t n,
         }
         int rc = upload_chains(ctx, cs, cv, stream, p->q);
         if (rc) return rc;
-        hipLaunchKernelGGL(init_chains_kernel, dim3(blocks_for(maxn, 2048), (unsigned)cs.desc.size()), dim3(kBlock),
-                           0, stream, cs.d_desc, cs.d_offset, nullptr, nullptr, nullptr, 0u, 0u, 1, cs.fp64 ? 1 : 0);
+        launch_init(stream, cs, nullptr, nullptr, nullptr, 0u, 1);
         HIP_TRY(ctx, hipGetLastError());
         rc = run_chains(ctx, cs, p, stream, (int64_t)p->table_burn + p->table_meas, 50, true);
         if (rc) return rc;
@@ -4390,20 +4454,12 @@ static int32_t simulate_call(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, con
         for (int b = 0; b < n; ++b)
             cs.states_n_total = std::max(cs.states_n_total, imgs[b].offset + (int64_t)imgs[b].nx * imgs[b].ny);
     }
-    const int eb = cs.fp64 ? 8 : 4;
     int rc = upload_chains(ctx, cs, cv, stream, p->q, resume);
     if (rc) return rc;
     int64_t maxn = 0;
     for (int b = 0; b < n; ++b) maxn = std::max(maxn, (int64_t)imgs[b].nx * imgs[b].ny);
     if (!resume) {
-        for (auto &d : cs.desc)
-            for (int c = 0; c < 2; ++c) {
-                HIP_TRY(ctx, hipMemsetAsync(d.h[c], 0, half_grid_bytes(d.nx, d.ny, eb), stream));
-                if (d.h2[c]) HIP_TRY(ctx, hipMemsetAsync(d.h2[c], 0, half_grid_bytes(d.nx, d.ny, eb), stream));
-            }
-        hipLaunchKernelGGL(init_chains_kernel, dim3(blocks_for(maxn, 2048), (unsigned)cs.desc.size()), dim3(kBlock),
-                           0, stream, cs.d_desc, cs.d_offset, phi, sampled, phi_init, (uint32_t)p->seed,
-                           (uint32_t)(p->seed >> 32), 0, cs.fp64 ? 1 : 0);
+        launch_init(stream, cs, phi, sampled, phi_init, p->seed, 0);
         HIP_TRY(ctx, hipGetLastError());
     }
     // sweeps left to the run's cap (a resumed run has done `swept` of them),
@@ -4779,12 +4835,9 @@ int32_t mpr_diag_half_sweep(mpr_ctx *ctx, int32_t nx, int32_t ny, float *phi, co
         (void)hipFree(buf);
         return rc;
     }
-    (void)hipMemsetAsync(d.h[0], 0, hg, stream);
-    (void)hipMemsetAsync(d.h[1], 0, hg, stream);
     const int64_t nsite = (int64_t)nx * ny;
     // the gap values of phi are the starting state
-    hipLaunchKernelGGL(init_chains_kernel, dim3(blocks_for(nsite, 2048), 1), dim3(kBlock), 0, stream, cs.d_desc,
-                       cs.d_offset, phi, sampled, phi, 0u, 0u, 0, 0);
+    launch_init(stream, cs, phi, sampled, phi, 0u, 0);
     if (flags) (void)hipMemsetAsync(flags, 0, nsite, stream);
     const SweepConsts sc = make_sc(q, seed);
     const dim3 grid((unsigned)cs.total_blocks[v]);
