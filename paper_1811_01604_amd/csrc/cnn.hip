@@ -37,9 +37,7 @@ constexpr int NBLK = 8;
 constexpr int NLAYER = 2 + 2 * NBLK;
 constexpr int WSZ = 9 * CH * CH;            // weights per layer
 constexpr int LSZ = WSZ + CH;                // weights + bias per layer
-constexpr int TH = 8, TW = 32;               // output tile (rows x cols)
 constexpr int PIXS = 40;                     // staged pixel stride in bf16 (80 B)
-constexpr int IN_T = (TH + 2) * (TW + 2);    // staged input pixels
 constexpr int WG_BLOCKS = 256;               // persistent blocks of the weight-gradient kernel
 constexpr int WG_PART = WSZ + CH;            // floats per partial
 
@@ -59,25 +57,6 @@ struct ConvArgs {
     const uint8_t *sampled;
     float *phi_out;
 };
-
-// Stages the (TH+2) x (TW+2) input pixels around an output tile into LDS,
-// zero outside the image.
-__device__ __forceinline__ void stage_tile(const bf16 *__restrict__ src, bf16 *tile, int n, int H, int W, int y0,
-                                           int x0, const bf16 *__restrict__ ref)
-{
-    for (int k = threadIdx.x; k < IN_T * 4; k += blockDim.x) {
-        const int chunk = k & 3, pix = k >> 2;
-        const int r = pix / (TW + 2), c = pix - r * (TW + 2);
-        const int gy = y0 - 1 + r, gx = x0 - 1 + c;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (gy >= 0 && gy < H && gx >= 0 && gx < W) {
-            const int64_t off = (((int64_t)n * H + gy) * W + gx) * CH + chunk * 8;
-            v = *reinterpret_cast<const uint4 *>(src + off);
-            (void)ref;
-        }
-        *reinterpret_cast<uint4 *>(tile + pix * PIXS + chunk * 8) = v;
-    }
-}
 
 // Forward convolution (and, with the dgrad packing, the input gradient).
 // Persistent blocks of 4 waves loop over 16 x 32-pixel output tiles.  The
@@ -627,102 +606,217 @@ struct WgradArgs {
     const bf16 *in;     // layer input, N x H x W x 32
     const bf16 *gout;   // output gradient, N x H x W x 32
     const bf16 *gref;   // multiply gout by (gref > 0), or null
-    float *partial;     // [gridDim.x * 4][WG_PART]
+    float *partial;     // [gridDim.x][WG_PART]
     int N, H, W;
 };
 
 // Weight and bias gradients of one conv layer: dW[tap][ci][co] = sum over
-// pixels of in(p + tap)[ci] * gout(p)[co]; db[co] = sum of gout(p)[co].
-// Persistent blocks loop over output tiles; each wave accumulates its own
-// partial sums, written out per wave and reduced in a fixed order.
-__global__ __launch_bounds__(256) void conv3x3_wgrad_kernel(WgradArgs a)
+// pixels of in(p + tap)[ci] * gout(p)[co]; db[co] = sum of gout(p)[co], with
+// v_mfma_f32_32x32x16_bf16 taking 16 pixels of a row as the K dimension.  Both
+// operands need a channel's consecutive pixels in one lane, while a staged
+// pixel holds its channels side by side: ds_read_b64_tr_b16 reads four pixels
+// of 16 channels per 16 lanes and hands each lane one channel of them, so the
+// tiles stay as they lie in memory (64 bytes per pixel: 32 lanes read 256
+// contiguous bytes, without bank conflicts).  Persistent blocks of 8 waves,
+// one per CU, take 16 x 32-pixel tiles; a wave holds two rows' output
+// gradients and reads every input operand once for the up to two rows it
+// feeds.  The next tile's pixels are loaded into registers meanwhile.
+// Bound by memory (two tensors once): 32 images of 256^2 WG_AFTER us per
+// layer, sum of the partials included, against 466 us with 2-byte reads of
+// each operand element, a partial per wave and one thread per weight for the
+// sum.
+constexpr int WG_NT = 512;
+constexpr int WG_NW = WG_NT / 64;
+constexpr int WG_TH = 16, WG_TW = 32;
+constexpr int WG_IN_W = WG_TW + 2;
+constexpr int WG_IN_CHUNKS = (WG_TH + 2) * WG_IN_W * 4;   // 16-byte chunks of the staged input
+constexpr int WG_IPT = (WG_IN_CHUNKS + WG_NT - 1) / WG_NT;
+constexpr int WG_GPT = WG_TH * WG_TW * 4 / WG_NT;         // chunks of the staged gradient per thread
+constexpr int WG_ROUND = 3;                               // taps summed over the waves at a time
+
+typedef short v4i16 __attribute__((ext_vector_type(4)));
+
+// Four pixels (64 bytes apart) of this lane's channel, from the lane's
+// address of the transposed read.
+__device__ __forceinline__ v4i16 lds_tr(const bf16 *p)
 {
-    __shared__ __attribute__((aligned(16))) bf16 itile[IN_T * PIXS];
-    __shared__ __attribute__((aligned(16))) bf16 gtile[TH * TW * PIXS];
-    const int tiles_x = (a.W + TW - 1) / TW, tiles_y = (a.H + TH - 1) / TH;
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4i16 *)(p));
+}
+
+__device__ __forceinline__ bf16x8 lds_tr8(const bf16 *p)
+{
+    union {
+        v4i16 h[2];
+        bf16x8 v;
+    } u;
+    u.h[0] = lds_tr(p);
+    u.h[1] = lds_tr(p + 4 * CH);
+    return u.v;
+}
+
+// The two bfloat16 values of v, zero where those of ref are not positive.
+__device__ __forceinline__ uint32_t keep_positive(uint32_t v, uint32_t ref)
+{
+    return (__uint_as_float(ref << 16) > 0.0f ? v & 0xFFFFu : 0u) |
+           (__uint_as_float(ref & 0xFFFF0000u) > 0.0f ? v & 0xFFFF0000u : 0u);
+}
+
+template <bool REF>
+__global__ __launch_bounds__(WG_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv3x3_wgrad_kernel(WgradArgs a)
+{
+    __shared__ __attribute__((aligned(16))) bf16 itile[(WG_TH + 2) * WG_IN_W * CH];
+    __shared__ __attribute__((aligned(16))) bf16 gtile[WG_TH * WG_TW * CH];
+    __shared__ __attribute__((aligned(16))) float red[WG_NW * WG_ROUND * 512];
+    const int tiles_x = (a.W + WG_TW - 1) / WG_TW, tiles_y = (a.H + WG_TH - 1) / WG_TH;
     const int n_tiles = tiles_x * tiles_y * a.N;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m = lane & 31, kq = lane >> 5;
+    // this lane's place in a transposed read of 16 pixels x 32 channels
+    const int tr = (kq * 8 + ((lane & 15) >> 2)) * CH + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
     f32x16 acc[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[t][i] = 0.0f;
     float db = 0.0f;
-    for (int tile_id = blockIdx.x; tile_id < n_tiles; tile_id += gridDim.x) {
-        int b = tile_id;
-        const int tx = b % tiles_x;
-        b /= tiles_x;
-        const int ty = b % tiles_y;
-        const int n = b / tiles_y;
-        const int y0 = ty * TH, x0 = tx * TW;
-        __syncthreads();
-        stage_tile(a.in, itile, n, a.H, a.W, y0, x0, nullptr);
-        for (int k = threadIdx.x; k < TH * TW * 4; k += blockDim.x) {
-            const int chunk = k & 3, pix = k >> 2;
-            const int r = pix / TW, c = pix - r * TW;
-            const int gy = y0 + r, gx = x0 + c;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (gy < a.H && gx < a.W) {
-                const int64_t off = (((int64_t)n * a.H + gy) * a.W + gx) * CH + chunk * 8;
-                v = *reinterpret_cast<const uint4 *>(a.gout + off);
-                if (a.gref) {
-                    const uint4 rv = *reinterpret_cast<const uint4 *>(a.gref + off);
-                    const bf16 *rp = reinterpret_cast<const bf16 *>(&rv);
-                    bf16 *vp = reinterpret_cast<bf16 *>(&v);
-                    for (int j = 0; j < 8; ++j)
-                        if (!((float)rp[j] > 0.0f)) vp[j] = (bf16)0.0f;
-                }
-            }
-            *reinterpret_cast<uint4 *>(gtile + pix * PIXS + chunk * 8) = v;
+    uint4 pi[WG_IPT], pg[WG_GPT], pr[REF ? WG_GPT : 1];
+    uint32_t valid = 0u;
+    // every load is issued, from a clamped pixel where the tile leaves the
+    // image (its valid bit is cleared and zeros are stored)
+    auto load = [&](int tile) {
+        const int tx = tile % tiles_x, rest = tile / tiles_x, ty = rest % tiles_y, n = rest / tiles_y;
+        const int y0 = ty * WG_TH, x0 = tx * WG_TW;
+        valid = 0u;
+#pragma unroll
+        for (int j = 0; j < WG_IPT; ++j) {
+            const int k = min(tid + WG_NT * j, WG_IN_CHUNKS - 1), pix = k >> 2;
+            const int r = pix / WG_IN_W, c = pix - r * WG_IN_W;
+            const int gy = y0 - 1 + r, gx = x0 - 1 + c;
+            if (gy >= 0 && gy < a.H && gx >= 0 && gx < a.W) valid |= 1u << j;
+            const int64_t p = ((int64_t)n * a.H + min(max(gy, 0), a.H - 1)) * a.W + min(max(gx, 0), a.W - 1);
+            pi[j] = *reinterpret_cast<const uint4 *>(a.in + p * CH + (k & 3) * 8);
         }
-        __syncthreads();
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            const int row = wave * 2 + mt;
+        for (int j = 0; j < WG_GPT; ++j) {
+            const int k = tid + WG_NT * j, pix = k >> 2;
+            const int gy = y0 + pix / WG_TW, gx = x0 + pix % WG_TW;
+            if (gy < a.H && gx < a.W) valid |= 1u << (WG_IPT + j);
+            const int64_t p = ((int64_t)n * a.H + min(gy, a.H - 1)) * a.W + min(gx, a.W - 1);
+            pg[j] = *reinterpret_cast<const uint4 *>(a.gout + p * CH + (k & 3) * 8);
+            if (REF) pr[j] = *reinterpret_cast<const uint4 *>(a.gref + p * CH + (k & 3) * 8);
+        }
+    };
+    auto store = [&]() {
 #pragma unroll
-            for (int kc = 0; kc < 2; ++kc) {
-                // B[k = pixel][n = co]: lane holds co = m, pixels kc*16 + kq*8 .. +7 of this row
-                bf16x8 bv;
+        for (int j = 0; j < WG_IPT; ++j) {
+            const int k = tid + WG_NT * j;
+            if (k < WG_IN_CHUNKS) *reinterpret_cast<uint4 *>(itile + k * 8) = 
+                ((valid >> j) & 1u) ? pi[j] : make_uint4(0u, 0u, 0u, 0u);
+        }
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    bv[i] = gtile[(row * TW + kc * 16 + kq * 8 + i) * PIXS + m];
-                    db += (float)bv[i];
-                }
-#pragma unroll
-                for (int t = 0; t < 9; ++t) {
-                    const int dy = t / 3 - 1, dx = t % 3 - 1;
-                    // A[m = ci][k = pixel]: lane holds ci = m at the shifted pixels
-                    bf16x8 av;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-                        av[i] = itile[((row + 1 + dy) * (TW + 2) + kc * 16 + kq * 8 + i + 1 + dx) * PIXS + m];
-                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[t], 0, 0, 0);
-                }
+        for (int j = 0; j < WG_GPT; ++j) {
+            uint4 v = ((valid >> (WG_IPT + j)) & 1u) ? pg[j] : make_uint4(0u, 0u, 0u, 0u);
+            if (REF) {
+                v.x = keep_positive(v.x, pr[j].x);
+                v.y = keep_positive(v.y, pr[j].y);
+                v.z = keep_positive(v.z, pr[j].z);
+                v.w = keep_positive(v.w, pr[j].w);
             }
+            *reinterpret_cast<uint4 *>(gtile + (tid + WG_NT * j) * 8) = v;
+        }
+    };
+    // contiguous runs of tiles per XCD (blocks go round-robin to the 8 XCDs),
+    // so that the halo pixels tiles share are read through one L2
+    const int G = (int)gridDim.x, xcd = (int)blockIdx.x & 7;
+    int before = 0;
+    for (int x = 0; x < xcd; ++x) before += (G - x + 7) >> 3;
+    const int step = (G - xcd + 7) >> 3;
+    const int t_lo = (int)((int64_t)n_tiles * before / G), t_hi = (int)((int64_t)n_tiles * (before + step) / G);
+    int tile = t_lo + ((int)blockIdx.x >> 3);
+    if (tile < t_hi) load(tile);
+    for (; tile < t_hi; tile += step) {
+        __syncthreads();  // every wave is done with the last tile
+        store();
+        __syncthreads();
+        load(min(tile + step, t_hi - 1));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kc = 0; kc < 2; ++kc) {
+            // B[k = pixel][n = co]: this lane's channel m, pixels kc * 16 + kq * 8 .. + 7 of rows 2 wave, 2 wave + 1
+            bf16x8 g[2];
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                g[o] = lds_tr8(gtile + ((2 * wave + o) * WG_TW + kc * 16) * CH + tr);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) db += (float)g[o][i];
+            }
+#pragma unroll
+            for (int ir = 0; ir < 4; ++ir)
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) {
+                    // A[m = ci][k = pixel] of staged row 2 wave + ir, shifted by dx
+                    const bf16x8 x = lds_tr8(itile + ((2 * wave + ir) * WG_IN_W + kc * 16 + dx) * CH + tr);
+#pragma unroll
+                    for (int o = 0; o < 2; ++o) {
+                        const int dy = ir - o;
+                        if (dy < 0 || dy > 2) continue;
+                        acc[dy * 3 + dx] =
+                            __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, g[o], acc[dy * 3 + dx], 0, 0, 0);
+                    }
+                }
         }
     }
-    // D[m = ci][n = co]: lane holds co = m for ci = 8 (i/4) + 4 kq + (i%4)
-    float *part = a.partial + (int64_t)(blockIdx.x * 4 + wave) * WG_PART;
+    // the waves' sums added in a fixed order, half a tap's accumulators of
+    // WG_ROUND taps at a time; D[m = ci][n = co]: lane holds co = m for
+    // ci = 8 (i / 4) + 4 kq + (i % 4)
+    float *part = a.partial + (int64_t)blockIdx.x * WG_PART;
 #pragma unroll
-    for (int t = 0; t < 9; ++t)
+    for (int t0 = 0; t0 < 9; t0 += WG_ROUND)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int ci = 8 * (i >> 2) + 4 * kq + (i & 3);
-            part[(t * CH + ci) * CH + m] = acc[t][i];
+        for (int hf = 0; hf < 2; ++hf) {
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < WG_ROUND; ++t)
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    red[((wave * WG_ROUND + t) * 8 + i) * 64 + lane] = acc[t0 + t][hf * 8 + i];
+            __syncthreads();
+            for (int k = tid; k < WG_ROUND * 512; k += WG_NT) {
+                float s = 0.0f;
+#pragma unroll
+                for (int w = 0; w < WG_NW; ++w) s += red[w * WG_ROUND * 512 + k];
+                const int t = k >> 9, i = hf * 8 + ((k >> 6) & 7), l = k & 63;
+                const int ci = 8 * (i >> 2) + 4 * (l >> 5) + (i & 3);
+                part[((t0 + t) * CH + ci) * CH + (l & 31)] = s;
+            }
         }
     db += __shfl_xor(db, 32);
-    if (kq == 0) part[WSZ + m] = db;
+    __syncthreads();
+    if (kq == 0) red[wave * CH + m] = db;
+    __syncthreads();
+    if (tid < CH) {
+        float s = 0.0f;
+        for (int w = 0; w < WG_NW; ++w) s += red[w * CH + tid];
+        part[WSZ + tid] = s;
+    }
 }
 
-// grads[j] = sum over partials p of partial[p][j], in order.
-__global__ void wgrad_reduce_kernel(const float *__restrict__ partial, int n_parts, float *__restrict__ grads)
+// grads[j] = sum over partials p of partial[p][j]: 32 weights per block, 8
+// threads each (every eighth partial), their sums added in order.
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restrict__ partial, int n_parts,
+                                                           float *__restrict__ grads)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= WG_PART) return;
+    __shared__ float red[8][32];
+    const int c = (int)threadIdx.x & 31, g = (int)threadIdx.x >> 5;
+    const int j = (int)blockIdx.x * 32 + c;
     float s = 0.0f;
-    for (int p = 0; p < n_parts; ++p) s += partial[(int64_t)p * WG_PART + j];
-    grads[j] = s;
+    for (int p = g; p < n_parts; p += 8) s += partial[(int64_t)p * WG_PART + j];
+    red[g][c] = s;
+    __syncthreads();
+    if (g == 0) {
+        for (int k = 1; k < 8; ++k) s += red[k][c];
+        grads[j] = s;
+    }
 }
 
 // Network input: (cos q phi, sin q phi, 1) at sampled sites, zeros elsewhere.
@@ -849,8 +943,6 @@ int64_t act_bytes(int n, int h, int w) { return ((int64_t)n * h * w * CH * 2 + 2
 
 bool shape_ok(int n, int h, int w) { return n >= 1 && h >= 1 && w >= 1 && (int64_t)n * h * w <= ((int64_t)1 << 31); }
 
-int64_t conv_blocks(int n, int h, int w) { return (int64_t)n * ((h + TH - 1) / TH) * ((w + TW - 1) / TW); }
-
 void launch_conv(hipStream_t st, const bf16 *in, const bf16 *wpack, const float *bias, const bf16 *add,
                  const bf16 *ref, int relu, bf16 *out, int n, int h, int w)
 {
@@ -930,10 +1022,12 @@ void launch_wgrad(hipStream_t st, const bf16 *in, const bf16 *gout, const bf16 *
     a.N = n;
     a.H = h;
     a.W = w;
-    const int blocks = (int)std::min<int64_t>(WG_BLOCKS, conv_blocks(n, h, w));
-    hipLaunchKernelGGL(conv3x3_wgrad_kernel, dim3(blocks), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((WG_PART + 255) / 256), dim3(256), 0, st, partial, blocks * 4,
-                       grads);
+    const int64_t tiles = (int64_t)n * ((h + WG_TH - 1) / WG_TH) * ((w + WG_TW - 1) / WG_TW);
+    const int blocks = (int)std::min<int64_t>(WG_BLOCKS, tiles);
+    if (gref) hipLaunchKernelGGL(conv3x3_wgrad_kernel<true>, dim3(blocks), dim3(WG_NT), 0, st, a);
+    else hipLaunchKernelGGL(conv3x3_wgrad_kernel<false>, dim3(blocks), dim3(WG_NT), 0, st, a);
+    static_assert(WG_PART % 32 == 0, "whole blocks of the sum");
+    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(WG_PART / 32), dim3(256), 0, st, partial, blocks, grads);
 }
 
 // Activation buffers of a training forward pass inside the workspace.
