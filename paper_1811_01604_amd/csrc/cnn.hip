@@ -621,10 +621,10 @@ struct WgradArgs {
 // one per CU, take 16 x 32-pixel tiles; a wave holds two rows' output
 // gradients and reads every input operand once for the up to two rows it
 // feeds.  The next tile's pixels are loaded into registers meanwhile.
-// Bound by memory (two tensors once): 32 images of 256^2 WG_AFTER us per
-// layer, sum of the partials included, against 466 us with 2-byte reads of
-// each operand element, a partial per wave and one thread per weight for the
-// sum.
+// Bound by memory (two tensors once): 32 images of 256^2 take 62 us a layer
+// (4.3 TB/s) and the sum of the partials 11 us, against 227 and 239 us with
+// 2-byte reads of each operand element, a partial per wave and one thread per
+// weight for the sum.
 constexpr int WG_NT = 512;
 constexpr int WG_NW = WG_NT / 64;
 constexpr int WG_TH = 16, WG_TW = 32;
