@@ -79,6 +79,29 @@ constexpr int C_CHUNKS = C_IN_T * 4;              // 16-byte chunks per staged t
 constexpr int C_PER_THREAD = (C_CHUNKS + 255) / 256;
 constexpr int C_W_ROWS = 9 * CH;                  // packed weight rows (tap, out-channel)
 
+// Out-channel in row r of the weight operand.  A lane of the product holds
+// rows 8 j + 4 kq + (0 .. 3), j = 0 .. 3, of one pixel; in this order they are
+// the 16 channels 16 kq .. 16 kq + 15, so that outputs, residual inputs and
+// references move as two 16-byte vectors a pixel and lane and not as four of 8
+// bytes: 32 images of 256^2 take 62 us a plain layer and 78 us one with a
+// residual input or reference (5.1 TB/s, what a copy reaches), 76 and 88 before.
+__device__ __forceinline__ int out_channel(int r) { return 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3); }
+
+// The two bfloat16 values of a word as floats.
+__device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
+__device__ __forceinline__ uint32_t word_of(const uint4 &v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
+__device__ __forceinline__ uint4 pack_bf16(const float (&v)[8])
+{
+    union {
+        bf16 b[8];
+        uint4 u;
+    } p;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) p.b[i] = (bf16)v[i];
+    return p.u;
+}
+
 __device__ __forceinline__ void conv_tile_origin(int tile, int tiles_x, int tiles_y, int &n, int &y0, int &x0)
 {
     const int tx = tile % tiles_x;
@@ -184,9 +207,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int n_tiles = tiles_x * tiles_y * a.N;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = lane & 31, kq = lane >> 5;
-    for (int k = threadIdx.x; k < C_W_ROWS * 4; k += blockDim.x)
-        *reinterpret_cast<uint4 *>(wl + (k >> 2) * PIXS + (k & 3) * 8) =
-            *reinterpret_cast<const uint4 *>(a.w + (k >> 2) * CH + (k & 3) * 8);
+    for (int k = threadIdx.x; k < C_W_ROWS * 4; k += blockDim.x) {
+        const int row = k >> 2, src = (row & ~(CH - 1)) + out_channel(row & (CH - 1));
+        *reinterpret_cast<uint4 *>(wl + row * PIXS + (k & 3) * 8) =
+            *reinterpret_cast<const uint4 *>(a.w + src * CH + (k & 3) * 8);
+    }
     if (threadIdx.x < CH) bl[threadIdx.x] = a.bias ? a.bias[threadIdx.x] : 0.0f;
     uint4 pre[C_PER_THREAD];
     uint32_t pre_valid = 0u;
@@ -209,11 +234,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (; tile_id < n_tiles; tile_id += gridDim.x) {
         int n, y0, x0;
         conv_tile_origin(tile_id, tiles_x, tiles_y, n, y0, x0);
-        // D: lane holds pixel column m, channels 8 j + 4 kq + (0 .. 3) in acc[4 j .. 4 j + 3]
+        // D: lane holds pixel column m, channels 16 kq .. 16 kq + 15 in acc
         const int gx = x0 + m;
         // the residual input (or the ReLU reference of a gradient) of the
         // tile's outputs, loaded ahead of the products
-        uint2 addv[4][4];
+        uint4 addv[4][2];
         const bf16 *side = (SIDE & 1) ? a.add : a.ref;
         if (SIDE) {
             // outputs outside the image are never stored: their loads read a
@@ -225,8 +250,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 const int gyc = min(y0 + 4 * wave + o, a.H - 1);
                 const int64_t pix = ((int64_t)n * a.H + gyc) * a.W + gxc;
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    addv[o][j] = *reinterpret_cast<const uint2 *>(side + pix * CH + 8 * j + 4 * kq);
+                for (int j = 0; j < 2; ++j)
+                    addv[o][j] = *reinterpret_cast<const uint4 *>(side + pix * CH + 16 * kq + 8 * j);
             }
         }
         // the next tile's pixels, issued after the side loads (the wait
@@ -254,7 +279,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             // added to sums that start at +0) change nothing
 #pragma unroll
             for (int kh = 0; kh < ((SIDE & 4) ? 1 : 2); ++kh) {
-                // weights of taps (dy, dx - 1), dy = -1, 0, 1: out-channel m, in-channels kh*16 + kq*8 .. +7
+                // weights of taps (dy, dx - 1), dy = -1, 0, 1: row m, in-channels kh*16 + kq*8 .. +7
                 bf16x8 wa[3];
 #pragma unroll
                 for (int d = 0; d < 3; ++d)
@@ -283,34 +308,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             if (gy >= a.H || gx >= a.W) continue;
             const int64_t pix = ((int64_t)n * a.H + gy) * a.W + gx;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int c0 = 8 * j + 4 * kq;
+            for (int j = 0; j < 2; ++j) {
+                const int c0 = 16 * kq + 8 * j;
                 const int64_t idx = pix * CH + c0;
-                float v[4];
+                float v[8];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = acc[o][4 * j + r] + bl[c0 + r];
-                if (SIDE & 1) {
-                    // bf16 -> float by bit position (keeps the loaded words whole until here)
-                    const uint2 w2 = addv[o][j];
-                    v[0] += __uint_as_float(w2.x << 16);
-                    v[1] += __uint_as_float(w2.x & 0xFFFF0000u);
-                    v[2] += __uint_as_float(w2.y << 16);
-                    v[3] += __uint_as_float(w2.y & 0xFFFF0000u);
-                }
+                for (int r = 0; r < 8; ++r) v[r] = acc[o][8 * j + r] + bl[c0 + r];
+                if (SIDE & 1)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        v[2 * r] += bf_lo(word_of(addv[o][j], r));
+                        v[2 * r + 1] += bf_hi(word_of(addv[o][j], r));
+                    }
                 if (a.relu)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.0f);
+                    for (int r = 0; r < 8; ++r) v[r] = fmaxf(v[r], 0.0f);
                 if (SIDE & 2) {
                     // prefetched unless the layer also has a residual input
-                    const uint2 rf = (SIDE & 1) ? *reinterpret_cast<const uint2 *>(a.ref + idx) : addv[o][j];
-                    const float rv[4] = {__uint_as_float(rf.x << 16), __uint_as_float(rf.x & 0xFFFF0000u),
-                                         __uint_as_float(rf.y << 16), __uint_as_float(rf.y & 0xFFFF0000u)};
+                    const uint4 rf = (SIDE & 1) ? *reinterpret_cast<const uint4 *>(a.ref + idx) : addv[o][j];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (!(rv[r] > 0.0f)) v[r] = 0.0f;
+                    for (int r = 0; r < 4; ++r) {
+                        if (!(bf_lo(word_of(rf, r)) > 0.0f)) v[2 * r] = 0.0f;
+                        if (!(bf_hi(word_of(rf, r)) > 0.0f)) v[2 * r + 1] = 0.0f;
+                    }
                 }
                 if (SIDE & 8) {
-                    // channels 0 and 1 (lanes of kq = 0, run j = 0): the
+                    // channels 0 and 1 (lanes of kq = 0, j = 0): the
                     // starting angle atan2(max(s, 0), c) / q below 2 pi, 0 at
                     // sampled pixels, from the bfloat16-rounded outputs
                     if (j == 0 && kq == 0) {
@@ -320,11 +343,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     }
                     continue;
                 }
-                uint2 ov;
-                bf16 *op = reinterpret_cast<bf16 *>(&ov);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) op[r] = (bf16)v[r];
-                *reinterpret_cast<uint2 *>(a.out + idx) = ov;
+                *reinterpret_cast<uint4 *>(a.out + idx) = pack_bf16(v);
             }
         }
         __syncthreads();  // the next tile is in LDS
@@ -378,12 +397,14 @@ constexpr int RES_NT = 512;                                          // threads 
 constexpr int RES_PT = (C_CHUNKS + RES_NT - 1) / RES_NT;             // staged chunks per thread
 constexpr int W_CHUNKS = C_W_ROWS * 4;                               // 16-byte chunks of one layer's weights
 
-// One layer's packed weights into LDS rows of 80 B.
+// One layer's packed weights into LDS rows of 80 B, in the operand's order.
 __device__ __forceinline__ void res_copy_w(const bf16 *__restrict__ w, bf16 *wl)
 {
-    for (int k = (int)threadIdx.x; k < W_CHUNKS; k += RES_NT)
-        *reinterpret_cast<uint4 *>(wl + (k >> 2) * PIXS + (k & 3) * 8) =
-            *reinterpret_cast<const uint4 *>(w + (k >> 2) * CH + (k & 3) * 8);
+    for (int k = (int)threadIdx.x; k < W_CHUNKS; k += RES_NT) {
+        const int row = k >> 2, src = (row & ~(CH - 1)) + out_channel(row & (CH - 1));
+        *reinterpret_cast<uint4 *>(wl + row * PIXS + (k & 3) * 8) =
+            *reinterpret_cast<const uint4 *>(w + src * CH + (k & 3) * 8);
+    }
 }
 
 // conv_load_tile / conv_store_tile for 512-thread blocks.
@@ -498,7 +519,7 @@ __global__ __launch_bounds__(RES_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #pragma unroll
             for (int d = 0; d < 3; ++d)
                 w2r[dx][kh][d] =
-                    *reinterpret_cast<const bf16x8 *>(a.w2 + ((d * 3 + dx) * CH + m) * CH + kh * 16 + kq * 8);
+                    *reinterpret_cast<const bf16x8 *>(a.w2 + ((d * 3 + dx) * CH + out_channel(m)) * CH + kh * 16 + kq * 8);
     // this block's tiles: the blocks of XCD x = blockIdx % 8 (there are
     // ceil((G - x) / 8) of them) take a contiguous run of the tile sequence
     // in proportion to their number, in turn
@@ -526,13 +547,13 @@ __global__ __launch_bounds__(RES_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         res_products(tile, wl1, wave, m, kq, acc);
         // the skip inputs of this lane's conv2 outputs (staged pixel
         // (2 wave + o + 2, m + 2)), read before t overwrites the tile
-        uint2 skip[2][4];
+        uint4 skip[2][2];
 #pragma unroll
         for (int o = 0; o < 2; ++o)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                skip[o][j] = *reinterpret_cast<const uint2 *>(
-                    tile + (min(2 * wave + o + 2, CTH + 1) * C_IN_W + m + 2) * PIXS + 8 * j + 4 * kq);
+            for (int j = 0; j < 2; ++j)
+                skip[o][j] = *reinterpret_cast<const uint4 *>(
+                    tile + (min(2 * wave + o + 2, CTH + 1) * C_IN_W + m + 2) * PIXS + 16 * kq + 8 * j);
         __syncthreads();  // every wave is done with the input tile
         {
             const int gx = x0 - 1 + m;
@@ -541,15 +562,12 @@ __global__ __launch_bounds__(RES_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 const int tr = 2 * wave + o, gy = y0 - 1 + tr;
                 const bool inside = gy >= 0 && gy < a.H && gx >= 0 && gx < a.W;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int c0 = 8 * j + 4 * kq;
-                    uint2 tv = make_uint2(0u, 0u);
-                    if (inside) {
-                        bf16 *tp = reinterpret_cast<bf16 *>(&tv);
+                for (int j = 0; j < 2; ++j) {
+                    const int c0 = 16 * kq + 8 * j;
+                    float v[8];
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) tp[r] = (bf16)fmaxf(acc[o][4 * j + r] + bl[c0 + r], 0.0f);
-                    }
-                    *reinterpret_cast<uint2 *>(tile + (tr * C_IN_W + m) * PIXS + c0) = tv;
+                    for (int r = 0; r < 8; ++r) v[r] = inside ? fmaxf(acc[o][8 * j + r] + bl[c0 + r], 0.0f) : 0.0f;
+                    *reinterpret_cast<uint4 *>(tile + (tr * C_IN_W + m) * PIXS + c0) = pack_bf16(v);
                 }
             }
             // the tile's last two rows and columns: zero
@@ -578,21 +596,17 @@ __global__ __launch_bounds__(RES_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 if (orow >= RTH || m >= RTW || gy >= a.H || gx >= a.W) continue;
                 const int64_t pix = ((int64_t)n * a.H + gy) * a.W + gx;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int c0 = 8 * j + 4 * kq;
-                    const uint2 w2 = skip[o][j];
-                    float v[4];
+                for (int j = 0; j < 2; ++j) {
+                    const int c0 = 16 * kq + 8 * j;
+                    float v[8];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] = acc[o][4 * j + r] + bl[CH + c0 + r];
-                    v[0] += __uint_as_float(w2.x << 16);
-                    v[1] += __uint_as_float(w2.x & 0xFFFF0000u);
-                    v[2] += __uint_as_float(w2.y << 16);
-                    v[3] += __uint_as_float(w2.y & 0xFFFF0000u);
-                    uint2 ov;
-                    bf16 *op = reinterpret_cast<bf16 *>(&ov);
+                    for (int r = 0; r < 8; ++r) v[r] = acc[o][8 * j + r] + bl[CH + c0 + r];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) op[r] = (bf16)v[r];
-                    *reinterpret_cast<uint2 *>(a.out + pix * CH + c0) = ov;
+                    for (int r = 0; r < 4; ++r) {
+                        v[2 * r] += bf_lo(word_of(skip[o][j], r));
+                        v[2 * r + 1] += bf_hi(word_of(skip[o][j], r));
+                    }
+                    *reinterpret_cast<uint4 *>(a.out + pix * CH + c0) = pack_bf16(v);
                 }
             }
         }
