@@ -2510,62 +2510,7 @@ __global__ void record_states_kernel(const ChainDesc *__restrict__ descs, const 
     }
 }
 
-// Quantiles of the M realizations at each gap site of image blockIdx.y: the
-// M states (states[m n_total + site]) are sorted in LDS (insertion sort, one
-// wave per block, a lane's values 64 apart so that lanes use distinct banks),
-// the p-quantile interpolates linearly between the order statistics around
-// h = (M - 1) p, and is back-transformed like the mean (double precision,
-// rounded once).  Sampled sites get their data value.
-constexpr int kQuantileLanes = 64;
 constexpr int kMaxQuantileStates = 256;
-
-__global__ __launch_bounds__(kQuantileLanes) void quantile_kernel(const ImgDev *__restrict__ imgs,
-                                                                  const double *__restrict__ zmm,
-                                                                  const double *__restrict__ probs, int nq,
-                                                                  const float *__restrict__ z,
-                                                                  const uint8_t *__restrict__ sampled,
-                                                                  const float *__restrict__ st, int M,
-                                                                  int64_t n_total, float *__restrict__ out)
-{
-#pragma clang fp contract(off)
-    __shared__ float v[kMaxQuantileStates * kQuantileLanes];
-    const ImgDev im = imgs[blockIdx.y];
-    const int64_t n = (int64_t)im.nx * im.ny;
-    const double lo = zmm[2 * blockIdx.y], hi = zmm[2 * blockIdx.y + 1];
-    const int t = threadIdx.x;
-    for (int64_t i0 = (int64_t)blockIdx.x * kQuantileLanes; i0 < n; i0 += (int64_t)gridDim.x * kQuantileLanes) {
-        const int64_t i = i0 + t;
-        if (i >= n) continue;
-        const int64_t k = im.offset + i;
-        if (sampled[k]) {
-            for (int q = 0; q < nq; ++q) out[q * n_total + k] = z[k];
-            continue;
-        }
-        for (int m = 0; m < M; ++m) {
-            // insertion of state m into the sorted prefix
-            const float x = st[(int64_t)m * n_total + k];
-            int j = m - 1;
-            while (j >= 0 && v[j * kQuantileLanes + t] > x) {
-                v[(j + 1) * kQuantileLanes + t] = v[j * kQuantileLanes + t];
-                --j;
-            }
-            v[(j + 1) * kQuantileLanes + t] = x;
-        }
-        for (int q = 0; q < nq; ++q) {
-            const double h = (double)(M - 1) * probs[q];
-            const int a = (int)floor(h);
-            double phi_p;
-            if (a >= M - 1) {
-                phi_p = (double)v[(M - 1) * kQuantileLanes + t];
-            } else {
-                const double va = (double)v[a * kQuantileLanes + t], vb = (double)v[(a + 1) * kQuantileLanes + t];
-                phi_p = va + (h - (double)a) * (vb - va);
-            }
-            const double tt = phi_p / kTwoPi;
-            out[q * n_total + k] = (float)(lo * (1.0 - tt) + hi * tt);
-        }
-    }
-}
 
 // The sampled sites kept for fitting when a fraction `hold` of them is held
 // out for validation: a sample is held out when the uniform of its site,
@@ -2643,46 +2588,200 @@ __device__ __forceinline__ void odd_even_merge_sort(float (&v)[N])
                     }
 }
 
-// quantile_kernel for M <= N states per site with the sort in registers (a
-// thread per site; states beyond M are +inf and sort last); the order
-// statistics at the runtime positions are picked by unrolled selects.
+// A bitonic sequence v[0..N-1], N a power of two, sorted ascending.
 template <int N>
-__global__ __launch_bounds__(kBlock) void quantile_net_kernel(const ImgDev *__restrict__ imgs,
-                                                              const double *__restrict__ zmm,
-                                                              const double *__restrict__ probs, int nq,
-                                                              const float *__restrict__ z,
-                                                              const uint8_t *__restrict__ sampled,
-                                                              const float *__restrict__ st, int M, int64_t n_total,
-                                                              float *__restrict__ out)
+__device__ __forceinline__ void bitonic_merge(float (&v)[N])
+{
+#pragma unroll
+    for (int k = N / 2; k >= 1; k >>= 1)
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (!(i & k)) {
+                const float a = v[i], b = v[i + k];
+                v[i] = fminf(a, b);
+                v[i + k] = fmaxf(a, b);
+            }
+}
+
+// v[a] and v[a + 1] (if there is one) for a wave-uniform a, without putting
+// v in memory: the eight entries around a by a branch (in a large v), one of
+// them by selects.
+template <int N>
+__device__ __forceinline__ void pick_two(const float (&v)[N], int a, float &va, float &vb)
+{
+    va = vb = 0.0f;
+#pragma unroll
+    for (int g = 0; g < N; g += 8)
+        if (N <= 32 || (a & ~7) == g) {
+            if (N > 32) __asm__ volatile("");
+#pragma unroll
+            for (int m = g; m < g + 8 && m < N; ++m) {
+                va = m == a ? v[m] : va;
+                if (m + 1 < N) vb = m == a ? v[m + 1] : vb;
+            }
+        }
+}
+
+// States first, first + 1, ... of element i into v, +inf beyond state M - 1
+// (state M - 1 is read again there, so that every load is issued at once);
+// at least `sure` of them exist.
+template <int N>
+__device__ __forceinline__ void load_states(float (&v)[N], const float *src, int first, int sure, int M,
+                                            int64_t n_total, uint32_t i)
+{
+    src += (int64_t)first * n_total;
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+        // (opaque, so that the addresses of many rows are not held in registers at once)
+        if (N > 32) __asm__ volatile("" : "+s"(src));
+        v[m] = gldi(src, i);
+        src += m + 1 < sure || first + m + 1 < M ? n_total : 0;
+    }
+#pragma unroll
+    for (int m = 0; m < N; ++m)
+        if (m >= sure) v[m] = first + m < M ? v[m] : INFINITY;
+}
+
+// The p-quantile from the order statistics around h = (M - 1) p, a = floor(h),
+// back-transformed like the mean (double precision, rounded once).
+__device__ __forceinline__ float quantile_value(double h, int a, int M, float va, float vb, double lo, double hi)
 {
 #pragma clang fp contract(off)
+    const double phi_p = a >= M - 1 ? (double)va : (double)va + (h - (double)a) * ((double)vb - (double)va);
+    const double tt = phi_p / kTwoPi;
+    return (float)(lo * (1.0 - tt) + hi * tt);
+}
+
+// Quantiles of the M realizations (states[m n_total + site]) at each gap site
+// of image blockIdx.y; sampled sites get their data value.  A wave works along
+// `span` sites: it lists their gap sites in LDS, 256 sites at a time, and
+// whenever 64 are listed each lane sorts the states of one of them in
+// registers, so that no lane idles over a sample; waves do not wait for each
+// other.  The network is that of the next multiple of eight entries (states
+// beyond M are +inf and sort last).  With BIG (M > 128, N = 128) two runs of N
+// states are sorted one after the other, the first kept in LDS meanwhile;
+// their lower and upper halves (minima and maxima of one run against the other
+// reversed) are bitonic and are merged in turn.  Bound by reading the states,
+// with the comparisons next (2300 min/max for M = 100); 2048^2 sites, half of
+// them gaps, three quantiles, a whole call: M = 100 475 us (939 with a sort of
+// 128 entries at every site), M = 50 246 us (336), M = 16 99 us (104); 1024^2
+// sites, M = 200: 0.35 ms (48 ms with an insertion sort in LDS).
+// waves per SIMD that the registers of a network leave
+constexpr int quantile_waves(int n, bool big) { return big ? 1 : n <= 48 ? 8 : n <= 104 ? 4 : 3; }
+// Up to 32 states a lane takes each site as it comes: reading the states
+// bounds such a sort even with half of the lanes idle (M = 16, half gaps: 99
+// us a call, 117 with the list).
+constexpr bool quantile_lists(int n) { return n > 32; }
+template <int N, bool BIG>
+__global__ __launch_bounds__(BIG ? 64 : kBlock)
+__attribute__((amdgpu_waves_per_eu(quantile_waves(N, BIG)))) void quantile_kernel(
+    const ImgDev *__restrict__ imgs, const double *__restrict__ zmm, const double *__restrict__ probs, int nq,
+    const float *__restrict__ z, const uint8_t *__restrict__ sampled, const float *__restrict__ st, int M,
+    int64_t n_total, int64_t span, float *__restrict__ out)
+{
+    constexpr int NW = BIG ? 1 : kBlock / 64;
+    constexpr bool LIST = quantile_lists(N);
+    constexpr int GROUP = LIST ? 256 : 64;  // sites at a time
+    __shared__ uint32_t lists[NW][LIST ? GROUP + 64 : 1];
+    __shared__ float runs[BIG ? N * 64 : 1];
     const ImgDev im = imgs[blockIdx.y];
     const int64_t n = (int64_t)im.nx * im.ny;
     const double lo = zmm[2 * blockIdx.y], hi = zmm[2 * blockIdx.y + 1];
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t k = im.offset + i;
-        if (sampled[k]) {
-            for (int q = 0; q < nq; ++q) out[q * n_total + k] = z[k];
-            continue;
-        }
+    const int lane = (int)(threadIdx.x & 63), wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t first = ((int64_t)blockIdx.x * NW + wid) * span;
+    if (first >= n) return;
+    const int64_t k0 = im.offset + first;
+    const uint32_t len = (uint32_t)min(n - first, span);
+    uint32_t *list = lists[wid];
+    int listed = 0;
+    // the quantiles of this lane's site
+    auto site = [&](uint32_t i) {
         float v[N];
-#pragma unroll
-        for (int m = 0; m < N; ++m) v[m] = m < M ? st[(int64_t)m * n_total + k] : INFINITY;
+        load_states<N>(v, st + k0, 0, BIG ? N : N - 8, M, n_total, i);
         odd_even_merge_sort<N>(v);
-        for (int q = 0; q < nq; ++q) {
-            const double h = (double)(M - 1) * probs[q];
-            const int a = (int)floor(h);
-            float va = v[0], vb = v[0];
+        if constexpr (BIG) {
+            float *run = runs + lane;
+#pragma unroll
+            for (int m = 0; m < N; ++m) run[m * 64] = v[m];
+            load_states<N>(v, st + k0, N, 0, M, n_total, i);
+            odd_even_merge_sort<N>(v);
 #pragma unroll
             for (int m = 0; m < N; ++m) {
-                va = m == a ? v[m] : va;
-                vb = m == a + 1 ? v[m] : vb;
+                const float x = run[(N - 1 - m) * 64];
+                run[(N - 1 - m) * 64] = fmaxf(v[m], x);
+                v[m] = fminf(v[m], x);
             }
-            const double phi_p = a >= M - 1 ? (double)va : (double)va + (h - (double)a) * ((double)vb - (double)va);
-            const double tt = phi_p / kTwoPi;
-            out[q * n_total + k] = (float)(lo * (1.0 - tt) + hi * tt);
+            bitonic_merge<N>(v);
+            // the lower half to LDS, the upper one from there
+#pragma unroll
+            for (int m = 0; m < N; ++m) {
+                const float x = run[m * 64];
+                run[m * 64] = v[m];
+                v[m] = x;
+            }
+            bitonic_merge<N>(v);
+        }
+        for (int q = 0; q < nq; ++q) {
+            const double h = (double)(M - 1) * probs[q];
+            const int a = __builtin_amdgcn_readfirstlane((int)floor(h));
+            float va, vb;
+            if (BIG && a < N) {
+                va = runs[a * 64 + lane];
+                vb = a + 1 < N ? runs[(a + 1) * 64 + lane] : v[0];
+            } else {
+                pick_two<N>(v, BIG ? a - N : a, va, vb);
+            }
+            out[q * n_total + k0 + i] = quantile_value(h, a, M, va, vb, lo, hi);
+        }
+    };
+    for (uint32_t g = 0; g < len; g += GROUP) {
+        uint8_t smp[GROUP / 64];
+#pragma unroll
+        for (int r = 0; r < GROUP / 64; ++r) {
+            const uint32_t i = g + 64u * r + (uint32_t)lane;
+            smp[r] = sampled[k0 + min(i, len - 1u)];
+        }
+#pragma unroll
+        for (int r = 0; r < GROUP / 64; ++r) {
+            const uint32_t i = g + 64u * r + (uint32_t)lane;
+            const bool gap = i < len && !smp[r];
+            if (LIST) {
+                const uint64_t b = __ballot(gap);
+                if (gap) list[listed + rank_below(b)] = i;
+                listed += (int)__popcll(b);
+            } else if (gap) {
+                site(i);
+            }
+            if (i < len && !gap)
+                for (int q = 0; q < nq; ++q) out[q * n_total + k0 + i] = z[k0 + i];
+        }
+        if (!LIST) continue;
+        __builtin_amdgcn_wave_barrier();
+        const bool last = g + GROUP >= len;
+        while (listed >= 64 || (last && listed > 0)) {
+            // the last listed sites (those before them stay listed)
+            const int take = min(listed, 64);
+            listed -= take;
+            if (lane < take) site(list[listed + lane]);
+            __builtin_amdgcn_wave_barrier();
         }
     }
+}
+
+template <int N, bool BIG>
+void launch_quantiles(hipStream_t stream, int64_t max_sites, int n, const ImgDev *imgs, const double *zmm,
+                      const double *probs, int nq, const float *z, const uint8_t *sampled, const float *states, int M,
+                      int64_t n_total, float *z_q)
+{
+    // four times as many waves as the 1024 SIMDs hold at once (one for BIG),
+    // each along at least 64 sites: at M = 100, half gaps, one to sixteen
+    // times as many take 511, 494, 481 and 506 us
+    const int64_t waves = 1024 * quantile_waves(N, BIG) * (BIG ? 1 : 4);
+    const int64_t span = std::max<int64_t>(64, ((max_sites * n + waves - 1) / waves + 63) / 64 * 64);
+    const int64_t per_block = span * (BIG ? 1 : kBlock / 64);
+    hipLaunchKernelGGL((quantile_kernel<N, BIG>), dim3((unsigned)((max_sites + per_block - 1) / per_block), n),
+                       dim3(BIG ? 64 : kBlock), 0, stream, imgs, zmm, probs, nq, z, sampled, states, M, n_total, span,
+                       z_q);
 }
 
 // Spread of the prediction: the standard deviation over the M realizations
@@ -4599,27 +4698,18 @@ int32_t mpr_quantiles(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, const floa
     HIP_TRY(ctx, hipMemcpyAsync(d_img, hi.data(), n * sizeof(ImgDev), hipMemcpyHostToDevice, stream));
     HIP_TRY(ctx, hipMemcpyAsync(d_zmm, zmin_zmax, n * 16, hipMemcpyHostToDevice, stream));
     HIP_TRY(ctx, hipMemcpyAsync(d_probs, probs, nq * 8, hipMemcpyHostToDevice, stream));
-    if (M <= 128) {
-        // sort in registers: a network of the smallest power-of-two size >= M
-        const int gb = blocks_for(maxn, 8192);
-        if (M <= 16)
-            hipLaunchKernelGGL(quantile_net_kernel<16>, dim3(gb, n), dim3(kBlock), 0, stream, d_img, d_zmm, d_probs,
-                               nq, z, sampled, phi_states, M, n_total, z_q);
-        else if (M <= 32)
-            hipLaunchKernelGGL(quantile_net_kernel<32>, dim3(gb, n), dim3(kBlock), 0, stream, d_img, d_zmm, d_probs,
-                               nq, z, sampled, phi_states, M, n_total, z_q);
-        else if (M <= 64)
-            hipLaunchKernelGGL(quantile_net_kernel<64>, dim3(gb, n), dim3(kBlock), 0, stream, d_img, d_zmm, d_probs,
-                               nq, z, sampled, phi_states, M, n_total, z_q);
-        else
-            hipLaunchKernelGGL(quantile_net_kernel<128>, dim3(gb, n), dim3(kBlock), 0, stream, d_img, d_zmm, d_probs,
-                               nq, z, sampled, phi_states, M, n_total, z_q);
-    } else {
-        const int gx =
-            (int)std::max<int64_t>(1, std::min<int64_t>((maxn + kQuantileLanes - 1) / kQuantileLanes, 8192));
-        hipLaunchKernelGGL(quantile_kernel, dim3(gx, n), dim3(kQuantileLanes), 0, stream, d_img, d_zmm, d_probs, nq,
-                           z, sampled, phi_states, M, n_total, z_q);
-    }
+    // the smallest network that holds M states
+    using Launch = void (*)(hipStream_t, int64_t, int, const ImgDev *, const double *, const double *, int,
+                            const float *, const uint8_t *, const float *, int, int64_t, float *);
+    static constexpr Launch kNets[16] = {
+        launch_quantiles<8, false>,   launch_quantiles<16, false>,  launch_quantiles<24, false>,
+        launch_quantiles<32, false>,  launch_quantiles<40, false>,  launch_quantiles<48, false>,
+        launch_quantiles<56, false>,  launch_quantiles<64, false>,  launch_quantiles<72, false>,
+        launch_quantiles<80, false>,  launch_quantiles<88, false>,  launch_quantiles<96, false>,
+        launch_quantiles<104, false>, launch_quantiles<112, false>, launch_quantiles<120, false>,
+        launch_quantiles<128, false>};
+    (M <= 128 ? kNets[(M - 1) / 8] : launch_quantiles<128, true>)(stream, maxn, n, d_img, d_zmm, d_probs, nq, z, sampled,
+                                                                   phi_states, M, n_total, z_q);
     HIP_TRY(ctx, hipGetLastError());
     HIP_TRY(ctx, hipStreamSynchronize(stream));
     return MPR_OK;
