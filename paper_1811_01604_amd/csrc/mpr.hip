@@ -105,6 +105,45 @@ struct ImgDev {
     int32_t nx, ny;
 };
 
+// The images of a call and their data ranges.  A few of them travel in the
+// kernel's arguments (a copy to the device before the launch costs some 8 us
+// of a small call), more in device memory.
+constexpr int kArgImages = 8;
+struct ImgArgs {
+    const ImgDev *dev;  // null: own
+    ImgDev own[kArgImages];
+    // (uniform over the wave: b is a block index)
+    __device__ ImgDev at(int b) const
+    {
+        ImgDev r = dev ? dev[b] : own[b];
+        r.offset = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(r.offset >> 32)) << 32) |
+                             (uint32_t)__builtin_amdgcn_readfirstlane((int)r.offset));
+        r.nx = __builtin_amdgcn_readfirstlane(r.nx);
+        r.ny = __builtin_amdgcn_readfirstlane(r.ny);
+        return r;
+    }
+};
+struct RangeArgs {
+    const double *dev;  // null: own
+    double own[2 * kArgImages];
+    __device__ double lo(int b) const { return dev ? dev[2 * b] : own[2 * b]; }
+    __device__ double hi(int b) const { return dev ? dev[2 * b + 1] : own[2 * b + 1]; }
+};
+constexpr int kMaxProbs = 64;
+struct ProbArgs {
+    double v[kMaxProbs];
+};
+
+// Head of a simulate workspace: what a resumed call checks before it
+// continues the run the workspace holds.
+struct RunHeader {
+    uint64_t magic;     // kRunMagic
+    uint64_t key;       // run_key of the images and parameters
+    int64_t bytes;      // sim_bytes of the run
+    int32_t n_chains;
+    int32_t state;      // 1: stopped at sweep_limit with chains running (resumable)
+};
+
 }  // namespace
 
 // ====================================================================== kernels
@@ -134,8 +173,10 @@ __global__ __launch_bounds__(kBlock) void init_chains_kernel(const ChainDesc *__
                                                              const float *__restrict__ phi,
                                                              const uint8_t *__restrict__ sampled,
                                                              const float *__restrict__ phi_init, uint32_t seed_lo,
-                                                             uint32_t seed_hi, int table_mode)
+                                                             uint32_t seed_hi, int table_mode, RunHeader hdr,
+                                                             RunHeader *__restrict__ d_hdr)
 {
+    if (d_hdr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *d_hdr = hdr;
     typedef RT v4 __attribute__((ext_vector_type(4)));
     const ChainDesc d = descs[blockIdx.y];
     const int64_t off = offsets[blockIdx.y];
@@ -2422,11 +2463,11 @@ __global__ void done_flags_kernel(const ChainState *__restrict__ states, int n, 
 // the sum over the R K states of the squared deviation from their mean: two
 // passes over the R final states (K == 1), or the chains' own sums combined
 // with the spread of their means (Chan et al.'s pairwise rule, K > 1).
-__global__ void finalize_kernel(const ChainDesc *__restrict__ descs, const ImgDev *__restrict__ imgs, int R,
+__global__ void finalize_kernel(const ChainDesc *__restrict__ descs, ImgArgs imgs, int R,
                                 int K, const uint8_t *__restrict__ sampled, float *__restrict__ phi_sum,
                                 float *__restrict__ phi_m2)
 {
-    const ImgDev im = imgs[blockIdx.y];
+    const ImgDev im = imgs.at((int)blockIdx.y);
     const int64_t n = (int64_t)im.nx * im.ny;
     const ChainDesc *dc = descs + (int64_t)blockIdx.y * R;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
@@ -2453,11 +2494,11 @@ __global__ void finalize_kernel(const ChainDesc *__restrict__ descs, const ImgDe
 
 // finalize_kernel for double-precision chains: the same sums taken in
 // double and rounded once.
-__global__ void finalize_fp64_kernel(const ChainDesc *__restrict__ descs, const ImgDev *__restrict__ imgs, int R,
+__global__ void finalize_fp64_kernel(const ChainDesc *__restrict__ descs, ImgArgs imgs, int R,
                                      int K, const uint8_t *__restrict__ sampled, float *__restrict__ phi_sum,
                                      float *__restrict__ phi_m2)
 {
-    const ImgDev im = imgs[blockIdx.y];
+    const ImgDev im = imgs.at((int)blockIdx.y);
     const int64_t n = (int64_t)im.nx * im.ny;
     const ChainDesc *dc = descs + (int64_t)blockIdx.y * R;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
@@ -2675,8 +2716,7 @@ constexpr bool quantile_lists(int n) { return n > 32; }
 template <int N, bool BIG>
 __global__ __launch_bounds__(BIG ? 64 : kBlock)
 __attribute__((amdgpu_waves_per_eu(quantile_waves(N, BIG)))) void quantile_kernel(
-    const ImgDev *__restrict__ imgs, const double *__restrict__ zmm, const double *__restrict__ probs, int nq,
-    const float *__restrict__ z, const uint8_t *__restrict__ sampled, const float *__restrict__ st, int M,
+    ImgArgs imgs, RangeArgs range, ProbArgs probs, int nq, const float *__restrict__ z, const uint8_t *__restrict__ sampled, const float *__restrict__ st, int M,
     int64_t n_total, int64_t span, float *__restrict__ out)
 {
     constexpr int NW = BIG ? 1 : kBlock / 64;
@@ -2684,9 +2724,9 @@ __attribute__((amdgpu_waves_per_eu(quantile_waves(N, BIG)))) void quantile_kerne
     constexpr int GROUP = LIST ? 256 : 64;  // sites at a time
     __shared__ uint32_t lists[NW][LIST ? GROUP + 64 : 1];
     __shared__ float runs[BIG ? N * 64 : 1];
-    const ImgDev im = imgs[blockIdx.y];
+    const ImgDev im = imgs.at((int)blockIdx.y);
     const int64_t n = (int64_t)im.nx * im.ny;
-    const double lo = zmm[2 * blockIdx.y], hi = zmm[2 * blockIdx.y + 1];
+    const double lo = range.lo((int)blockIdx.y), hi = range.hi((int)blockIdx.y);
     const int lane = (int)(threadIdx.x & 63), wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t first = ((int64_t)blockIdx.x * NW + wid) * span;
     if (first >= n) return;
@@ -2722,7 +2762,7 @@ __attribute__((amdgpu_waves_per_eu(quantile_waves(N, BIG)))) void quantile_kerne
             bitonic_merge<N>(v);
         }
         for (int q = 0; q < nq; ++q) {
-            const double h = (double)(M - 1) * probs[q];
+            const double h = (double)(M - 1) * probs.v[q];
             const int a = __builtin_amdgcn_readfirstlane((int)floor(h));
             float va, vb;
             if (BIG && a < N) {
@@ -2769,8 +2809,8 @@ __attribute__((amdgpu_waves_per_eu(quantile_waves(N, BIG)))) void quantile_kerne
 }
 
 template <int N, bool BIG>
-void launch_quantiles(hipStream_t stream, int64_t max_sites, int n, const ImgDev *imgs, const double *zmm,
-                      const double *probs, int nq, const float *z, const uint8_t *sampled, const float *states, int M,
+void launch_quantiles(hipStream_t stream, int64_t max_sites, int n, const ImgArgs &imgs, const RangeArgs &range,
+                      const ProbArgs &probs, int nq, const float *z, const uint8_t *sampled, const float *states, int M,
                       int64_t n_total, float *z_q)
 {
     // four times as many waves as the 1024 SIMDs hold at once (one for BIG),
@@ -2780,20 +2820,20 @@ void launch_quantiles(hipStream_t stream, int64_t max_sites, int n, const ImgDev
     const int64_t span = std::max<int64_t>(64, ((max_sites * n + waves - 1) / waves + 63) / 64 * 64);
     const int64_t per_block = span * (BIG ? 1 : kBlock / 64);
     hipLaunchKernelGGL((quantile_kernel<N, BIG>), dim3((unsigned)((max_sites + per_block - 1) / per_block), n),
-                       dim3(BIG ? 64 : kBlock), 0, stream, imgs, zmm, probs, nq, z, sampled, states, M, n_total, span,
+                       dim3(BIG ? 64 : kBlock), 0, stream, imgs, range, probs, nq, z, sampled, states, M, n_total, span,
                        z_q);
 }
 
 // Spread of the prediction: the standard deviation over the M realizations
 // of z = G^{-1}(phi), which is (z_max - z_min) / (2 pi) times that of phi,
 // sqrt(m2 / (M - 1)); zero at sampled sites and for M = 1.
-__global__ void spread_kernel(const ImgDev *__restrict__ imgs, const double *__restrict__ zmin_zmax, int M,
+__global__ void spread_kernel(ImgArgs imgs, RangeArgs range, int M,
                               const uint8_t *__restrict__ sampled, const float *__restrict__ phi_m2,
                               float *__restrict__ z_std)
 {
-    const ImgDev im = imgs[blockIdx.y];
+    const ImgDev im = imgs.at((int)blockIdx.y);
     const int64_t n = (int64_t)im.nx * im.ny;
-    const double scale = (zmin_zmax[2 * blockIdx.y + 1] - zmin_zmax[2 * blockIdx.y]) / kTwoPi;
+    const double scale = (range.hi((int)blockIdx.y) - range.lo((int)blockIdx.y)) / kTwoPi;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const int64_t k = im.offset + i;
         float v = 0.0f;
@@ -2851,12 +2891,12 @@ __global__ void grid_energy_kernel(const float *__restrict__ phi, int nx, int ny
 }
 
 // Per-block min / max / count of the sampled values of image blockIdx.y.
-__global__ void map_minmax_kernel(const ImgDev *__restrict__ imgs, const float *__restrict__ z,
+__global__ void map_minmax_kernel(ImgArgs imgs, const float *__restrict__ z,
                                   const uint8_t *__restrict__ sampled, float *__restrict__ pmin,
                                   float *__restrict__ pmax, unsigned long long *__restrict__ pcount,
                                   unsigned int *__restrict__ pbad)
 {
-    const ImgDev im = imgs[blockIdx.y];
+    const ImgDev im = imgs.at((int)blockIdx.y);
     const int64_t n = (int64_t)im.nx * im.ny;
     float lo = INFINITY, hi = -INFINITY;
     unsigned long long cnt = 0ull;
@@ -2904,13 +2944,66 @@ __global__ void map_minmax_kernel(const ImgDev *__restrict__ imgs, const float *
     }
 }
 
-__global__ void map_apply_kernel(const ImgDev *__restrict__ imgs, const double *__restrict__ zmm,
-                                 const float *__restrict__ z, const uint8_t *__restrict__ sampled,
-                                 float *__restrict__ phi)
+// The map of image blockIdx.y from its range; with `parts` > 0 (one image) the
+// range is first reduced from that many partial results, by every block for
+// itself, written to `found` (host memory: minimum, maximum, samples, whether
+// one is not finite), and nothing is mapped unless it is valid.
+__global__ __launch_bounds__(kBlock) void map_apply_kernel(ImgArgs imgs, RangeArgs range, int parts,
+                                                           const float *__restrict__ pmin,
+                                                           const float *__restrict__ pmax,
+                                                           const unsigned long long *__restrict__ pcount,
+                                                           const unsigned int *__restrict__ pbad,
+                                                           double *__restrict__ found, const float *__restrict__ z,
+                                                           const uint8_t *__restrict__ sampled,
+                                                           float *__restrict__ phi)
 {
 #pragma clang fp contract(off)
-    const ImgDev im = imgs[blockIdx.y];
-    const double zmin = zmm[2 * blockIdx.y], zmax = zmm[2 * blockIdx.y + 1];
+    const ImgDev im = imgs.at((int)blockIdx.y);
+    double zmin, zmax;
+    if (parts > 0) {
+        __shared__ float slo[kBlock / 64], shi[kBlock / 64];
+        __shared__ uint32_t scnt[kBlock / 64], sbad[kBlock / 64];
+        float lo = INFINITY, hi = -INFINITY;
+        uint32_t cnt = 0u, bad = 0u;
+        for (int k = (int)threadIdx.x; k < parts; k += kBlock) {
+            lo = fminf(lo, pmin[k]);
+            hi = fmaxf(hi, pmax[k]);
+            cnt = min(cnt + (uint32_t)min(pcount[k], 2ull), 2u);  // fewer than two samples are refused
+            bad |= pbad[k];
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            lo = fminf(lo, __shfl_xor(lo, off));
+            hi = fmaxf(hi, __shfl_xor(hi, off));
+            cnt += __shfl_xor(cnt, off);
+            bad |= __shfl_xor(bad, off);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            slo[threadIdx.x >> 6] = lo;
+            shi[threadIdx.x >> 6] = hi;
+            scnt[threadIdx.x >> 6] = cnt;
+            sbad[threadIdx.x >> 6] = bad;
+        }
+        __syncthreads();
+        lo = slo[0], hi = shi[0], cnt = scnt[0], bad = sbad[0];
+        for (int k = 1; k < kBlock / 64; ++k) {
+            lo = fminf(lo, slo[k]);
+            hi = fmaxf(hi, shi[k]);
+            cnt += scnt[k];
+            bad |= sbad[k];
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            found[0] = (double)lo;
+            found[1] = (double)hi;
+            found[2] = (double)cnt;
+            found[3] = (double)bad;
+        }
+        if (bad || cnt < 2u || !(hi > lo)) return;
+        zmin = (double)lo;
+        zmax = (double)hi;
+    } else {
+        zmin = range.lo((int)blockIdx.y);
+        zmax = range.hi((int)blockIdx.y);
+    }
     const int64_t n = (int64_t)im.nx * im.ny;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const int64_t j = im.offset + i;
@@ -2918,13 +3011,13 @@ __global__ void map_apply_kernel(const ImgDev *__restrict__ imgs, const double *
     }
 }
 
-__global__ void predict_kernel(const ImgDev *__restrict__ imgs, const double *__restrict__ zmm, int M,
+__global__ void predict_kernel(ImgArgs imgs, RangeArgs range, int M,
                                const float *__restrict__ z, const uint8_t *__restrict__ sampled,
                                const float *__restrict__ phi_sum, float *__restrict__ z_hat)
 {
 #pragma clang fp contract(off)
-    const ImgDev im = imgs[blockIdx.y];
-    const double zmin = zmm[2 * blockIdx.y], zmax = zmm[2 * blockIdx.y + 1];
+    const ImgDev im = imgs.at((int)blockIdx.y);
+    const double zmin = range.lo((int)blockIdx.y), zmax = range.hi((int)blockIdx.y);
     const int64_t n = (int64_t)im.nx * im.ny;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const int64_t j = im.offset + i;
@@ -2947,11 +3040,11 @@ __host__ __device__ inline int image_blocks(int64_t n)
     return (int)(b < 1 ? 1 : (b > kMapBlocks ? kMapBlocks : b));
 }
 
-__global__ void sample_energy_kernel(const ImgDev *__restrict__ imgs, const float *__restrict__ phi,
+__global__ void sample_energy_kernel(ImgArgs imgs, const float *__restrict__ phi,
                                      const uint8_t *__restrict__ sampled, double q, double *__restrict__ psum,
                                      unsigned long long *__restrict__ pcount)
 {
-    const ImgDev im = imgs[blockIdx.y];
+    const ImgDev im = imgs.at((int)blockIdx.y);
     const int64_t n = (int64_t)im.nx * im.ny;
     const int nbk = image_blocks(n);  // this image's blocks (the grid covers the largest image)
     if ((int)blockIdx.x >= nbk) return;
@@ -3131,6 +3224,36 @@ char *stage_for(mpr_ctx *ctx, int64_t bytes, std::vector<char> &spill)
     return spill.data();
 }
 
+// The images of a call (and, where given, their ranges) as kernel arguments;
+// more than kArgImages of them are copied to d_img and d_zmm, from `hi`, which
+// the caller keeps until it has waited for the stream.
+int image_args(mpr_ctx *ctx, hipStream_t stream, const mpr_image *imgs, int n, std::vector<ImgDev> &hi, ImgDev *d_img,
+               ImgArgs &out)
+{
+    hi.resize(n);
+    for (int b = 0; b < n; ++b) hi[b] = {imgs[b].offset, imgs[b].nx, imgs[b].ny};
+    std::memset(&out, 0, sizeof out);
+    if (n <= kArgImages) {
+        for (int b = 0; b < n; ++b) out.own[b] = hi[b];
+    } else {
+        HIP_TRY(ctx, hipMemcpyAsync(d_img, hi.data(), n * sizeof(ImgDev), hipMemcpyHostToDevice, stream));
+        out.dev = d_img;
+    }
+    return MPR_OK;
+}
+
+int range_args(mpr_ctx *ctx, hipStream_t stream, const double *zmin_zmax, int n, double *d_zmm, RangeArgs &out)
+{
+    std::memset(&out, 0, sizeof out);
+    if (n <= kArgImages) {
+        std::memcpy(out.own, zmin_zmax, (size_t)n * 16);
+    } else {
+        HIP_TRY(ctx, hipMemcpyAsync(d_zmm, zmin_zmax, (size_t)n * 16, hipMemcpyHostToDevice, stream));
+        out.dev = d_zmm;
+    }
+    return MPR_OK;
+}
+
 struct Carver {
     char *base;
     int64_t cap, used = 0;
@@ -3249,15 +3372,6 @@ bool valid_images(const mpr_image *imgs, int n)
     return true;
 }
 
-// Head of a simulate workspace: what a resumed call checks before it
-// continues the run the workspace holds.
-struct RunHeader {
-    uint64_t magic;     // kRunMagic
-    uint64_t key;       // run_key of the images and parameters
-    int64_t bytes;      // sim_bytes of the run
-    int32_t n_chains;
-    int32_t state;      // 1: stopped at sweep_limit with chains running (resumable)
-};
 constexpr uint64_t kRunMagic = 0x4D50522D52554E31ull;  // "MPR-RUN1"
 constexpr int64_t kRunHeaderBytes = 256;
 
@@ -3435,7 +3549,10 @@ struct ChainSet {
     int64_t total_blocks[kNumShapes] = {};
     std::vector<int64_t> h_start;  // host copies (kept until their upload is done)
     std::vector<int32_t> h_ids;
-    Redo redo = {nullptr, nullptr};      // deferred double-precision updates (zeroed)
+    std::vector<char> upload;      // host copy of the descriptors' upload, unless it is staged in pinned memory
+    Redo redo = {nullptr, nullptr};      // deferred double-precision updates
+    int64_t redo_mask_bytes = 0, redo_bits_bytes = 0;
+    bool redo_clean = false;             // both zeroed
     bool fp64 = false;                   // double-precision chains (no deferred redo)
     float *states_out = nullptr;         // recorded equilibrium states (nullable)
     int64_t states_n_total = 0;          // sites of the whole batch (stride of a state)
@@ -3649,10 +3766,9 @@ hipError_t launch_resident(mpr_ctx *ctx, hipStream_t st, const ChainSet &cs, int
                                       dim3(kResThreads), args, 0, st);
 }
 
-// Builds the launch list of a chain set from the chains in `active`: block
-// prefix sums for every shape and the chain ids, uploaded on `stream` (and
-// waited for, so that the host copies can be reused).
-int set_active(mpr_ctx *ctx, ChainSet &cs, const std::vector<int32_t> &active, hipStream_t stream)
+// The launch list of a chain set from the chains in `active`: block prefix
+// sums for every shape and the chain ids, in the set's host copies.
+int list_active(mpr_ctx *ctx, ChainSet &cs, const std::vector<int32_t> &active)
 {
     const int n = (int)cs.desc.size();
     const int na = (int)active.size();
@@ -3666,18 +3782,37 @@ int set_active(mpr_ctx *ctx, ChainSet &cs, const std::vector<int32_t> &active, h
     }
     cs.h_ids = active;
     cs.n_active = na;
+    return MPR_OK;
+}
+
+// list_active, uploaded on `stream` and waited for, so that the host copies
+// can be reused.
+int set_active(mpr_ctx *ctx, ChainSet &cs, const std::vector<int32_t> &active, hipStream_t stream)
+{
+    if (int rc = list_active(ctx, cs, active)) return rc;
     HIP_TRY(ctx, hipMemcpyAsync(cs.d_start[0], cs.h_start.data(), cs.h_start.size() * 8, hipMemcpyHostToDevice,
                                 stream));
-    if (na > 0)
-        HIP_TRY(ctx, hipMemcpyAsync(cs.d_ids, cs.h_ids.data(), (size_t)na * 4, hipMemcpyHostToDevice, stream));
+    if (cs.n_active > 0)
+        HIP_TRY(ctx, hipMemcpyAsync(cs.d_ids, cs.h_ids.data(), (size_t)cs.n_active * 4, hipMemcpyHostToDevice, stream));
     HIP_TRY(ctx, hipStreamSynchronize(stream));
     return MPR_OK;
 }
 
+// Zeroes the deferred-redo buffers of a chain set (the half-sweep shapes
+// leave them zero).
+int clear_redo(mpr_ctx *ctx, ChainSet &cs, hipStream_t stream)
+{
+    if (cs.redo_clean) return MPR_OK;
+    HIP_TRY(ctx, hipMemsetAsync(cs.redo.mask, 0, (size_t)cs.redo_mask_bytes, stream));
+    HIP_TRY(ctx, hipMemsetAsync(cs.redo.blocks, 0, (size_t)cs.redo_bits_bytes, stream));
+    cs.redo_clean = true;
+    return MPR_OK;
+}
+
 // Runs sweeps until every chain is done.  Returns 0 or an error code.
-// Sweeps run on ctx->gstream: a few direct sweeps per block shape first (to
-// tune it, unless fixed or cached), then groups of `spl` sweeps replayed as
-// a captured graph (launched directly when `graphs` is false: instantiating
+// A few direct sweeps per block shape come first (to tune it, unless fixed or
+// cached), then groups of `spl` sweeps, those of the half-sweep shapes replayed
+// as a captured graph (launched directly when `graphs` is false: instantiating
 // a graph allocates), checking the done-counter after each group.  At most
 // max_sweeps sweeps run; chains still running then are an error, or with
 // `stop_ok` the result MPR_INCOMPLETE.
@@ -3703,9 +3838,7 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     }
     const SweepConsts sc = make_sc(p->q, p->seed);
     const int cblocks = (n + 63) / 64;
-    hipStream_t st = ctx->gstream;
-    HIP_TRY(ctx, hipEventRecord(ctx->ev_in, stream));
-    HIP_TRY(ctx, hipStreamWaitEvent(st, ctx->ev_in, 0));
+    hipStream_t st = stream;  // the context's own once a shape is captured into graphs
 
     // the control runs at the end of the colour-1 redo kernel unless
     // something must run between them (the state record) or there is no
@@ -3776,12 +3909,15 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     bool finished = false;
     // Runs `count` sweeps directly or as graph `ge`, timed; then polls.
     auto block = [&](int v, int count, hipGraphExec_t ge, float *ms_out) -> int {
-        HIP_TRY(ctx, hipEventRecord(ctx->ev_t0, st));
+        const bool timed = ms_out || ctx->profile;
+        if (!kShapes[v].fused && !cs.fp64)
+            if (int rc = clear_redo(ctx, cs, st)) return rc;
+        if (timed) HIP_TRY(ctx, hipEventRecord(ctx->ev_t0, st));
         if (ge) HIP_TRY(ctx, hipGraphLaunch(ge, st));
         else sweeps(v, count);
         if (perr != hipSuccess) return fail(ctx, MPR_ERR_HIP, "persistent sweep launch: %s", hipGetErrorString(perr));
         HIP_TRY(ctx, hipGetLastError());
-        HIP_TRY(ctx, hipEventRecord(ctx->ev_t1, st));
+        if (timed) HIP_TRY(ctx, hipEventRecord(ctx->ev_t1, st));
         // the done counter; after a resident launch the words up to the
         // abort word, in one copy (done counter, sweeps run, abort word)
         HIP_TRY(ctx, hipMemcpyAsync(ctx->done_host, d_done,
@@ -3795,7 +3931,7 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
             count = (int)ctx->done_host[kGenOffset / 4];
         }
         float ms = 0.0f;
-        HIP_TRY(ctx, hipEventElapsedTime(&ms, ctx->ev_t0, ctx->ev_t1));
+        if (timed) HIP_TRY(ctx, hipEventElapsedTime(&ms, ctx->ev_t0, ctx->ev_t1));
         if (ms_out) *ms_out = ms;
         if (ctx->profile) {
             ctx->prof_ms += ms;
@@ -3830,13 +3966,22 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     }
     const auto key = std::make_tuple((table ? 1 : 0) | (cs.fp64 ? 2 : 0), n, maxnx, maxny);
     float sweep_ms = -1.0f;
+    bool resident = false;
+    for (int k = 0; k < kNumShapes; ++k) resident = resident || fits(k);
+    // Half-sweeps are captured into graphs, on the context's own stream (the
+    // caller's may be the default one, which cannot be captured), ordered
+    // after and before the caller's with two events; all other shapes run on
+    // the caller's stream.
+    if (v >= 0 ? !kShapes[v].fused : !resident) {
+        st = ctx->gstream;
+        HIP_TRY(ctx, hipEventRecord(ctx->ev_in, stream));
+        HIP_TRY(ctx, hipStreamWaitEvent(st, ctx->ev_in, 0));
+    }
     if (v < 0) {
         // Where the tiles fit on the GPU only the resident shapes are timed:
         // they take 4.4 us per 64^2 sweep, 8.4 us per 1024^2 one and 28.7 us
         // per 2048^2 one (one chain), one launch per sweep 13.4, 27.4 and
         // 41.3 us at best.
-        bool resident = false;
-        for (int k = 0; k < kNumShapes; ++k) resident = resident || fits(k);
         mpr_ctx::Tuned &tn = ctx->tuned_rows[key];
         const int ts = std::max(1, std::min(poll_every, 3));
         unsigned int done_before = 0;
@@ -3960,41 +4105,14 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     }
     cap.release();
     if (rc) return rc;
-    HIP_TRY(ctx, hipEventRecord(ctx->ev_out, st));
-    HIP_TRY(ctx, hipStreamWaitEvent(stream, ctx->ev_out, 0));
+    if (st != stream) {
+        HIP_TRY(ctx, hipEventRecord(ctx->ev_out, st));
+        HIP_TRY(ctx, hipStreamWaitEvent(stream, ctx->ev_out, 0));
+    }
     if (!finished)
         return stop_ok ? MPR_INCOMPLETE
                        : fail(ctx, MPR_ERR_HIP, "chains did not finish within %lld sweeps", (long long)max_sweeps);
     return MPR_OK;
-}
-
-// Carves the launch list and the deferred-redo buffers (sized for every
-// chain) of a chain set from the workspace and fills the list with the
-// chains that are not done.
-int upload_starts(mpr_ctx *ctx, ChainSet &cs, Carver &cv, hipStream_t stream)
-{
-    const int n = (int)cs.desc.size();
-    int64_t *d = (int64_t *)cv.take((int64_t)kNumStarts * (n + 1) * 8);
-    cs.d_ids = (int32_t *)cv.take((int64_t)n * 4 + 4);
-    if (!d || !cs.d_ids) return fail(ctx, MPR_ERR_WORKSPACE, "workspace too small");
-    for (int k = 0; k < kNumStarts; ++k) cs.d_start[k] = d + (size_t)k * (n + 1);
-    int64_t words = 0, blocks = 0;
-    for (int k = 0; k < kNumShapes; ++k) {
-        int64_t b = 0;
-        for (int c = 0; c < n; ++c) b += chain_blocks(cs.desc[c], k);
-        words = std::max(words, b * redo_words(k));
-        blocks = std::max(blocks, b);
-    }
-    const int64_t mask_bytes = words * 4, bits_bytes = (blocks + 31) / 32 * 4;
-    cs.redo.mask = (uint32_t *)cv.take(mask_bytes);
-    cs.redo.blocks = (uint32_t *)cv.take(bits_bytes);
-    if (!cs.redo.mask || !cs.redo.blocks) return fail(ctx, MPR_ERR_WORKSPACE, "workspace too small");
-    HIP_TRY(ctx, hipMemsetAsync(cs.redo.mask, 0, mask_bytes, stream));
-    HIP_TRY(ctx, hipMemsetAsync(cs.redo.blocks, 0, bits_bytes, stream));
-    std::vector<int32_t> active;
-    for (int c = 0; c < n; ++c)
-        if (cs.state[c].phase != PH_DONE) active.push_back(c);
-    return set_active(ctx, cs, active, stream);
 }
 
 ChainState fresh_state(double T, int phase)
@@ -4014,16 +4132,36 @@ ChainState fresh_state(double T, int phase)
     return s;
 }
 
-// With `resume` the states are not uploaded but read back from the
-// workspace (the run it holds), and each chain whose fused sweeps left h and
-// h2 exchanged gets them exchanged in its descriptor too.
+// Carves descriptors, states, launch list and deferred-redo buffers (sized for
+// every chain) of a chain set from the workspace and uploads them, in one copy:
+// they lie one after the other.  The launch list holds the chains that are not
+// done.  With `resume` the states are read back from the workspace first (the
+// run it holds), and each chain whose fused sweeps left h and h2 exchanged gets
+// them exchanged in its descriptor too.
 int upload_chains(mpr_ctx *ctx, ChainSet &cs, Carver &cv, hipStream_t stream, double q, bool resume = false)
 {
     const int n = (int)cs.desc.size();
     cs.d_desc = (ChainDesc *)cv.take(n * (int64_t)sizeof(ChainDesc));
     cs.d_state = (ChainState *)cv.take(n * (int64_t)sizeof(ChainState));
     cs.d_offset = (int64_t *)cv.take(n * 8);
-    if (!cs.d_desc || !cs.d_state || !cs.d_offset) return fail(ctx, MPR_ERR_WORKSPACE, "workspace too small");
+    int64_t *d = (int64_t *)cv.take((int64_t)kNumStarts * (n + 1) * 8);
+    cs.d_ids = (int32_t *)cv.take((int64_t)n * 4 + 4);
+    if (!cs.d_desc || !cs.d_state || !cs.d_offset || !d || !cs.d_ids)
+        return fail(ctx, MPR_ERR_WORKSPACE, "workspace too small");
+    for (int k = 0; k < kNumStarts; ++k) cs.d_start[k] = d + (size_t)k * (n + 1);
+    int64_t words = 0, blocks = 0;
+    for (int k = 0; k < kNumShapes; ++k) {
+        int64_t b = 0;
+        for (int c = 0; c < n; ++c) b += chain_blocks(cs.desc[c], k);
+        words = std::max(words, b * redo_words(k));
+        blocks = std::max(blocks, b);
+    }
+    cs.redo_mask_bytes = words * 4;
+    cs.redo_bits_bytes = (blocks + 31) / 32 * 4;
+    cs.redo.mask = (uint32_t *)cv.take(cs.redo_mask_bytes);
+    cs.redo.blocks = (uint32_t *)cv.take(cs.redo_bits_bytes);
+    cs.redo_clean = false;
+    if (!cs.redo.mask || !cs.redo.blocks) return fail(ctx, MPR_ERR_WORKSPACE, "workspace too small");
     if (resume) {
         HIP_TRY(ctx, hipMemcpyAsync(cs.state.data(), cs.d_state, n * sizeof(ChainState), hipMemcpyDeviceToHost,
                                     stream));
@@ -4038,12 +4176,23 @@ int upload_chains(mpr_ctx *ctx, ChainSet &cs, Carver &cv, hipStream_t stream, do
             s.inv_T = (float)(1.0 / s.T);
             s.dscale = (float)(kTwoPi * q / s.a_cur);
         }
-        HIP_TRY(ctx, hipMemcpyAsync(cs.d_state, cs.state.data(), n * sizeof(ChainState), hipMemcpyHostToDevice,
-                                    stream));
     }
-    HIP_TRY(ctx, hipMemcpyAsync(cs.d_desc, cs.desc.data(), n * sizeof(ChainDesc), hipMemcpyHostToDevice, stream));
-    HIP_TRY(ctx, hipMemcpyAsync(cs.d_offset, cs.offset.data(), n * 8, hipMemcpyHostToDevice, stream));
-    return upload_starts(ctx, cs, cv, stream);
+    std::vector<int32_t> active;
+    for (int c = 0; c < n; ++c)
+        if (cs.state[c].phase != PH_DONE) active.push_back(c);
+    int rc = list_active(ctx, cs, active);
+    if (rc) return rc;
+    char *const base = (char *)cs.d_desc;
+    const int64_t bytes = (char *)(cs.d_ids + n + 1) - base;
+    char *h = stage_for(ctx, bytes, cs.upload);
+    std::memset(h, 0, (size_t)bytes);
+    std::memcpy(h, cs.desc.data(), n * sizeof(ChainDesc));
+    std::memcpy(h + ((char *)cs.d_state - base), cs.state.data(), n * sizeof(ChainState));
+    std::memcpy(h + ((char *)cs.d_offset - base), cs.offset.data(), (size_t)n * 8);
+    std::memcpy(h + ((char *)d - base), cs.h_start.data(), cs.h_start.size() * 8);
+    std::memcpy(h + ((char *)cs.d_ids - base), cs.h_ids.data(), cs.h_ids.size() * 4);
+    HIP_TRY(ctx, hipMemcpyAsync(base, h, (size_t)bytes, hipMemcpyHostToDevice, stream));
+    return MPR_OK;
 }
 
 // Allocates both half-grids (and accumulators) of a chain of `eb`-byte
@@ -4066,19 +4215,21 @@ bool carve_chain(Carver &cv, ChainDesc &d, int nx, int ny, bool with_acc, bool w
     return true;
 }
 
-// Starting angles of every chain of a set (table: pi everywhere).
+// Starting angles of every chain of a set (table: pi everywhere), and the
+// run's header, if there is one.
 void launch_init(hipStream_t stream, const ChainSet &cs, const float *phi, const uint8_t *sampled,
-                 const float *phi_init, uint64_t seed, int table)
+                 const float *phi_init, uint64_t seed, int table, const RunHeader &hdr = RunHeader{},
+                 RunHeader *d_hdr = nullptr)
 {
     int64_t groups = 1;
     for (const auto &d : cs.desc) groups = std::max(groups, (int64_t)d.ny * d.S / 2);
     const dim3 grid(blocks_for(groups, 2048), (unsigned)cs.desc.size());
     if (cs.fp64)
         hipLaunchKernelGGL(init_chains_kernel<double>, grid, dim3(kBlock), 0, stream, cs.d_desc, cs.d_offset, phi,
-                           sampled, phi_init, (uint32_t)seed, (uint32_t)(seed >> 32), table);
+                           sampled, phi_init, (uint32_t)seed, (uint32_t)(seed >> 32), table, hdr, d_hdr);
     else
         hipLaunchKernelGGL(init_chains_kernel<float>, grid, dim3(kBlock), 0, stream, cs.d_desc, cs.d_offset, phi,
-                           sampled, phi_init, (uint32_t)seed, (uint32_t)(seed >> 32), table);
+                           sampled, phi_init, (uint32_t)seed, (uint32_t)(seed >> 32), table, hdr, d_hdr);
 }
 
 // Monotone (pool-adjacent-violators) fit of y, then log T interpolated
@@ -4255,14 +4406,35 @@ int32_t mpr_map_to_angles(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, const 
         unsigned int *pbad = (unsigned int *)(pcnt + (int64_t)nb * kMapBlocks);
         double *d_zmm = (double *)(pbad + (int64_t)nb * kMapBlocks + 64);
         d_zmm = (double *)round_up((int64_t)d_zmm, 256);
-        std::vector<ImgDev> hi(nb);
-        for (int b = 0; b < nb; ++b) hi[b] = {imgs[b0 + b].offset, imgs[b0 + b].nx, imgs[b0 + b].ny};
-        HIP_TRY(ctx, hipMemcpyAsync(d_img, hi.data(), nb * sizeof(ImgDev), hipMemcpyHostToDevice, stream));
+        std::vector<ImgDev> hi;
+        ImgArgs img;
+        RangeArgs range;
+        std::memset(&range, 0, sizeof range);
+        if (int rc = image_args(ctx, stream, imgs + b0, nb, hi, d_img, img)) return rc;
         int mb = 1;  // partial blocks per image: the largest image's count (min, max and counts are exact)
-        for (int b = 0; b < nb; ++b) mb = std::max(mb, image_blocks((int64_t)hi[b].nx * hi[b].ny));
-        hipLaunchKernelGGL(map_minmax_kernel, dim3(mb, nb), dim3(kBlock), 0, stream, d_img, z, sampled, pmin,
+        int64_t maxn = 0;
+        for (int b = 0; b < nb; ++b) {
+            mb = std::max(mb, image_blocks((int64_t)hi[b].nx * hi[b].ny));
+            maxn = std::max(maxn, (int64_t)hi[b].nx * hi[b].ny);
+        }
+        hipLaunchKernelGGL(map_minmax_kernel, dim3(mb, nb), dim3(kBlock), 0, stream, img, z, sampled, pmin,
                            pmax, pcnt, pbad);
         HIP_TRY(ctx, hipGetLastError());
+        if (n == 1) {
+            // one image: its range goes from one kernel to the next on the
+            // device, and one wait ends the call
+            double *found = (double *)((char *)ctx->done_host + kHostWordsBytes);
+            hipLaunchKernelGGL(map_apply_kernel, dim3(blocks_for(maxn, 4096)), dim3(kBlock), 0, stream, img, range, mb,
+                               pmin, pmax, pcnt, pbad, found, z, sampled, phi);
+            HIP_TRY(ctx, hipGetLastError());
+            HIP_TRY(ctx, hipStreamSynchronize(stream));
+            if (found[3] != 0.0) return fail(ctx, MPR_ERR_ARG, "image 0: non-finite sampled value");
+            if (found[2] < 2.0 || !(found[1] > found[0]))
+                return fail(ctx, MPR_ERR_DEGENERATE, "image 0: fewer than 2 samples or z_max == z_min");
+            zmin_zmax[0] = found[0];
+            zmin_zmax[1] = found[1];
+            return MPR_OK;
+        }
         std::vector<float> hmin(nb * mb), hmax(nb * mb);
         std::vector<unsigned long long> hcnt(nb * mb);
         std::vector<unsigned int> hbad(nb * mb);
@@ -4298,11 +4470,9 @@ int32_t mpr_map_to_angles(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, const 
             zmin_zmax[2 * (b0 + b)] = lo;
             zmin_zmax[2 * (b0 + b) + 1] = hi2;
         }
-        HIP_TRY(ctx, hipMemcpyAsync(d_zmm, zmm.data(), zmm.size() * 8, hipMemcpyHostToDevice, stream));
-        int64_t maxn = 0;
-        for (int b = 0; b < nb; ++b) maxn = std::max(maxn, (int64_t)hi[b].nx * hi[b].ny);
-        hipLaunchKernelGGL(map_apply_kernel, dim3(blocks_for(maxn, 4096), nb), dim3(kBlock), 0, stream, d_img, d_zmm,
-                           z, sampled, phi);
+        if (int rc = range_args(ctx, stream, zmm.data(), nb, d_zmm, range)) return rc;
+        hipLaunchKernelGGL(map_apply_kernel, dim3(blocks_for(maxn, 4096), nb), dim3(kBlock), 0, stream, img, range, 0,
+                           nullptr, nullptr, nullptr, nullptr, nullptr, z, sampled, phi);
         HIP_TRY(ctx, hipGetLastError());
         HIP_TRY(ctx, hipStreamSynchronize(stream));
     }
@@ -4328,27 +4498,27 @@ int32_t mpr_estimate_temperature(mpr_ctx *ctx, const mpr_image *imgs, int32_t n,
         double *psum = (double *)cv.take((int64_t)n * kMapBlocks * 8);
         unsigned long long *pcnt = (unsigned long long *)cv.take((int64_t)n * kMapBlocks * 8);
         if (!d_img || !psum || !pcnt) return fail(ctx, MPR_ERR_WORKSPACE, "workspace too small");
-        std::vector<ImgDev> hi(n);
-        for (int b = 0; b < n; ++b) hi[b] = {imgs[b].offset, imgs[b].nx, imgs[b].ny};
-        HIP_TRY(ctx, hipMemcpyAsync(d_img, hi.data(), n * sizeof(ImgDev), hipMemcpyHostToDevice, stream));
+        std::vector<ImgDev> hi;
+        ImgArgs img;
+        if (int rc = image_args(ctx, stream, imgs, n, hi, d_img, img)) return rc;
         int mb = 1;  // the grid covers the largest image; each image uses image_blocks of its own size
         for (int b = 0; b < n; ++b) mb = std::max(mb, image_blocks((int64_t)hi[b].nx * hi[b].ny));
-        hipLaunchKernelGGL(sample_energy_kernel, dim3(mb, n), dim3(kBlock), 0, stream, d_img, phi, sampled,
-                           p->q, psum, pcnt);
+        // the partial sums and counts straight into pinned host memory where
+        // they fit, else through the workspace and one copy
+        const int64_t parts = (int64_t)n * mb;
+        const bool direct = parts * 16 <= kHostStageBytes - kHostWordsBytes;
+        std::vector<char> big;
+        char *h = stage_for(ctx, direct ? parts * 16 : (const char *)(pcnt + parts) - (const char *)psum, big);
+        double *os = direct ? (double *)h : psum;
+        unsigned long long *oc = direct ? (unsigned long long *)(h + parts * 8) : pcnt;
+        hipLaunchKernelGGL(sample_energy_kernel, dim3(mb, n), dim3(kBlock), 0, stream, img, phi, sampled, p->q, os, oc);
         HIP_TRY(ctx, hipGetLastError());
-        std::vector<double> hs((size_t)n * mb);
-        std::vector<unsigned long long> hc((size_t)n * mb);
-        // the sums, then the counts (carved after them): one copy
-        {
-            const char *src = (const char *)psum;
-            const int64_t span = (const char *)(pcnt + (int64_t)n * mb) - src;
-            std::vector<char> big;
-            char *h = stage_for(ctx, span, big);
-            HIP_TRY(ctx, hipMemcpyAsync(h, src, (size_t)span, hipMemcpyDeviceToHost, stream));
-            HIP_TRY(ctx, hipStreamSynchronize(stream));
-            std::memcpy(hs.data(), h, hs.size() * 8);
-            std::memcpy(hc.data(), h + ((const char *)pcnt - src), hc.size() * 8);
-        }
+        if (!direct)
+            HIP_TRY(ctx, hipMemcpyAsync(h, psum, (size_t)((const char *)(pcnt + parts) - (const char *)psum),
+                                        hipMemcpyDeviceToHost, stream));
+        HIP_TRY(ctx, hipStreamSynchronize(stream));
+        const double *hs = (const double *)h;
+        const unsigned long long *hc = (const unsigned long long *)(h + ((const char *)oc - (const char *)os));
         for (int b = 0; b < n; ++b) {
             double s = 0.0;
             unsigned long long c = 0;
@@ -4489,13 +4659,11 @@ static int32_t simulate_call(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, con
             return fail(ctx, MPR_ERR_ARG,
                         "simulate: resume needs a workspace holding a run stopped at sweep_limit with the same "
                         "images, parameters and temperatures");
-    } else {
-        HIP_TRY(ctx, hipMemcpyAsync(d_hdr, &hdr, sizeof hdr, hipMemcpyHostToDevice, stream));
     }
     ImgDev *d_img = (ImgDev *)cv.take(n * (int64_t)sizeof(ImgDev));
-    std::vector<ImgDev> hi(n);
-    for (int b = 0; b < n; ++b) hi[b] = {imgs[b].offset, imgs[b].nx, imgs[b].ny};
-    HIP_TRY(ctx, hipMemcpyAsync(d_img, hi.data(), n * sizeof(ImgDev), hipMemcpyHostToDevice, stream));
+    std::vector<ImgDev> hi;
+    ImgArgs img;
+    if (int rc = image_args(ctx, stream, imgs, n, hi, d_img, img)) return rc;
     std::vector<int64_t> gaps(n, 0);
     {
         // count gaps with the map reduction on a constant z
@@ -4509,12 +4677,16 @@ static int32_t simulate_call(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, con
         unsigned int *pbad = (unsigned int *)(pcnt + (int64_t)n * mb);
         if ((int64_t)n * mb * 24 + 512 > (int64_t)kScratchBytes - kVarOffset)
             return fail(ctx, MPR_ERR_ARG, "too many images in one call");
-        // map_minmax counts sampled sites of finite value; phi is finite
-        hipLaunchKernelGGL(map_minmax_kernel, dim3(mb, n), dim3(kBlock), 0, stream, d_img, phi, sampled, pmin,
-                           pmax, pcnt, pbad);
+        // map_minmax counts sampled sites of finite value; phi is finite.  The
+        // counts go straight into pinned host memory where they fit.
+        const int64_t cnt_bytes = (int64_t)n * mb * 8;
+        std::vector<char> big;
+        unsigned long long *hc = (unsigned long long *)stage_for(ctx, cnt_bytes, big);
+        const bool direct = big.empty();
+        hipLaunchKernelGGL(map_minmax_kernel, dim3(mb, n), dim3(kBlock), 0, stream, img, phi, sampled, pmin,
+                           pmax, direct ? hc : pcnt, pbad);
         HIP_TRY(ctx, hipGetLastError());
-        std::vector<unsigned long long> hc((size_t)n * mb);
-        HIP_TRY(ctx, hipMemcpyAsync(hc.data(), pcnt, hc.size() * 8, hipMemcpyDeviceToHost, stream));
+        if (!direct) HIP_TRY(ctx, hipMemcpyAsync(hc, pcnt, (size_t)cnt_bytes, hipMemcpyDeviceToHost, stream));
         HIP_TRY(ctx, hipStreamSynchronize(stream));
         for (int b = 0; b < n; ++b) {
             unsigned long long c = 0;
@@ -4558,7 +4730,7 @@ static int32_t simulate_call(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, con
     int64_t maxn = 0;
     for (int b = 0; b < n; ++b) maxn = std::max(maxn, (int64_t)imgs[b].nx * imgs[b].ny);
     if (!resume) {
-        launch_init(stream, cs, phi, sampled, phi_init, p->seed, 0);
+        launch_init(stream, cs, phi, sampled, phi_init, p->seed, 0, hdr, d_hdr);
         HIP_TRY(ctx, hipGetLastError());
     }
     // sweeps left to the run's cap (a resumed run has done `swept` of them),
@@ -4579,20 +4751,24 @@ static int32_t simulate_call(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, con
     if (!incomplete) {  // an incomplete run writes no outputs, only its statistics so far
         if (cs.fp64)
             hipLaunchKernelGGL(finalize_fp64_kernel, dim3(blocks_for(maxn, 4096), n), dim3(kBlock), 0, stream,
-                               cs.d_desc, d_img, p->R, p->K, sampled, phi_sum, phi_m2);
+                               cs.d_desc, img, p->R, p->K, sampled, phi_sum, phi_m2);
         else
             hipLaunchKernelGGL(finalize_kernel, dim3(blocks_for(maxn, 4096), n), dim3(kBlock), 0, stream,
-                               cs.d_desc, d_img, p->R, p->K, sampled, phi_sum, phi_m2);
+                               cs.d_desc, img, p->R, p->K, sampled, phi_sum, phi_m2);
         HIP_TRY(ctx, hipGetLastError());
     }
+    std::vector<char> big;
+    const ChainState *final_state = nullptr;
     if (stats) {
-        HIP_TRY(ctx, hipMemcpyAsync(cs.state.data(), cs.d_state, cs.state.size() * sizeof(ChainState),
-                                    hipMemcpyDeviceToHost, stream));
+        const int64_t bytes = (int64_t)(cs.state.size() * sizeof(ChainState));
+        char *h = stage_for(ctx, bytes, big);
+        HIP_TRY(ctx, hipMemcpyAsync(h, cs.d_state, (size_t)bytes, hipMemcpyDeviceToHost, stream));
+        final_state = (const ChainState *)h;
     }
     HIP_TRY(ctx, hipStreamSynchronize(stream));
     if (stats) {
         for (size_t c = 0; c < cs.state.size(); ++c) {
-            const ChainState &s = cs.state[c];
+            const ChainState &s = final_state[c];
             stats[c].relax_sweeps = s.relax_sweeps;
             stats[c].not_converged = s.not_converged;
             stats[c].a_final = s.a_relax;
@@ -4649,15 +4825,14 @@ int32_t mpr_predict(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, const float 
     char *sp = (char *)ctx->scratch + kVarOffset;
     ImgDev *d_img = (ImgDev *)sp;
     double *d_zmm = (double *)(sp + round_up((int64_t)n * sizeof(ImgDev), 256));
-    std::vector<ImgDev> hi(n);
     int64_t maxn = 0;
-    for (int b = 0; b < n; ++b) {
-        hi[b] = {imgs[b].offset, imgs[b].nx, imgs[b].ny};
-        maxn = std::max(maxn, (int64_t)imgs[b].nx * imgs[b].ny);
-    }
-    HIP_TRY(ctx, hipMemcpyAsync(d_img, hi.data(), n * sizeof(ImgDev), hipMemcpyHostToDevice, stream));
-    HIP_TRY(ctx, hipMemcpyAsync(d_zmm, zmin_zmax, n * 16, hipMemcpyHostToDevice, stream));
-    hipLaunchKernelGGL(predict_kernel, dim3(blocks_for(maxn, 4096), n), dim3(kBlock), 0, stream, d_img, d_zmm, M, z,
+    for (int b = 0; b < n; ++b) maxn = std::max(maxn, (int64_t)imgs[b].nx * imgs[b].ny);
+    std::vector<ImgDev> hi;
+    ImgArgs img;
+    RangeArgs range;
+    if (int rc = image_args(ctx, stream, imgs, n, hi, d_img, img)) return rc;
+    if (int rc = range_args(ctx, stream, zmin_zmax, n, d_zmm, range)) return rc;
+    hipLaunchKernelGGL(predict_kernel, dim3(blocks_for(maxn, 4096), n), dim3(kBlock), 0, stream, img, range, M, z,
                        sampled, phi_sum, z_hat);
     HIP_TRY(ctx, hipGetLastError());
     // the host arrays above must outlive the copies
@@ -4671,7 +4846,7 @@ int32_t mpr_quantiles(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, const floa
 {
     if (!ctx) return MPR_ERR_ARG;
     if (!valid_images(imgs, n) || !z || !sampled || !phi_states || !probs || !zmin_zmax || !z_q || M < 1 ||
-        M > kMaxQuantileStates || nq < 1 || nq > 64)
+        M > kMaxQuantileStates || nq < 1 || nq > kMaxProbs)
         return fail(ctx, MPR_ERR_ARG, "quantiles: invalid argument (1 <= M <= %d, 1 <= nq <= 64)",
                     kMaxQuantileStates);
     for (int k = 0; k < nq; ++k)
@@ -4687,19 +4862,21 @@ int32_t mpr_quantiles(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, const floa
     char *sp = (char *)ctx->scratch + kVarOffset;
     ImgDev *d_img = (ImgDev *)sp;
     double *d_zmm = (double *)(sp + img_bytes);
-    double *d_probs = (double *)(sp + img_bytes + round_up((int64_t)n * 16, 256));
-    std::vector<ImgDev> hi(n);
+    std::vector<ImgDev> hi;
     int64_t maxn = 0, n_total = 0;
     for (int b = 0; b < n; ++b) {
-        hi[b] = {imgs[b].offset, imgs[b].nx, imgs[b].ny};
         maxn = std::max(maxn, (int64_t)imgs[b].nx * imgs[b].ny);
         n_total = std::max(n_total, imgs[b].offset + (int64_t)imgs[b].nx * imgs[b].ny);
     }
-    HIP_TRY(ctx, hipMemcpyAsync(d_img, hi.data(), n * sizeof(ImgDev), hipMemcpyHostToDevice, stream));
-    HIP_TRY(ctx, hipMemcpyAsync(d_zmm, zmin_zmax, n * 16, hipMemcpyHostToDevice, stream));
-    HIP_TRY(ctx, hipMemcpyAsync(d_probs, probs, nq * 8, hipMemcpyHostToDevice, stream));
+    ImgArgs img;
+    RangeArgs range;
+    ProbArgs pr;
+    if (int rc = image_args(ctx, stream, imgs, n, hi, d_img, img)) return rc;
+    if (int rc = range_args(ctx, stream, zmin_zmax, n, d_zmm, range)) return rc;
+    std::memset(&pr, 0, sizeof pr);
+    std::memcpy(pr.v, probs, (size_t)nq * 8);
     // the smallest network that holds M states
-    using Launch = void (*)(hipStream_t, int64_t, int, const ImgDev *, const double *, const double *, int,
+    using Launch = void (*)(hipStream_t, int64_t, int, const ImgArgs &, const RangeArgs &, const ProbArgs &, int,
                             const float *, const uint8_t *, const float *, int, int64_t, float *);
     static constexpr Launch kNets[16] = {
         launch_quantiles<8, false>,   launch_quantiles<16, false>,  launch_quantiles<24, false>,
@@ -4708,7 +4885,7 @@ int32_t mpr_quantiles(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, const floa
         launch_quantiles<80, false>,  launch_quantiles<88, false>,  launch_quantiles<96, false>,
         launch_quantiles<104, false>, launch_quantiles<112, false>, launch_quantiles<120, false>,
         launch_quantiles<128, false>};
-    (M <= 128 ? kNets[(M - 1) / 8] : launch_quantiles<128, true>)(stream, maxn, n, d_img, d_zmm, d_probs, nq, z, sampled,
+    (M <= 128 ? kNets[(M - 1) / 8] : launch_quantiles<128, true>)(stream, maxn, n, img, range, pr, nq, z, sampled,
                                                                    phi_states, M, n_total, z_q);
     HIP_TRY(ctx, hipGetLastError());
     HIP_TRY(ctx, hipStreamSynchronize(stream));
@@ -4730,15 +4907,14 @@ int32_t mpr_spread(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, const uint8_t
     char *sp = (char *)ctx->scratch + kVarOffset;
     ImgDev *d_img = (ImgDev *)sp;
     double *d_zmm = (double *)(sp + round_up((int64_t)n * sizeof(ImgDev), 256));
-    std::vector<ImgDev> hi(n);
     int64_t maxn = 0;
-    for (int b = 0; b < n; ++b) {
-        hi[b] = {imgs[b].offset, imgs[b].nx, imgs[b].ny};
-        maxn = std::max(maxn, (int64_t)imgs[b].nx * imgs[b].ny);
-    }
-    HIP_TRY(ctx, hipMemcpyAsync(d_img, hi.data(), n * sizeof(ImgDev), hipMemcpyHostToDevice, stream));
-    HIP_TRY(ctx, hipMemcpyAsync(d_zmm, zmin_zmax, n * 16, hipMemcpyHostToDevice, stream));
-    hipLaunchKernelGGL(spread_kernel, dim3(blocks_for(maxn, 4096), n), dim3(kBlock), 0, stream, d_img, d_zmm, M,
+    for (int b = 0; b < n; ++b) maxn = std::max(maxn, (int64_t)imgs[b].nx * imgs[b].ny);
+    std::vector<ImgDev> hi;
+    ImgArgs img;
+    RangeArgs range;
+    if (int rc = image_args(ctx, stream, imgs, n, hi, d_img, img)) return rc;
+    if (int rc = range_args(ctx, stream, zmin_zmax, n, d_zmm, range)) return rc;
+    hipLaunchKernelGGL(spread_kernel, dim3(blocks_for(maxn, 4096), n), dim3(kBlock), 0, stream, img, range, M,
                        sampled, phi_m2, z_std);
     HIP_TRY(ctx, hipGetLastError());
     HIP_TRY(ctx, hipStreamSynchronize(stream));
@@ -4921,6 +5097,7 @@ int32_t mpr_diag_half_sweep(mpr_ctx *ctx, int32_t nx, int32_t ny, float *phi, co
     cs.state.push_back(st);
     cs.offset.push_back(0);
     int rc = upload_chains(ctx, cs, cv, stream, q);
+    if (!rc) rc = clear_redo(ctx, cs, stream);
     if (rc) {
         (void)hipFree(buf);
         return rc;
