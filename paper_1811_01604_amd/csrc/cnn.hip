@@ -91,15 +91,17 @@ __device__ __forceinline__ int out_channel(int r) { return 16 * ((r >> 2) & 1) +
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 __device__ __forceinline__ uint32_t word_of(const uint4 &v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+// two values per conversion instruction
+__device__ __forceinline__ uint32_t pack2_bf16(float a, float b)
+{
+    const f32x2 f = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
+}
 __device__ __forceinline__ uint4 pack_bf16(const float (&v)[8])
 {
-    union {
-        bf16 b[8];
-        uint4 u;
-    } p;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) p.b[i] = (bf16)v[i];
-    return p.u;
+    return make_uint4(pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]), pack2_bf16(v[4], v[5]), pack2_bf16(v[6], v[7]));
 }
 
 __device__ __forceinline__ void conv_tile_origin(int tile, int tiles_x, int tiles_y, int &n, int &y0, int &x0)
@@ -350,27 +352,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
-// A residual block of the inference forward pass in one kernel:
+// A residual block of the forward pass in one kernel:
 //   out = h + conv2(t) + b2,  t = bf16(ReLU(conv1(h) + b1))
 // with the inner activation t kept on chip instead of a round trip through
-// HBM.  Persistent blocks of 8 waves, one per CU, loop over 14 x 30-pixel
-// output tiles; both layers' packed weights stay in LDS for the whole
-// kernel.  The (14 + 4) x (30 + 4) input pixels around a tile are staged in
-// LDS like conv3x3_kernel's tile (the same 18 x 34 shape), and conv1
-// computes t on the 16 x 32 pixels around the output tile, each wave two
-// rows (the MFMA scheme of conv3x3_kernel, whose products for one output
-// row come in the same order), so two waves per SIMD hide each other's LDS
-// latency.  Each lane then keeps the skip inputs of its conv2 outputs in
-// registers, and t, rounded to bfloat16 as the layer-by-layer path stores
-// it, overwrites the staged tile (zero outside the image, conv2's zero
-// padding, and in the tile's last two rows and columns).  conv2 computes
-// 16 x 32 outputs of which the first 14 x 30 are the tile's (the rest read
-// the zero border); the next tile's pixels are loaded into registers while
-// it runs, and its epilogue adds b2 and the skip input.  Every product and
-// rounding is that of the two conv3x3_kernel launches, so the output is the
-// same bits.  Tiles are ordered so that each XCD takes a contiguous run of
-// them: tiles in flight on one XCD are neighbours and share their halo
-// pixels in its L2.
+// HBM (KEEP: a training pass also writes it out).  Persistent blocks of 8
+// waves loop over 14 x 30-pixel output tiles.  The 18 x 34 input pixels around
+// a tile are staged in LDS, conv1 computes t on the 16 x 32 pixels around the
+// tile, each wave two rows (the MFMA scheme of conv3x3_kernel, whose products
+// for one output row come in the same order).  Each lane then keeps the skip
+// inputs of its conv2 outputs in registers, and t, rounded to bfloat16 as the
+// layer-by-layer path stores it (zero outside the image, conv2's padding),
+// overwrites the staged tile.  conv2 computes the tile from it; the products
+// of its last rows and columns read values beyond t, and are dropped.  Every
+// product and rounding is that of the two conv3x3_kernel launches, so the
+// output is the same bits.
+//
+// Bound by the chain of LDS reads, products and epilogues between barriers
+// (matrix cores and LDS are each busy for 35 to 40% of the time with one block
+// per CU, two waves per SIMD, which wait 42% of theirs), so two blocks share a
+// CU: 76 KB of LDS, both layers' weights in it, and at most 128 registers.
+// LDS holds the four 16-byte channel chunks of the pixels (and of the weight
+// rows) in planes of their own: 32 lanes read 512 contiguous bytes, without
+// bank conflicts, and every operand is an immediate offset from one address.
+// Measured: 2048^2 162 us, against 205 with one block per CU, conv2's
+// weights in registers and 80-byte pixels, and 212 in a version of that with
+// two input buffers and half as many barriers; with KEEP 32 images of 256^2 124
+// us, against 62 + 78 in two convolutions.  Tiles are ordered so that each
+// XCD takes a contiguous run of them: tiles in flight on one XCD are
+// neighbours and share their halo pixels in its L2.
 constexpr int RTH = CTH - 2, RTW = CTW - 2;             // output tile of the fused block
 
 struct ResArgs {
@@ -379,6 +388,7 @@ struct ResArgs {
     const bf16 *w2;
     const float *b1;
     const float *b2;
+    bf16 *t;           // inner activation, written with KEEP
     bf16 *out;
     int N, H, W;
 };
@@ -397,17 +407,10 @@ constexpr int RES_NT = 512;                                          // threads 
 constexpr int RES_PT = (C_CHUNKS + RES_NT - 1) / RES_NT;             // staged chunks per thread
 constexpr int W_CHUNKS = C_W_ROWS * 4;                               // 16-byte chunks of one layer's weights
 
-// One layer's packed weights into LDS rows of 80 B, in the operand's order.
-__device__ __forceinline__ void res_copy_w(const bf16 *__restrict__ w, bf16 *wl)
-{
-    for (int k = (int)threadIdx.x; k < W_CHUNKS; k += RES_NT) {
-        const int row = k >> 2, src = (row & ~(CH - 1)) + out_channel(row & (CH - 1));
-        *reinterpret_cast<uint4 *>(wl + row * PIXS + (k & 3) * 8) =
-            *reinterpret_cast<const uint4 *>(w + src * CH + (k & 3) * 8);
-    }
-}
+constexpr int R_PLANE = C_IN_T * 16;   // bytes of one channel chunk of a staged tile
+constexpr int R_WPLANE = C_W_ROWS * 16;
 
-// conv_load_tile / conv_store_tile for 512-thread blocks.
+// conv_load_tile / conv_store_tile for 512-thread blocks and chunk planes.
 __device__ __forceinline__ void res_load_tile(const bf16 *__restrict__ src, int n, int H, int W, int y0, int x0,
                                               uint4 (&r)[RES_PT], uint32_t &valid)
 {
@@ -425,28 +428,32 @@ __device__ __forceinline__ void res_load_tile(const bf16 *__restrict__ src, int 
     }
 }
 
-__device__ __forceinline__ void res_store_tile(bf16 *tile, const uint4 (&r)[RES_PT], uint32_t valid)
+__device__ __forceinline__ void res_store_tile(char *tile, const uint4 (&r)[RES_PT], uint32_t valid)
 {
+    char *p = tile + (threadIdx.x & 3) * R_PLANE + (threadIdx.x >> 2) * 16;
 #pragma unroll
-    for (int j = 0; j < RES_PT; ++j) {
-        const int k = (int)threadIdx.x + RES_NT * j;
-        if (k < C_CHUNKS)
-            *reinterpret_cast<uint4 *>(tile + (k >> 2) * PIXS + (k & 3) * 8) =
+    for (int j = 0; j < RES_PT; ++j)
+        if ((int)threadIdx.x + RES_NT * j < C_CHUNKS)
+            *reinterpret_cast<uint4 *>(p + j * (RES_NT / 4) * 16) =
                 ((valid >> j) & 1u) ? r[j] : make_uint4(0u, 0u, 0u, 0u);
+}
+
+// One layer's packed weights into LDS, rows in the operand's order.
+__device__ __forceinline__ void res_copy_w(const bf16 *__restrict__ w, char *wl)
+{
+    for (int k = (int)threadIdx.x; k < W_CHUNKS; k += RES_NT) {
+        const int row = k >> 2, src = (row & ~(CH - 1)) + out_channel(row & (CH - 1));
+        *reinterpret_cast<uint4 *>(wl + (k & 3) * R_WPLANE + row * 16) =
+            *reinterpret_cast<const uint4 *>(w + src * CH + (k & 3) * 8);
     }
 }
 
-// One convolution's products over a staged tile for wave w's output rows
-// 2w and 2w + 1 (pixel column m = lane & 31, weights from LDS rows of
-// 80 B): per output row the products of conv3x3_kernel in its order (column
-// shift dx, channel chunk kh, row tap d).
-__device__ __forceinline__ void res_products(const bf16 *tile, const bf16 *wl, int wave, int m, int kq,
-                                             f32x16 (&acc)[2])
+// One convolution's products over a staged tile for a wave's two output rows,
+// in conv3x3_kernel's order per row (column shift dx, channel half kh, row tap
+// d).  tile, wl: this lane's pixel of the first staged row and its weight row,
+// in the plane of its chunk of channel half 0.
+__device__ __forceinline__ void res_products(const char *tile, const char *wl, f32x16 (&acc)[2])
 {
-#pragma unroll
-    for (int o = 0; o < 2; ++o)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[o][i] = 0.0f;
 #pragma unroll
     for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
@@ -454,52 +461,27 @@ __device__ __forceinline__ void res_products(const bf16 *tile, const bf16 *wl, i
             bf16x8 wa[3];
 #pragma unroll
             for (int d = 0; d < 3; ++d)
-                wa[d] = *reinterpret_cast<const bf16x8 *>(wl + ((d * 3 + dx) * CH + m) * PIXS + kh * 16 + kq * 8);
+                wa[d] = *reinterpret_cast<const bf16x8 *>(wl + kh * 2 * R_WPLANE + (d * 3 + dx) * CH * 16);
 #pragma unroll
             for (int ir = 0; ir < 4; ++ir) {
-                const bf16x8 pb = *reinterpret_cast<const bf16x8 *>(
-                    tile + ((2 * wave + ir) * C_IN_W + m + dx) * PIXS + kh * 16 + kq * 8);
+                const bf16x8 pb =
+                    *reinterpret_cast<const bf16x8 *>(tile + kh * 2 * R_PLANE + (ir * C_IN_W + dx) * 16);
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
                     const int o = ir - d;
                     if (o < 0 || o > 1) continue;
-                    acc[o] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[d], pb, acc[o], 0, 0, 0);
+                    const f32x16 zero = {};
+                    acc[o] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[d], pb, dx + kh + d == 0 ? zero : acc[o], 0, 0, 0);
                 }
             }
         }
 }
 
-// res_products with the weight operands in registers: this lane's output
-// channel m and input-channel half kq, per column shift dx, channel chunk
-// kh and row tap d.
-__device__ __forceinline__ void res_products_reg(const bf16 *tile, const bf16x8 (&wr)[3][2][3], int wave, int m,
-                                                 int kq, f32x16 (&acc)[2])
+template <bool KEEP>
+__global__ __launch_bounds__(RES_NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void resblock_kernel(ResArgs a)
 {
-#pragma unroll
-    for (int o = 0; o < 2; ++o)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[o][i] = 0.0f;
-#pragma unroll
-    for (int dx = 0; dx < 3; ++dx)
-#pragma unroll
-        for (int kh = 0; kh < 2; ++kh)
-#pragma unroll
-            for (int ir = 0; ir < 4; ++ir) {
-                const bf16x8 pb = *reinterpret_cast<const bf16x8 *>(
-                    tile + ((2 * wave + ir) * C_IN_W + m + dx) * PIXS + kh * 16 + kq * 8);
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    const int o = ir - d;
-                    if (o < 0 || o > 1) continue;
-                    acc[o] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[dx][kh][d], pb, acc[o], 0, 0, 0);
-                }
-            }
-}
-
-__global__ __launch_bounds__(RES_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void resblock_kernel(ResArgs a)
-{
-    __shared__ __attribute__((aligned(16))) bf16 tile[C_IN_T * PIXS];  // staged input, then t: 18 x 34 pixels
-    __shared__ __attribute__((aligned(16))) bf16 wl1[C_W_ROWS * PIXS];  // conv1's packed weights
+    __shared__ __attribute__((aligned(16))) char tile[4 * R_PLANE];     // staged input, then t: 18 x 34 pixels
+    __shared__ __attribute__((aligned(16))) char wl[2][4 * R_WPLANE];   // both layers' packed weights
     __shared__ float bl[2 * CH];                                        // b1, b2
     const int tiles_x = (a.W + RTW - 1) / RTW, tiles_y = (a.H + RTH - 1) / RTH;
     const int n_tiles = tiles_x * tiles_y * a.N;
@@ -509,17 +491,12 @@ __global__ __launch_bounds__(RES_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         bl[threadIdx.x] = a.b1[threadIdx.x];
         bl[CH + threadIdx.x] = a.b2[threadIdx.x];
     }
-    // conv1's weights in LDS, conv2's weight operands in registers, for the whole kernel
-    res_copy_w(a.w1, wl1);
-    bf16x8 w2r[3][2][3];
-#pragma unroll
-    for (int dx = 0; dx < 3; ++dx)
-#pragma unroll
-        for (int kh = 0; kh < 2; ++kh)
-#pragma unroll
-            for (int d = 0; d < 3; ++d)
-                w2r[dx][kh][d] =
-                    *reinterpret_cast<const bf16x8 *>(a.w2 + ((d * 3 + dx) * CH + out_channel(m)) * CH + kh * 16 + kq * 8);
+    res_copy_w(a.w1, wl[0]);
+    res_copy_w(a.w2, wl[1]);
+    const char *const pix0 = tile + kq * R_PLANE + (2 * wave * C_IN_W + m) * 16;
+    const char *const w1 = wl[0] + kq * R_WPLANE + m * 16, *const w2 = wl[1] + kq * R_WPLANE + m * 16;
+    // this lane's pixel of staged row 2 wave, in the plane of channels 16 kq .. 16 kq + 7
+    char *const own = tile + 2 * kq * R_PLANE + (2 * wave * C_IN_W + m) * 16;
     // this block's tiles: the blocks of XCD x = blockIdx % 8 (there are
     // ceil((G - x) / 8) of them) take a contiguous run of the tile sequence
     // in proportion to their number, in turn
@@ -532,10 +509,25 @@ __global__ __launch_bounds__(RES_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     int tile_id = t_lo + ((int)blockIdx.x >> 3);
     uint4 pre[RES_PT];
     uint32_t pre_valid = 0u;
-    if (tile_id < t_hi) {
+    // a tile whose staged pixels all lie in the image needs no clamps
+    auto load = [&](int id) {
         int n, y0, x0;
-        res_tile_origin(tile_id, tiles_x, tiles_y, n, y0, x0);
-        res_load_tile(a.in, n, a.H, a.W, y0 - 1, x0 - 1, pre, pre_valid);
+        res_tile_origin(id, tiles_x, tiles_y, n, y0, x0);
+        if (y0 >= 2 && x0 >= 2 && y0 + RTH + 2 <= a.H && x0 + RTW + 2 <= a.W) {
+            const bf16 *src = a.in + (((int64_t)n * a.H + y0 - 2) * a.W + x0 - 2) * CH;
+#pragma unroll
+            for (int j = 0; j < RES_PT; ++j) {
+                const int k = min((int)threadIdx.x + RES_NT * j, C_CHUNKS - 1), pix = k >> 2;
+                pre[j] = *reinterpret_cast<const uint4 *>(
+                    src + (uint32_t)((pix / C_IN_W) * a.W + pix % C_IN_W) * CH + (k & 3) * 8);
+            }
+            pre_valid = ~0u;
+        } else {
+            res_load_tile(a.in, n, a.H, a.W, y0 - 1, x0 - 1, pre, pre_valid);
+        }
+    };
+    if (tile_id < t_hi) {
+        load(tile_id);
         res_store_tile(tile, pre, pre_valid);
     }
     __syncthreads();
@@ -544,7 +536,7 @@ __global__ __launch_bounds__(RES_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         res_tile_origin(tile_id, tiles_x, tiles_y, n, y0, x0);
         f32x16 acc[2];
         // conv1: t at rows y0 - 1 + 2 wave + o, columns x0 - 1 + m
-        res_products(tile, wl1, wave, m, kq, acc);
+        res_products(pix0, w1, acc);
         // the skip inputs of this lane's conv2 outputs (staged pixel
         // (2 wave + o + 2, m + 2)), read before t overwrites the tile
         uint4 skip[2][2];
@@ -553,7 +545,7 @@ __global__ __launch_bounds__(RES_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #pragma unroll
             for (int j = 0; j < 2; ++j)
                 skip[o][j] = *reinterpret_cast<const uint4 *>(
-                    tile + (min(2 * wave + o + 2, CTH + 1) * C_IN_W + m + 2) * PIXS + 16 * kq + 8 * j);
+                    own + j * R_PLANE + (2 * wave < RTH ? ((o + 2) * C_IN_W + 2) * 16 : 0));
         __syncthreads();  // every wave is done with the input tile
         {
             const int gx = x0 - 1 + m;
@@ -561,39 +553,32 @@ __global__ __launch_bounds__(RES_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             for (int o = 0; o < 2; ++o) {
                 const int tr = 2 * wave + o, gy = y0 - 1 + tr;
                 const bool inside = gy >= 0 && gy < a.H && gx >= 0 && gx < a.W;
+                const bool kept = KEEP && inside && tr >= 1 && tr <= RTH && m >= 1 && m <= RTW;
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     const int c0 = 16 * kq + 8 * j;
                     float v[8];
 #pragma unroll
-                    for (int r = 0; r < 8; ++r) v[r] = inside ? fmaxf(acc[o][8 * j + r] + bl[c0 + r], 0.0f) : 0.0f;
-                    *reinterpret_cast<uint4 *>(tile + (tr * C_IN_W + m) * PIXS + c0) = pack_bf16(v);
+                    for (int r = 0; r < 8; ++r) v[r] = fmaxf(acc[o][8 * j + r] + bl[c0 + r], 0.0f);
+                    uint4 tv = pack_bf16(v);
+                    if (!inside) tv = make_uint4(0u, 0u, 0u, 0u);
+                    *reinterpret_cast<uint4 *>(own + j * R_PLANE + o * C_IN_W * 16) = tv;
+                    if (kept) *reinterpret_cast<uint4 *>(a.t + (((int64_t)n * a.H + gy) * a.W + gx) * CH + c0) = tv;
                 }
-            }
-            // the tile's last two rows and columns: zero
-            for (int k = threadIdx.x; k < (2 * C_IN_W + 2 * CTH) * 4; k += RES_NT) {
-                const int q = k >> 2, chunk = k & 3;
-                const int pix = q < 2 * C_IN_W ? (CTH + q / C_IN_W) * C_IN_W + q % C_IN_W
-                                               : ((q - 2 * C_IN_W) >> 1) * C_IN_W + CTW + ((q - 2 * C_IN_W) & 1);
-                *reinterpret_cast<uint4 *>(tile + pix * PIXS + chunk * 8) = make_uint4(0u, 0u, 0u, 0u);
             }
         }
         __syncthreads();  // t is in LDS
         // the next tile's pixels, in flight during conv2 and the epilogue
         const bool more = tile_id + step < t_hi;
-        if (more) {
-            int n2, y2, x2;
-            res_tile_origin(tile_id + step, tiles_x, tiles_y, n2, y2, x2);
-            res_load_tile(a.in, n2, a.H, a.W, y2 - 1, x2 - 1, pre, pre_valid);
-        }
+        if (more) load(tile_id + step);
         // conv2: outputs at rows y0 + 2 wave + o, columns x0 + m
-        res_products_reg(tile, w2r, wave, m, kq, acc);
-        {
+        if (2 * wave < RTH) {
+            res_products(pix0, w2, acc);
             const int gx = x0 + m;
 #pragma unroll
             for (int o = 0; o < 2; ++o) {
-                const int orow = 2 * wave + o, gy = y0 + orow;
-                if (orow >= RTH || m >= RTW || gy >= a.H || gx >= a.W) continue;
+                const int gy = y0 + 2 * wave + o;
+                if (m >= RTW || gy >= a.H || gx >= a.W) continue;
                 const int64_t pix = ((int64_t)n * a.H + gy) * a.W + gx;
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
@@ -1007,8 +992,9 @@ void launch_conv_io(hipStream_t st, bool stem, const bf16 *in, const bf16 *wpack
     else hipLaunchKernelGGL(conv3x3_kernel<8>, grid, dim3(256), 0, st, a);
 }
 
+// (t null: inference, the inner activation is not kept)
 void launch_resblock(hipStream_t st, const bf16 *in, const bf16 *w1, const float *b1, const bf16 *w2,
-                     const float *b2, bf16 *out, int n, int h, int w)
+                     const float *b2, bf16 *t, bf16 *out, int n, int h, int w)
 {
     ResArgs a;
     a.in = in;
@@ -1016,13 +1002,16 @@ void launch_resblock(hipStream_t st, const bf16 *in, const bf16 *w1, const float
     a.w2 = w2;
     a.b1 = b1;
     a.b2 = b2;
+    a.t = t;
     a.out = out;
     a.N = n;
     a.H = h;
     a.W = w;
-    // persistent: one 512-thread block per compute unit (95 KB of LDS)
+    // persistent: two 512-thread blocks per compute unit (76 KB of LDS each)
     const int64_t tiles = (int64_t)n * ((h + RTH - 1) / RTH) * ((w + RTW - 1) / RTW);
-    hipLaunchKernelGGL(resblock_kernel, dim3((unsigned)std::min<int64_t>(tiles, 256)), dim3(RES_NT), 0, st, a);
+    const dim3 grid((unsigned)std::min<int64_t>(tiles, 512));
+    if (t) hipLaunchKernelGGL(resblock_kernel<true>, grid, dim3(RES_NT), 0, st, a);
+    else hipLaunchKernelGGL(resblock_kernel<false>, grid, dim3(RES_NT), 0, st, a);
 }
 
 void launch_wgrad(hipStream_t st, const bf16 *in, const bf16 *gout, const bf16 *gref, float *partial, float *grads,
@@ -1144,17 +1133,12 @@ int32_t mpr_cnn_forward(mpr_ctx *ctx, int32_t n, int32_t h, int32_t w, const flo
     if (!carve_acts(ws, ws_bytes, n, h, w, training != 0, A)) return cfail(ctx, MPR_ERR_WORKSPACE, "workspace");
     hipStream_t st = (hipStream_t)stream;
     launch_conv(st, (const bf16 *)x, fwd_pack(packed, 0), bias_of(params, 0), nullptr, nullptr, 1, A.h[0], n, h, w);
-    for (int b = 0; b < NBLK; ++b) {
-        if (training) {  // the inner activations are kept for the backward pass
-            launch_conv(st, A.h[b], fwd_pack(packed, 1 + 2 * b), bias_of(params, 1 + 2 * b), nullptr, nullptr, 1,
-                        A.t[b], n, h, w);
-            launch_conv(st, A.t[b], fwd_pack(packed, 2 + 2 * b), bias_of(params, 2 + 2 * b), A.h[b], nullptr, 0,
+    // the bits of two convolutions, the inner activation in LDS (and kept for
+    // the backward pass)
+    for (int b = 0; b < NBLK; ++b)
+        launch_resblock(st, A.h[b], fwd_pack(packed, 1 + 2 * b), bias_of(params, 1 + 2 * b),
+                        fwd_pack(packed, 2 + 2 * b), bias_of(params, 2 + 2 * b), training ? A.t[b] : nullptr,
                         A.h[b + 1], n, h, w);
-        } else {  // the same bits with the inner activation in LDS
-            launch_resblock(st, A.h[b], fwd_pack(packed, 1 + 2 * b), bias_of(params, 1 + 2 * b),
-                            fwd_pack(packed, 2 + 2 * b), bias_of(params, 2 + 2 * b), A.h[b + 1], n, h, w);
-        }
-    }
     launch_conv(st, A.h[NBLK], fwd_pack(packed, NLAYER - 1), bias_of(params, NLAYER - 1), nullptr, nullptr, 0,
                 (bf16 *)y, n, h, w);
     CHIP(ctx, hipGetLastError());
@@ -1182,7 +1166,7 @@ int32_t mpr_cnn_infer(mpr_ctx *ctx, int32_t n, int32_t h, int32_t w, const float
                    w);
     for (int b = 0; b < NBLK; ++b)
         launch_resblock(st, A.h[b], fwd_pack(packed, 1 + 2 * b), bias_of(params, 1 + 2 * b),
-                        fwd_pack(packed, 2 + 2 * b), bias_of(params, 2 + 2 * b), A.h[b + 1], n, h, w);
+                        fwd_pack(packed, 2 + 2 * b), bias_of(params, 2 + 2 * b), nullptr, A.h[b + 1], n, h, w);
     launch_conv_io(st, false, A.h[NBLK], fwd_pack(packed, NLAYER - 1), bias_of(params, NLAYER - 1), nullptr,
                    nullptr, sampled, phi_init, n, h, w);
     CHIP(ctx, hipGetLastError());
