@@ -1164,8 +1164,10 @@ __device__ __forceinline__ void tile_update(TileShared<TH> &L, const ChainDesc &
         uint16_t *lst = L.list[wid];
         // List the gap sites (and, for the energy, the sampled sites): a
         // wave takes one row at a time, lane l its tile column j = 4 + l;
-        // with the ring, then the ring's side columns j = 3 and kTileH + 4,
-        // two lanes per row.  A site in the tile is either a gap or a
+        // with the ring, the last wave (which has the fewest rows) then takes
+        // the ring's sites beside the tile, of which colour 1 reads one per
+        // row (16 chains of 4096^2, 66% missing: 228.6 ms a fill, 232.7 with
+        // both sides of every row, dealt to the first waves).  A site in the tile is either a gap or a
         // sample, so a lane's rank among the sampled lanes is its rank among
         // the lanes holding a site less its rank among the gap lanes: one
         // ballot per row.  FULL: every lane of the wave holds a site (the
@@ -1197,9 +1199,9 @@ __device__ __forceinline__ void tile_update(TileShared<TH> &L, const ChainDesc &
             }
         };
         for (int r = r_lo + wid; r < r_hi; r += NW) add(std::integral_constant<bool, !EDGE>{}, true, r, 4 + lane);
-        if (ring) {
-            const int k = wid * 64 + lane;
-            add(std::false_type{}, k < 2 * (TH + 2), 1 + (k >> 1), (k & 1) ? kTileH + 4 : 3);
+        if (ring && wid == NW - 1) {
+            const int r = 2 + (lane < TH ? lane : 0);
+            add(std::false_type{}, lane < TH, r, (r & 1) ? 3 : kTileH + 4);
         }
         __syncthreads();
         // the listed gap sites
