@@ -818,23 +818,44 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
     }
 }
 
+// A wave's 64 consecutive pixels, whose channels 0 to 3 the lanes hold in
+// (w0, w1) and whose other channels are zero, to dst.  The stores bound both
+// callers; a lane that wrote its own pixel's 64 bytes left every store
+// instruction 64 bytes apart from lane to lane, so the lanes pass the words
+// on and each store covers 1 KiB without a gap (encoding 32 x 256^2 pixels:
+// 67 -> 28 us, which is 145 MB at the rate of a copy; the loss: 64 -> 38 us).
+__device__ __forceinline__ void store_leading(bf16 *__restrict__ dst, int64_t first, int64_t npix, uint32_t w0,
+                                              uint32_t w1)
+{
+    const int lane = (int)(threadIdx.x & 63);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int src = 16 * k + (lane >> 2);
+        const uint32_t a = (uint32_t)__shfl((int)w0, src), b = (uint32_t)__shfl((int)w1, src);
+        const bool lead = (lane & 3) == 0;
+        if (first + src < npix)
+            reinterpret_cast<uint4 *>(dst + first * CH)[64 * k + lane] =
+                make_uint4(lead ? a : 0u, lead ? b : 0u, 0u, 0u);
+    }
+}
+
 // Network input: (cos q phi, sin q phi, 1) at sampled sites, zeros elsewhere.
 __global__ void encode_kernel(const float *__restrict__ phi, const uint8_t *__restrict__ sampled, int64_t npix,
                               float q, bf16 *__restrict__ x)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= npix) return;
-    bf16 v[CH];
-    for (int c = 0; c < CH; ++c) v[c] = (bf16)0.0f;
-    if (sampled[p]) {
+    union {
+        bf16 v[4];
+        uint32_t w[2];
+    } u;
+    u.w[0] = u.w[1] = 0u;
+    if (p < npix && sampled[p]) {
         const float th = q * fabsf(phi[p]);
-        v[0] = (bf16)cosf(th);
-        v[1] = (bf16)sinf(th);
-        v[2] = (bf16)1.0f;
+        u.v[0] = (bf16)cosf(th);
+        u.v[1] = (bf16)sinf(th);
+        u.v[2] = (bf16)1.0f;
     }
-    uint4 *dst = reinterpret_cast<uint4 *>(x + p * CH);
-    const uint4 *s = reinterpret_cast<const uint4 *>(v);
-    for (int k = 0; k < 4; ++k) dst[k] = s[k];
+    store_leading(x, p - (int64_t)(threadIdx.x & 63), npix, u.w[0], u.w[1]);
 }
 
 // Head output -> starting gap angle: atan2(max(s, 0), c) / q, below 2 pi.
@@ -861,20 +882,19 @@ __global__ void loss_kernel(const bf16 *__restrict__ y, const float *__restrict_
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     double l = 0.0;
-    if (p < npix) {
-        bf16 g[CH];
-        for (int c = 0; c < CH; ++c) g[c] = (bf16)0.0f;
-        if (!sampled[p]) {
-            const float d0 = (float)y[p * CH] - target[2 * p];
-            const float d1 = (float)y[p * CH + 1] - target[2 * p + 1];
-            l = (double)d0 * d0 + (double)d1 * d1;
-            g[0] = (bf16)(2.0f * d0 * inv_n);
-            g[1] = (bf16)(2.0f * d1 * inv_n);
-        }
-        uint4 *dst = reinterpret_cast<uint4 *>(dy + p * CH);
-        const uint4 *s = reinterpret_cast<const uint4 *>(g);
-        for (int k = 0; k < 4; ++k) dst[k] = s[k];
+    union {
+        bf16 v[2];
+        uint32_t w;
+    } g;
+    g.w = 0u;
+    if (p < npix && !sampled[p]) {
+        const float d0 = (float)y[p * CH] - target[2 * p];
+        const float d1 = (float)y[p * CH + 1] - target[2 * p + 1];
+        l = (double)d0 * d0 + (double)d1 * d1;
+        g.v[0] = (bf16)(2.0f * d0 * inv_n);
+        g.v[1] = (bf16)(2.0f * d1 * inv_n);
     }
+    store_leading(dy, p - (int64_t)(threadIdx.x & 63), npix, g.w, 0u);
     for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
     __shared__ double red[4];
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = l;
