@@ -536,7 +536,7 @@ def main():
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": measured_traffic(args.workload, prm.R,
                                         ("fp64-" if args.fp64 else "") + str(prof["last_tile"])),
-            "kernel": ("sweep_tile_persist_kernel" if prof["last_tile"] & mpr.TILE_PERSIST else
+            "kernel": ("sweep_resident_kernel" if prof["last_tile"] & mpr.TILE_PERSIST else
                        "sweep_tile_kernel" if prof["last_tile"] & mpr.TILE_FUSED else
                        "half_sweep_" + ("fp64_" if args.fp64 else "") +
                        ("compact_kernel" if prof["last_tile"] & mpr.TILE_COMPACT else "kernel")),

@@ -109,7 +109,7 @@ typedef struct {
                              (results do not depend on it) */
     double table_T_lo, table_T_hi;
     uint64_t seed;        /* Philox key */
-    int32_t sweeps_per_launch;  /* sweeps per captured graph between done-checks;
+    int32_t sweeps_per_launch;  /* sweeps per launch group between done-checks;
                                    0 = chosen from the measured sweep time */
     int32_t spread;       /* 1: also keep, per chain and site, the squared deviations
                              of the equilibrium states from their running mean (K > 1;
@@ -212,11 +212,12 @@ int32_t mpr_estimate_temperature(mpr_ctx *ctx, const mpr_image *imgs, int32_t n_
                                  void *stream);
 
 /* Algorithm 2 steps 2, 5 and 6 with Algorithm 1 sweeps on the GPU, for all
- * images and R chains per image at once: every half-sweep is one launch over
- * the blocks of all chains of the (ragged) batch, and groups of sweeps are
- * replayed as a captured HIP graph.  Unless tile_rows is set, the first
- * sweeps of a new batch shape time each block shape and the fastest is kept
- * for that shape (cached in ctx).  Each chain starts from U(0, 2 pi)
+ * images and R chains per image at once: a launch covers the blocks of all
+ * chains of the (ragged) batch, for one sweep (fused shapes), for one colour
+ * (two-pass shapes, replayed in groups as a captured HIP graph), or for many
+ * sweeps when all tiles fit on the GPU at once.  Unless tile_rows is set, the
+ * first sweeps of a new batch shape time each block shape and the fastest is
+ * kept for that shape (cached in ctx).  Each chain starts from U(0, 2 pi)
  * gap angles (or phi_init), relaxes with the hybrid update until the energy
  * slope is >= 0 or i_max (or fixed_relax sweeps), then runs K equilibrium
  * sweeps.  Random numbers are Philox4x32-10 keyed by (seed; site, sweep,

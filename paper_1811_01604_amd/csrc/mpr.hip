@@ -985,7 +985,9 @@ constexpr int kTileLS = kTileH + 8;       // LDS row: half-columns hx0 - 4 .. hx
 constexpr int kTileNW = kBlock / 64;      // waves per block
 // Fused sweeps of at most this many blocks run the control themselves (a
 // chain's last block, found by a returning atomic that every block waits for
-// at its end).  
+// at its end).  A batch of 24 images of 128 to 1024 a side: 24.4 ms a fill with
+// control_kernel after every sweep, 20.2 ms without; at 44032 blocks (sixteen
+// chains of 4096^2) 250.1 and 250.6 ms, and the atomics only grow from there.
 constexpr int64_t kTileCtlMaxBlocks = 16384;
 
 // The double-precision decision of one tile site (colour c, local row r,
