@@ -40,6 +40,7 @@ constexpr int LSZ = WSZ + CH;                // weights + bias per layer
 constexpr int PIXS = 40;                     // staged pixel stride in bf16 (80 B)
 constexpr int WG_BLOCKS = 256;               // persistent blocks of the weight-gradient kernel
 constexpr int WG_PART = WSZ + CH;            // floats per partial
+constexpr int WG_LAYERS = 4;                 // layers whose partials the workspace holds
 
 struct ConvArgs {
     const bf16 *in;        // N x H x W x 32
@@ -801,20 +802,32 @@ __global__ __launch_bounds__(WG_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) v
 }
 
 // grads[j] = sum over partials p of partial[p][j]: 32 weights per block, 8
-// threads each (every eighth partial), their sums added in order.
+// threads each (every eighth partial), their sums added in order; blockIdx.y:
+// the layer before, with the next partials.  Up to WG_LAYERS layers share a
+// launch: one layer's sum (289 blocks, each a chain of loads) took 11 us for
+// 9.5 MB, four with eight loads in flight take 9.4 us for 38 MB.
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restrict__ partial, int n_parts,
                                                            float *__restrict__ grads)
 {
     __shared__ float red[8][32];
     const int c = (int)threadIdx.x & 31, g = (int)threadIdx.x >> 5;
     const int j = (int)blockIdx.x * 32 + c;
+    const float *src = partial + (int64_t)blockIdx.y * WG_BLOCKS * WG_PART + j;
     float s = 0.0f;
-    for (int p = g; p < n_parts; p += 8) s += partial[(int64_t)p * WG_PART + j];
+    int p = g;
+    for (; p + 56 < n_parts; p += 64) {  // eight loads in flight
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = src[(int64_t)(p + 8 * k) * WG_PART];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += v[k];
+    }
+    for (; p < n_parts; p += 8) s += src[(int64_t)p * WG_PART];
     red[g][c] = s;
     __syncthreads();
     if (g == 0) {
         for (int k = 1; k < 8; ++k) s += red[k][c];
-        grads[j] = s;
+        grads[j - (int64_t)blockIdx.y * LSZ] = s;
     }
 }
 
@@ -1034,14 +1047,23 @@ void launch_resblock(hipStream_t st, const bf16 *in, const bf16 *w1, const float
     else hipLaunchKernelGGL(resblock_kernel<false>, grid, dim3(RES_NT), 0, st, a);
 }
 
-void launch_wgrad(hipStream_t st, const bf16 *in, const bf16 *gout, const bf16 *gref, float *partial, float *grads,
+// Layers whose partials wait to be summed, the first one's gradients at
+// `grads` and each further one's a layer before.
+struct WgradSums {
+    float *partial;
+    float *grads;
+    int pending;
+};
+
+// Queues one layer's weight gradient; sums the queue when it is full or `last`.
+void launch_wgrad(hipStream_t st, const bf16 *in, const bf16 *gout, const bf16 *gref, WgradSums &sums, bool last,
                   int n, int h, int w)
 {
     WgradArgs a;
     a.in = in;
     a.gout = gout;
     a.gref = gref;
-    a.partial = partial;
+    a.partial = sums.partial + (int64_t)sums.pending * WG_BLOCKS * WG_PART;
     a.N = n;
     a.H = h;
     a.W = w;
@@ -1050,7 +1072,11 @@ void launch_wgrad(hipStream_t st, const bf16 *in, const bf16 *gout, const bf16 *
     if (gref) hipLaunchKernelGGL(conv3x3_wgrad_kernel<true>, dim3(blocks), dim3(WG_NT), 0, st, a);
     else hipLaunchKernelGGL(conv3x3_wgrad_kernel<false>, dim3(blocks), dim3(WG_NT), 0, st, a);
     static_assert(WG_PART % 32 == 0, "whole blocks of the sum");
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(WG_PART / 32), dim3(256), 0, st, partial, blocks, grads);
+    if (++sums.pending < WG_LAYERS && !last) return;
+    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(WG_PART / 32, sums.pending), dim3(256), 0, st, sums.partial, blocks,
+                       sums.grads);
+    if (!last) sums.grads -= (int64_t)sums.pending * LSZ;
+    sums.pending = 0;
 }
 
 // Activation buffers of a training forward pass inside the workspace.
@@ -1078,7 +1104,7 @@ bool carve_acts(void *ws, int64_t ws_bytes, int n, int h, int w, bool training, 
         for (int k = 0; k < NBLK; ++k)
             if (!(A.t[k] = (bf16 *)take(ab))) return false;
         if (!(A.g0 = (bf16 *)take(ab)) || !(A.g1 = (bf16 *)take(ab))) return false;
-        if (!(A.partial = (float *)take((int64_t)WG_BLOCKS * 4 * WG_PART * 4))) return false;
+        if (!(A.partial = (float *)take((int64_t)WG_BLOCKS * WG_LAYERS * WG_PART * 4))) return false;
     } else {
         // inference: ping-pong h and one t
         bf16 *b0 = (bf16 *)take(ab), *b1 = (bf16 *)take(ab), *b2 = (bf16 *)take(ab);
@@ -1107,7 +1133,7 @@ int64_t mpr_cnn_workspace_size(int32_t n, int32_t h, int32_t w, int32_t training
 {
     if (!shape_ok(n, h, w)) return -1;
     const int64_t ab = act_bytes(n, h, w);
-    if (training) return (2 * NBLK + 3) * ab + (int64_t)WG_BLOCKS * 4 * WG_PART * 4 + 4096;
+    if (training) return (2 * NBLK + 3) * ab + (int64_t)WG_BLOCKS * WG_LAYERS * WG_PART * 4 + 4096;
     return 3 * ab + 4096;
 }
 
@@ -1237,21 +1263,22 @@ int32_t mpr_cnn_backward(mpr_ctx *ctx, int32_t n, int32_t h, int32_t w, const fl
     if (!carve_acts(ws, ws_bytes, n, h, w, true, A)) return cfail(ctx, MPR_ERR_WORKSPACE, "workspace");
     hipStream_t st = (hipStream_t)stream;
     const bf16 *g = (const bf16 *)dy;
-    float *G = grads;
+    // the layers' weight gradients from the head to the stem, in this order
+    WgradSums sums = {A.partial, grads + (int64_t)(NLAYER - 1) * LSZ, 0};
     // head
-    launch_wgrad(st, A.h[NBLK], g, nullptr, A.partial, G + (int64_t)(NLAYER - 1) * LSZ, n, h, w);
+    launch_wgrad(st, A.h[NBLK], g, nullptr, sums, false, n, h, w);
     bf16 *dh = A.g0, *dt = A.g1;
     launch_conv(st, g, dgrad_pack(packed, NLAYER - 1), nullptr, nullptr, nullptr, 0, dh, n, h, w);
     for (int b = NBLK - 1; b >= 0; --b) {
         const int l2 = 2 + 2 * b, l1 = 1 + 2 * b;
-        launch_wgrad(st, A.t[b], dh, nullptr, A.partial, G + (int64_t)l2 * LSZ, n, h, w);
+        launch_wgrad(st, A.t[b], dh, nullptr, sums, false, n, h, w);
         launch_conv(st, dh, dgrad_pack(packed, l2), nullptr, nullptr, A.t[b], 0, dt, n, h, w);
-        launch_wgrad(st, A.h[b], dt, nullptr, A.partial, G + (int64_t)l1 * LSZ, n, h, w);
+        launch_wgrad(st, A.h[b], dt, nullptr, sums, false, n, h, w);
         // dh <- dh + dgrad(dt) (in place: each output reads only its own dh entry)
         launch_conv(st, dt, dgrad_pack(packed, l1), nullptr, dh, nullptr, 0, dh, n, h, w);
     }
     // stem: gradient through its ReLU applied while staging
-    launch_wgrad(st, (const bf16 *)x, dh, A.h[0], A.partial, G, n, h, w);
+    launch_wgrad(st, (const bf16 *)x, dh, A.h[0], sums, true, n, h, w);
     CHIP(ctx, hipGetLastError());
     CHIP(ctx, hipStreamSynchronize(st));
     return MPR_OK;
@@ -1315,9 +1342,10 @@ int32_t mpr_cnn_diag_wgrad(mpr_ctx *ctx, int32_t n, int32_t h, int32_t w, const 
     if (int rc = mpr_check_device(ctx, "cnn_diag_wgrad",
                                   {{"in", in}, {"gout", gout}, {"gref", gref}, {"grads", grads}, {"workspace", ws}}))
         return rc;
-    if (ws_bytes < (int64_t)WG_BLOCKS * 4 * WG_PART * 4) return cfail(ctx, MPR_ERR_WORKSPACE, "cnn_diag_wgrad: workspace");
+    if (ws_bytes < (int64_t)WG_BLOCKS * WG_LAYERS * WG_PART * 4) return cfail(ctx, MPR_ERR_WORKSPACE, "cnn_diag_wgrad: workspace");
     hipStream_t st = (hipStream_t)stream;
-    launch_wgrad(st, (const bf16 *)in, (const bf16 *)gout, (const bf16 *)gref, (float *)ws, grads, n, h, w);
+    WgradSums sums = {(float *)ws, grads, 0};
+    launch_wgrad(st, (const bf16 *)in, (const bf16 *)gout, (const bf16 *)gref, sums, true, n, h, w);
     CHIP(ctx, hipGetLastError());
     CHIP(ctx, hipStreamSynchronize(st));
     return MPR_OK;
