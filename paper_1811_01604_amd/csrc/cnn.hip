@@ -519,8 +519,9 @@ __global__ __launch_bounds__(RES_NT) __attribute__((amdgpu_waves_per_eu(4, 4))) 
 #pragma unroll
             for (int j = 0; j < RES_PT; ++j) {
                 const int k = min((int)threadIdx.x + RES_NT * j, C_CHUNKS - 1), pix = k >> 2;
+                // (18 rows of 32 channels pass 2^32 elements from 7.9e6 columns on)
                 pre[j] = *reinterpret_cast<const uint4 *>(
-                    src + (uint32_t)((pix / C_IN_W) * a.W + pix % C_IN_W) * CH + (k & 3) * 8);
+                    src + (int64_t)((pix / C_IN_W) * a.W + pix % C_IN_W) * CH + (k & 3) * 8);
             }
             pre_valid = ~0u;
         } else {
