@@ -3418,6 +3418,21 @@ bool valid_images(const mpr_image *imgs, int n)
     return true;
 }
 
+// Writes `hdr` (a run that cannot be resumed) over the header of a workspace
+// at the end of its scope, unless d_hdr is null by then.
+struct HeaderGuard {
+    RunHeader *d_hdr;
+    const RunHeader &hdr;
+    hipStream_t stream;
+    ~HeaderGuard()
+    {
+        if (!d_hdr) return;
+        (void)hipMemcpyAsync(d_hdr, &hdr, sizeof hdr, hipMemcpyHostToDevice, stream);
+        (void)hipStreamSynchronize(stream);
+        (void)hipGetLastError();
+    }
+};
+
 constexpr uint64_t kRunMagic = 0x4D50522D52554E31ull;  // "MPR-RUN1"
 constexpr int64_t kRunHeaderBytes = 256;
 
@@ -4708,6 +4723,10 @@ static int32_t simulate_call(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, con
                         "simulate: resume needs a workspace holding a run stopped at sweep_limit with the same "
                         "images, parameters and temperatures");
     }
+    // a call that fails leaves no run to resume: not the one the workspace held
+    // before a fresh call (which may have written over it by then), nor one
+    // whose sweeps were cut off
+    HeaderGuard guard{resume ? nullptr : d_hdr, hdr, stream};
     ImgDev *d_img = (ImgDev *)cv.take(n * (int64_t)sizeof(ImgDev));
     std::vector<ImgDev> hi;
     ImgArgs img;
@@ -4788,9 +4807,11 @@ static int32_t simulate_call(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, con
     for (const auto &st : cs.state) swept = std::max<int64_t>(swept, (int64_t)st.sweep);
     int64_t limit = std::max<int64_t>(1, relax_cap + p->K + 1 - swept);
     if (p->sweep_limit > 0) limit = std::min<int64_t>(limit, p->sweep_limit);
+    guard.d_hdr = d_hdr;
     rc = run_chains(ctx, cs, p, stream, limit, p->n_f, false, graphs, p->sweep_limit > 0);
     const bool incomplete = rc == MPR_INCOMPLETE;
     if (rc && !incomplete) return rc;
+    guard.d_hdr = nullptr;
     if (incomplete || resume) {
         // resumable while chains are running, not once the run is finished
         hdr.state = incomplete ? 1 : 0;

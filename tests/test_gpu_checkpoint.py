@@ -167,3 +167,44 @@ def test_resume_is_refused_without_a_matching_stopped_run(ctx, data):
     # the stopped run itself resumes
     done, _ = ctx.simulate(imgs, phi, mk, Ts, q, ws, ps, allow_incomplete=True)
     assert not done
+
+
+def test_a_failed_call_leaves_nothing_to_resume(ctx, data):
+    """A workspace holds a stopped run.  A fresh call on it that fails (17
+    images, the last of one site: the list of images has been written by then)
+    or a resumed one whose sweeps time out leaves a workspace whose contents
+    are lost, so a resume is refused."""
+    imgs, phi, mk, Ts = data
+    many = mpr.images([(2, 3)] * 16 + [(1, 1)])
+    small = dev(np.linspace(0.0, 6.0, 97))
+    small_mk = dev(np.arange(97) % 2, torch.uint8)
+    z = synth.workload_l1024()
+    big = mpr.images([z.z.shape])
+    big_mk = dev(z.mask, torch.uint8)
+    big_phi = torch.zeros(z.z.shape, device="cuda")
+    ctx.map_to_angles(big, dev(z.z.astype(np.float32)), big_mk, big_phi)
+    persist = 32 | mpr.TILE_FUSED | mpr.TILE_PERSIST
+
+    def fresh(ws):
+        ctx.simulate(many, small, small_mk, np.full(17, 0.1), mpr.default_params(R=1, K=1), ws,
+                     torch.zeros_like(small))
+
+    def cut_off(ws):
+        ctx.simulate(big, big_phi, big_mk, np.array([0.09]),
+                     mpr.default_params(sweep_limit=20, resume=1, tile_rows=persist, barrier_timeout_us=1,
+                                        **{**PRM, "R": 1}),
+                     ws, torch.zeros_like(big_phi))
+
+    for im, ph, m, T, fail, code in ((imgs, phi, mk, Ts, fresh, mpr.MPR_ERR_DEGENERATE),
+                                     (big, big_phi, big_mk, np.array([0.09]), cut_off, mpr.MPR_ERR_HIP)):
+        prm = mpr.default_params(sweep_limit=3, tile_rows=persist, **{**PRM, "R": PRM["R"] if fail is fresh else 1})
+        ws = torch.zeros(ctx.workspace_size(im, prm), dtype=torch.uint8, device="cuda")
+        ps = torch.zeros_like(ph)
+        assert not ctx.simulate(im, ph, m, T, prm, ws, ps, allow_incomplete=True)[0]
+        with pytest.raises(mpr.MprError) as e:
+            fail(ws)
+        assert e.value.code == code
+        prm.resume = 1
+        with pytest.raises(mpr.MprError) as e:
+            ctx.simulate(im, ph, m, T, prm, ws, ps, allow_incomplete=True)
+        assert e.value.code == mpr.MPR_ERR_ARG
