@@ -147,11 +147,18 @@ typedef struct {
                                 sweeps_per_launch) instead of starting its chains; phi_init is
                                 ignored.  Results equal those of an uninterrupted run bit for
                                 bit (random numbers are keyed by sweep, not by call). */
-    int32_t barrier_timeout_us; /* > 0: the longest a block of the persistent sweep
+    int32_t barrier_timeout_us; /* > 0: the longest a block of the resident sweeps
                                 (MPR_TILE_PERSIST) waits for other blocks, in microseconds,
                                 before the call gives up with MPR_ERR_HIP (every block then
                                 leaves at its next wait; the workspace contents are lost);
-                                0: 2 seconds.  Results do not depend on it. */
+                                0: 2 seconds.  Resident sweeps also run, where the tiles fit,
+                                in calls that name no shape: single and double precision, with
+                                recorded states, the e(T, L) table chains of
+                                mpr_estimate_temperature and mpr_select_q, and the last chains
+                                of a larger set.  A bound below 2 seconds holds for single
+                                precision without recorded states, in tiles of at most 32 rows
+                                from the call's start; the others wait 2 seconds at least.
+                                Results do not depend on it. */
 } mpr_params;
 
 /* Per chain results of mpr_simulate (R per image, image-major). */

@@ -2434,7 +2434,7 @@ __global__ void control_kernel(ChainDesc *__restrict__ descs, ChainState *__rest
 }
 
 // Zeroes the control words given (null: skipped) and n64 64-bit words at
-// `wide`, in one launch of one block: the counters and barrier words a run of
+// `wide`, in one launch of one block: the counters and control words a run of
 // sweeps starts from (one small kernel in place of a memset per word).
 __global__ void clear_words_kernel(unsigned int *w0, unsigned int *w1, unsigned int *w2,
                                    unsigned long long *wide, int n64)
@@ -3170,7 +3170,7 @@ struct mpr_ctx {
     void *scratch = nullptr;          // small device scratch (partials, counters)
     void *static_ws = nullptr;        // this device's static_workspace (device address)
     // pinned host memory: the first kHostWordsBytes mirror the scratch's
-    // control words (done counter, barrier generation, abort word); the
+    // control words (done counter, sweeps run, abort word); the
     // rest stages small read-backs (the per-block partials of the map and
     // of the sample energies) in one copy each
     unsigned int *done_host = nullptr;
@@ -3939,11 +3939,19 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     rc0.states_out = cs.states_out;
     rc0.offsets = cs.d_offset;
     rc0.states_n_total = cs.states_n_total;
-    rc0.wait_ticks = p->barrier_timeout_us > 0 ? (uint64_t)p->barrier_timeout_us * 100u : kPersistWaitTicks;
     rc0.K = cs.K;
+    // The caller's bound on a block's wait holds where MPR_TILE_PERSIST can be
+    // asked for: single-precision chains that record no states, in tiles of at
+    // most 32 rows from the call's start.  Elsewhere resident sweeps stand in
+    // for launches that wait for nothing, and a bound below the default must
+    // not end the call.
+    const uint64_t own_wait = (uint64_t)p->barrier_timeout_us * 100u;
+    const bool bounded = own_wait > 0 && fuse && !table;
+    bool tail = false;  // the last chains of a set, made resident on the way
     hipError_t perr = hipSuccess;
     auto sweeps = [&](int v, int count) {
         if (kShapes[v].persist) {
+            rc0.wait_ticks = bounded && !tail && kShapes[v].rows <= 32 ? own_wait : std::max(own_wait, kPersistWaitTicks);
             rc0.count = count;
             perr = launch_resident(ctx, st, cs, v, sc, cp, rc0);
             return;
@@ -3987,7 +3995,9 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         HIP_TRY(ctx, hipStreamSynchronize(st));
         if (kShapes[v].persist) {
             if (ctx->done_host[kAbortOffset / 4] != 0u)
-                return fail(ctx, MPR_ERR_HIP, "persistent sweep: a block timed out at the grid barrier");
+                return fail(ctx, MPR_ERR_HIP,
+                            "resident sweeps: a block waited for another one longer than its bound (2 s, or "
+                            "params.barrier_timeout_us)");
             // the launch stops early once every chain is done
             count = (int)ctx->done_host[kGenOffset / 4];
         }
@@ -4159,6 +4169,7 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
                 if (fits(k) && (best < 0 || cs.total_blocks[best] > kResMaxBlocks / 2)) best = k;
             if (best >= 0) {
                 v = best;
+                tail = true;
                 if (p->sweeps_per_launch <= 0) spl = 256;
             }
         }

@@ -85,3 +85,25 @@ def test_resident_table_chains_equal_half_sweeps(ny, nx, q):
         got.append((e_s[0], T[0], cl[0]))
         ctx.close()
     assert got[0] == got[1]
+
+
+def test_a_short_wait_bound_does_not_end_other_calls(ctx):
+    """A bound of 1 us on a block's wait holds for single-precision chains
+    without recorded states; double precision, recorded states, table chains,
+    tiles above 32 rows and the last chains of a larger set give the results
+    of the default bound."""
+    imgs, mk, phi = image(ctx, 512, 512)
+    got = {}
+    for bound in (0, 1):
+        kw = dict(barrier_timeout_us=bound)
+        tab = mpr.default_params(table_nT=8, table_T_lo=1e-4, table_T_hi=2.0, table_burn=40, table_meas=30, **kw)
+        c = mpr.Context(0)  # (a table is kept by its context)
+        ws = torch.empty(c.workspace_size(imgs, tab), dtype=torch.uint8, device="cuda")
+        e_s, T, _ = c.estimate_temperature(imgs, phi, mk, tab, ws)
+        big, big_mk, big_phi = image(c, 2048, 2047)
+        got[bound] = (e_s[0], T[0], run(c, imgs, phi, mk, 0.05, 0, R=2, K=5, fp64=1, **kw),
+                      run(c, imgs, phi, mk, 0.05, 0, R=2, K=5, record=True, **kw),
+                      run(c, imgs, phi, mk, 0.05, 0, R=40, K=1, **kw),
+                      run(c, big, big_phi, big_mk, 0.05, 0, R=1, K=3, fixed_relax=6, **kw))
+        c.close()
+    assert got[0] == got[1]
