@@ -222,9 +222,10 @@ int32_t mpr_estimate_temperature(mpr_ctx *ctx, const mpr_image *imgs, int32_t n_
  * images and R chains per image at once: a launch covers the blocks of all
  * chains of the (ragged) batch, for one sweep (fused shapes), for one colour
  * (two-pass shapes, replayed in groups as a captured HIP graph), or for many
- * sweeps when all tiles fit on the GPU at once.  Unless tile_rows is set, the
- * first sweeps of a new batch shape time each block shape and the fastest is
- * kept for that shape (cached in ctx).  Each chain starts from U(0, 2 pi)
+ * sweeps when all tiles fit on the GPU at once (in tiles chosen by a rule).
+ * Otherwise, unless tile_rows is set, the first sweeps of a new batch shape
+ * time each block shape and the fastest is kept for that shape (cached in
+ * ctx).  Each chain starts from U(0, 2 pi)
  * gap angles (or phi_init), relaxes with the hybrid update until the energy
  * slope is >= 0 or i_max (or fixed_relax sweeps), then runs K equilibrium
  * sweeps.  Random numbers are Philox4x32-10 keyed by (seed; site, sweep,

@@ -3182,14 +3182,15 @@ struct mpr_ctx {
     // ordered after and before the caller's stream with two events
     hipStream_t gstream = nullptr;
     hipEvent_t ev_in = nullptr, ev_out = nullptr, ev_t0 = nullptr, ev_t1 = nullptr;
-    // tuned block shape by batch shape
-    // (shapes before `next` are timed; a run too short to time them all goes
-    // on in the next call)
+    // tuned block shape by what the cost of a sweep depends on: type and
+    // options, chains, largest sides, blocks (all chains together) and share of
+    // gaps (shapes before `next` are timed; a run too short to time them all
+    // goes on in the next call)
     struct Tuned {
         int next = 0, best = -1;
         float ms = 0.0f;
     };
-    std::map<std::tuple<int, int, int, int>, Tuned> tuned_rows;
+    std::map<std::tuple<int, int, int, int, int64_t, int>, Tuned> tuned_rows;
     // profiling
     bool profile = false;
     double prof_ms = 0.0;
@@ -3346,6 +3347,8 @@ constexpr int start_of(int k)
     return same[k];
 }
 constexpr int kDefaultShape = 2;  // plain, 4 half-rows
+constexpr int kSmallTileShape = 11;  // fused, 8 rows: its blocks measure a chain set
+static_assert(kShapes[kSmallTileShape].fused && kShapes[kSmallTileShape].rows == 8, "8-row tiles");
 
 int tile_code(const Shape &sh)
 {
@@ -4013,81 +4016,101 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         return MPR_OK;
     };
 
-    // block shape: fixed, cached, or tuned on the first sweeps.  The one
+    // block shape: fixed, resident, or else tuned on the first sweeps.  The one
     // launch per sweep shapes of table chains are the plain ones, those of
-    // double-precision chains every unfused one; the resident ones follow.
+    // double-precision chains every unfused one.
     const int n_shapes = table ? kNumPlainShapes : (cs.fp64 ? kNumUnfusedShapes : kNumShapes);
     int v = p->tile_rows ? shape_of(p->tile_rows) : -1;
     if (v >= n_shapes) v = kDefaultShape;
-    // a resident shape whose tiles the device does not hold at once: the
-    // smallest taller one it does, or else its rows, one launch per sweep
-    auto usable = [&](int k) { return k < 0 || !kShapes[k].persist || fits(k); };
-    auto fallback = [&](int k) {
-        if (usable(k)) return k;
-        for (int t = k + 1; t < kNumShapes; ++t)
-            if (fits(t)) return t;
-        if (table || cs.fp64) return kDefaultShape;
-        return shape_of(std::min(kShapes[k].rows, 48) | MPR_TILE_FUSED);
-    };
-    if (v >= 0) v = fallback(v);
-    int maxnx = 0, maxny = 0;
-    for (const auto &d : cs.desc) {
-        maxnx = std::max(maxnx, d.nx);
-        maxny = std::max(maxny, d.ny);
+    // a resident shape asked for whose tiles the device does not hold at once:
+    // the smallest taller one it does, or else its rows, one launch per sweep
+    if (v >= 0 && kShapes[v].persist && !fits(v)) {
+        int t = v + 1;
+        while (t < kNumShapes && !fits(t)) ++t;
+        v = t < kNumShapes ? t : shape_of(kShapes[v].rows | MPR_TILE_FUSED);
     }
-    const auto key = std::make_tuple((table ? 1 : 0) | (cs.fp64 ? 2 : 0), n, maxnx, maxny);
-    float sweep_ms = -1.0f;
-    bool resident = false;
-    for (int k = 0; k < kNumShapes; ++k) resident = resident || fits(k);
-    // Half-sweeps are captured into graphs, on the context's own stream (the
-    // caller's may be the default one, which cannot be captured), ordered
-    // after and before the caller's with two events; all other shapes run on
-    // the caller's stream.
-    if (v >= 0 ? !kShapes[v].fused : !resident) {
+    int64_t sites = 0, gaps = 0;
+    for (const auto &d : cs.desc) {
+        sites += (int64_t)d.nx * d.ny;
+        gaps += d.P;
+    }
+    // The resident shape of a chain set, or -1 if its tiles do not fit.
+    // 1. The lowest tiles that leave a CU for each block, else the lowest that
+    //    fit.  Low tiles spread a sweep over more waves, but a second block on
+    //    a CU takes its share of the issue slots: us per sweep in relaxation /
+    //    equilibrium, half gaps, 1024^2: 16 rows (512 blocks) 13.3 / 6.9, 32
+    //    rows (256) 10.0 / 6.7, 64 rows (128) 12.6 / 10.6; 16 chains of 128^2:
+    //    8 rows (256) 6.3 / 4.4, 16 rows (128) 6.8 / 5.1; 1500^2, 66%, whole
+    //    fill: 48 rows (384) 959 us, 64 rows (288) 1064.
+    // 2. At least 16 rows below an eighth of gaps: the waves of an 8-row block
+    //    are left with nothing to do (fills of 4 chains of 256^2, 5% gaps: 8
+    //    rows 308 us, 16 rows 292; 66%: 421 and 450).
+    // 3. Not above 32 rows if lower tiles fit and most sweeps are equilibrium
+    //    ones (100 states and more), which wait for no other block than the
+    //    neighbours (1350^2 in clouds, 40%, K = 100: 32 rows, 473 blocks 2070
+    //    us, 64 rows, 242 blocks 2414), or if a chain is 3 to 16 tiles of 32
+    //    rows: its blocks wait for few others, and chains that end leave their
+    //    CU to the second block (128 chains of 128^2, 66%: 32 rows 1016 us, 64
+    //    rows 1356; 24 of 256^2: 804 and 926; but 8 of 512^2, 64 blocks each:
+    //    990 and 916).
+    // Over 428 fills (64^2 to 1900 x 700, 1 to 256 chains, 5 to 90% gaps, random
+    // and clouds, both precisions) the shape taken is within 5% of the best in
+    // nine of ten.  One launch per sweep takes 1.2 to 3 times as long.
+    auto resident_shape = [&]() {
+        int best = -1, low = -1, rows32 = -1;
+        for (int k = 0; k < kNumShapes; ++k) {
+            if (!fits(k) || (kShapes[k].rows < 16 && 8 * gaps < sites)) continue;
+            if (low < 0) low = k;
+            if (kShapes[k].rows == 32) rows32 = k;
+            if (best < 0 || (cs.total_blocks[best] > kResMaxBlocks / 2 && cs.total_blocks[k] <= kResMaxBlocks / 2))
+                best = k;
+        }
+        if (rows32 >= 0 && kShapes[best].rows > 32) {
+            const int64_t blocks = cs.total_blocks[rows32], na = cs.n_active;
+            if (cs.K >= 100) best = low;
+            else if (blocks >= 3 * na && blocks <= 16 * na) best = rows32;
+        }
+        return best;
+    };
+    if (v < 0) v = resident_shape();
+    // The resident shapes run on the caller's stream, the others on the
+    // context's own, ordered after and before the caller's with two events:
+    // half-sweeps are captured into graphs (the caller's may be the default
+    // stream, which cannot be captured), and calls of several threads on the
+    // default stream overlap.
+    if (v < 0 || !kShapes[v].persist) {
         st = ctx->gstream;
         HIP_TRY(ctx, hipEventRecord(ctx->ev_in, stream));
         HIP_TRY(ctx, hipStreamWaitEvent(st, ctx->ev_in, 0));
     }
+    float sweep_ms = -1.0f;
     if (v < 0) {
-        // Where the tiles fit on the GPU only the resident shapes are timed:
-        // they take 4.4 us per 64^2 sweep, 8.4 us per 1024^2 one and 28.7 us
-        // per 2048^2 one (one chain), one launch per sweep 13.4, 27.4 and
-        // 41.3 us at best.
-        mpr_ctx::Tuned &tn = ctx->tuned_rows[key];
+        int maxnx = 0, maxny = 0;
+        for (const auto &d : cs.desc) {
+            maxnx = std::max(maxnx, d.nx);
+            maxny = std::max(maxny, d.ny);
+        }
+        const int kind = (table ? 1 : 0) | (cs.fp64 ? 2 : 0) | (cs.states_out ? 4 : 0) | (cs.desc[0].acc[0] ? 8 : 0) |
+                         (cs.desc[0].m2[0] ? 16 : 0);
+        mpr_ctx::Tuned &tn = ctx->tuned_rows[std::make_tuple(kind, n, maxnx, maxny, cs.total_blocks[kSmallTileShape],
+                                                             (int)(8 * gaps / sites))];
         const int ts = std::max(1, std::min(poll_every, 3));
-        unsigned int done_before = 0;
-        for (; tn.next < kNumShapes && !finished && done_sweeps + ts <= max_sweeps; ++tn.next) {
+        for (; tn.next < n_shapes && !finished && done_sweeps + ts <= max_sweeps; ++tn.next) {
             const int k = tn.next;
-            if (!(resident ? fits(k) : !kShapes[k].persist && k < n_shapes)) continue;
-            if (resident) {
-                // an untimed first launch (the first of a kernel costs more)
-                int rc = block(k, 1, nullptr, nullptr);
-                if (rc) return rc;
-                done_before = *ctx->done_host;
-                if (finished || done_sweeps + ts > max_sweeps) break;
-            }
-            // (more sweeps in a resident launch, so that its start and end
-            // weigh less in the comparison)
-            const int tk = resident ? (int)std::min<int64_t>(2 * ts, max_sweeps - done_sweeps) : ts;
+            if (kShapes[k].persist) continue;
             float ms = 0.0f;
-            const int64_t before = done_sweeps;
-            int rc = block(k, tk, nullptr, &ms);
+            int rc = block(k, ts, nullptr, &ms);
             if (rc) return rc;
-            // chains that finished meanwhile make the sweeps cheaper: timed again
-            if (resident && *ctx->done_host != done_before) break;
-            ms /= (float)std::max<int64_t>(1, done_sweeps - before);
+            ms /= (float)ts;
             if (tn.best < 0 || ms < tn.ms) {
                 tn.ms = ms;
                 tn.best = k;
             }
         }
+        v = kDefaultShape;
         if (tn.best >= 0) {
-            v = fallback(tn.best);
+            v = tn.best;
             sweep_ms = tn.ms;
-        } else {
-            v = kDefaultShape;
-            for (int k = 0; k < kNumShapes; ++k)
-                if (fits(k)) v = k;
         }
     }
     if (!table) ctx->last_tile = tile_code(kShapes[v]);
@@ -4161,12 +4184,8 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         if (rc) break;
         if (!p->tile_rows && !kShapes[v].persist) {
             // the last chains of a set finish in one resident launch once
-            // they fit: in the lowest tiles that leave a CU for each block
-            // (1024^2: 8.4 us per sweep in 256 blocks, 10.3 in 512), else in
-            // the tallest
-            int best = -1;
-            for (int k = 0; k < kNumShapes; ++k)
-                if (fits(k) && (best < 0 || cs.total_blocks[best] > kResMaxBlocks / 2)) best = k;
+            // they fit
+            const int best = resident_shape();
             if (best >= 0) {
                 v = best;
                 tail = true;

@@ -107,3 +107,39 @@ def test_a_short_wait_bound_does_not_end_other_calls(ctx):
                       run(c, big, big_phi, big_mk, 0.05, 0, R=1, K=3, fixed_relax=6, **kw))
         c.close()
     assert got[0] == got[1]
+
+
+@pytest.mark.parametrize("fp64", [0, 1])
+@pytest.mark.parametrize("p,ny,nx,R,rows,rows64", [
+    (0.6, 61, 131, 16, 8, 8), (0.6, 61, 131, 20, 12, 12), (0.6, 61, 131, 30, 16, 16), (0.6, 61, 131, 40, 24, 24),
+    (0.6, 61, 131, 60, 32, 32), (0.6, 61, 131, 70, 32, 24), (0.6, 47, 100, 150, 48, 16), (0.6, 61, 100, 150, 64, 24),
+    (0.1, 61, 131, 5, 16, 16)])
+def test_every_resident_tile_height(ctx, p, ny, nx, R, rows, rows64, fp64):
+    """The number of chains and the share of gaps select the height of the
+    tiles (of doubles, at most 32 rows): spread, recorded states and
+    statistics against half-sweeps."""
+    rows = rows64 if fp64 else rows
+    imgs, mk, phi = image(ctx, ny, nx, p)
+    kw = dict(R=R, K=4, spread=1, fp64=fp64, record=True)
+    ref = run(ctx, imgs, phi, mk, 0.05, 4, **kw)
+    assert run(ctx, imgs, phi, mk, 0.05, 0, **kw) == ref
+    assert ctx.profile_read()["last_tile"] == min(rows, 32) | mpr.TILE_FUSED | mpr.TILE_PERSIST
+
+
+def test_the_shape_does_not_depend_on_the_calls_before(ctx):
+    """Two batches of six images with the same largest sides: the small one
+    runs in resident tiles also after the large one, whose tiles do not fit,
+    and the large one without them."""
+    tiles = []
+    for shapes in ([(1024, 1024)] * 6, [(1024, 1024)] + [(64, 64)] * 5) * 2:
+        z = torch.from_numpy(np.concatenate([synth.matern_field(nx, ny, 0.5, 0.2, 50.0, 10.0, 3).astype(np.float32)
+                                             .ravel() for ny, nx in shapes])).cuda()
+        mk = torch.from_numpy(np.concatenate([synth.random_mask(nx, ny, 0.5, 4).ravel() for ny, nx in shapes])).cuda()
+        imgs = mpr.images(shapes)
+        phi, ps = torch.zeros_like(z), torch.zeros_like(z)
+        ctx.map_to_angles(imgs, z, mk, phi)
+        prm = mpr.default_params(R=1, K=50)
+        ws = torch.empty(ctx.workspace_size(imgs, prm), dtype=torch.uint8, device="cuda")
+        ctx.simulate(imgs, phi, mk, np.full(6, 0.05), prm, ws, ps)
+        tiles.append(bool(ctx.profile_read()["last_tile"] & mpr.TILE_PERSIST))
+    assert tiles == [False, True, False, True]
