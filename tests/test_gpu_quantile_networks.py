@@ -35,3 +35,34 @@ def test_quantiles_equal_sorted_states(M, ny, nx, p):
         want = np.where(mask != 0, z, (lo * (1.0 - t) + hi * t).astype(np.float32))
         got = out[q * n:(q + 1) * n].cpu().numpy()
         assert np.array_equal(got.view(np.uint32), want.view(np.uint32)), (q, pr)
+
+
+@pytest.mark.parametrize("M,ny,nx,p", [(40, 2917, 2903, 0.5), (100, 2051, 2049, 0.5), (100, 2051, 2049, 0.04),
+                                       (104, 1033, 1021, 0.9), (128, 1801, 1777, 0.5), (129, 521, 509, 0.5),
+                                       (129, 521, 509, 0.04), (256, 307, 499, 0.9)])
+def test_quantiles_of_many_sites(M, ny, nx, p):
+    """Sizes at which a wave works along more than 64 sites, and (all but the
+    104 and 256 states) along 320: gaps carried over from one group of 256
+    sites to the next, full lists with a remainder, and the last few gaps.
+    Every site, against a sort of the same states, bit for bit."""
+    n = ny * nx
+    g = torch.Generator(device="cuda").manual_seed(M + nx)
+    st = 6.28 * torch.rand((M, n), generator=g, device="cuda")
+    z = torch.randn(n, generator=g, device="cuda")
+    mask = (torch.rand(n, generator=g, device="cuda") >= p).to(torch.uint8)
+    probs = np.array([0.0, 0.37, 1.0])
+    lo, hi = 12.5, 97.25
+    ctx = mpr.Context(0)
+    out = torch.full((probs.size, n), -1.0, device="cuda")
+    ctx.quantiles(mpr.images([(ny, nx)]), z, mask, st.flatten(), M, probs, np.array([lo, hi]), out)
+    ctx.close()
+    for i in range(0, n, 1 << 20):
+        v = torch.sort(st[:, i:i + (1 << 20)], dim=0).values.double()
+        for q, pr in enumerate(probs):
+            h = (M - 1) * pr
+            a = int(np.floor(h))
+            phi = v[a] if a >= M - 1 else v[a] + (h - a) * (v[a + 1] - v[a])
+            t = phi / (2.0 * np.pi)
+            j = slice(i, i + v.shape[1])
+            want = torch.where(mask[j] != 0, z[j], (lo * (1.0 - t) + hi * t).float())
+            assert torch.equal(out[q, j], want), (i, q)
