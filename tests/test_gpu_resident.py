@@ -3,6 +3,8 @@ one half-sweep launch at a time, bit for bit: double-precision chains, the
 e(T, L) table chains, recorded states and tiles of 48 and 64 rows, at the
 edges of the tiles (a single site wide, one tile, one row or column beyond a
 tile, several ragged tiles)."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -143,3 +145,51 @@ def test_the_shape_does_not_depend_on_the_calls_before(ctx):
         ctx.simulate(imgs, phi, mk, np.full(6, 0.05), prm, ws, ps)
         tiles.append(bool(ctx.profile_read()["last_tile"] & mpr.TILE_PERSIST))
     assert tiles == [False, True, False, True]
+
+
+@pytest.mark.parametrize("own_streams", [False, True])
+def test_threads_with_a_context_each(own_streams):
+    """Three threads, each with its own context, on the default stream or on
+    streams of their own: single precision, double precision and recorded
+    states, with their e(T, L) tables, give the results of one thread."""
+    jobs = [(side, kind) for side in (64, 300, 512, 1024) for kind in range(3)]
+
+    def job(c, side, kind, stream):
+        with torch.cuda.stream(stream):
+            g = torch.Generator(device="cuda").manual_seed(side)
+            z = 50 + 10 * torch.randn((side, side), generator=g, device="cuda")
+            mk = (torch.rand((side, side), generator=g, device="cuda") >= 0.5).to(torch.uint8)
+            imgs = mpr.images([(side, side)])
+            phi, ps = torch.zeros_like(z), torch.zeros_like(z)
+            c.map_to_angles(imgs, z, mk, phi, stream=stream)
+            prm = mpr.default_params(R=2, K=20, fp64=1 if kind == 1 else 0, table_nT=8, table_burn=30, table_meas=30)
+            ws = torch.empty(c.workspace_size(imgs, prm), dtype=torch.uint8, device="cuda")
+            states = torch.zeros(40 * side * side, device="cuda") if kind == 2 else None
+            e_s, T, _ = c.estimate_temperature(imgs, phi, mk, prm, ws, stream=stream)
+            c.simulate(imgs, phi, mk, np.array([0.1]), prm, ws, ps, phi_states=states, stream=stream)
+            stream.synchronize()
+            return e_s[0], T[0], [o.cpu().numpy().tobytes() for o in (ps, states) if o is not None]
+
+    c = mpr.Context(0)
+    ref = [job(c, *j, torch.cuda.default_stream()) for j in jobs]
+    c.close()
+    wrong = []
+
+    def worker(first):
+        c = mpr.Context(0)
+        stream = torch.cuda.Stream() if own_streams else torch.cuda.default_stream()
+        for i in range(len(jobs)):
+            k = (first + i) % len(jobs)
+            try:
+                if job(c, *jobs[k], stream) != ref[k]:
+                    wrong.append((jobs[k], "differs"))
+            except mpr.MprError as e:
+                wrong.append((jobs[k], str(e)))
+        c.close()
+
+    threads = [threading.Thread(target=worker, args=(5 * t,)) for t in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
