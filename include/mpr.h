@@ -155,10 +155,12 @@ typedef struct {
                                 in calls that name no shape: single and double precision, with
                                 recorded states, the e(T, L) table chains of
                                 mpr_estimate_temperature and mpr_select_q, and the last chains
-                                of a larger set.  A bound below 2 seconds holds for single
-                                precision without recorded states, in tiles of at most 32 rows
-                                from the call's start; the others wait 2 seconds at least.
-                                Results do not depend on it. */
+                                of a larger set.  The bound ends a call of single precision
+                                without recorded states, in tiles of at most 32 rows from the
+                                call's start.  Of the other calls it bounds the time (2 ms by
+                                default) until the blocks are on the GPU together, after which
+                                they go on with one launch per sweep; their further waits are
+                                bounded by 2 seconds at least.  Results do not depend on it. */
 } mpr_params;
 
 /* Per chain results of mpr_simulate (R per image, image-major). */

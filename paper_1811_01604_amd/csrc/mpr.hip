@@ -50,7 +50,7 @@ constexpr uint32_t kInitSweep = 0xFFFFFFFFu;
 // per-call partial results.
 constexpr int64_t kDoneOffset = 0;       // done-chain counter
 constexpr int64_t kTicketOffset = 256;   // last-block ticket of the redo kernel with the control fused
-constexpr int64_t kGenOffset = 512;      // sweeps a resident launch has run
+constexpr int64_t kGenOffset = 512;      // four words of a resident launch (kResArrive, kResGoes, kResStart)
 constexpr int64_t kAbortOffset = 768;    // time-out word of the resident sweeps
 constexpr int64_t kSlotsOffset = 16384;  // the blocks' sums of the resident sweeps
 constexpr int64_t kWorkOffset = 1024;    // three work counters (profiling)
@@ -1444,9 +1444,8 @@ __global__ __launch_bounds__(kBlock) void sweep_tile_kernel(ChainDesc *__restric
     }
 }
 
-// Many fused sweeps per cooperative launch (which guarantees that every block
-// is resident), for chain sets whose tiles the GPU holds at once: a
-// 1024 x 1024 chain is 256 tiles of 32 rows.  A block keeps its tile (TH rows
+// Many fused sweeps per cooperative launch, for chain sets whose tiles the GPU
+// holds at once: a 1024 x 1024 chain is 256 tiles of 32 rows.  A block keeps its tile (TH rows
 // x 2 kTileH columns, both colours) in LDS from the launch's first sweep to
 // its last, and exchanges only the sites around it with the tiles beside it.
 //
@@ -1480,13 +1479,29 @@ __global__ __launch_bounds__(kBlock) void sweep_tile_kernel(ChainDesc *__restric
 // 512^2 17.3 us, against two half-sweep launches of 12 us; 32 table chains of
 // 256^2 17 us, against 38 us of half-sweeps and deferred redos.
 //
-// A block that waits longer than its bound (2 s unless the call sets another)
-// sets `abort` and every block leaves at its next wait; the host then reports
-// an error.  The update of a site is that of sweep_tile_kernel (or, for
+// That a cooperative launch fits the GPU does not put all of its blocks on it:
+// two blocks of 8 waves and 128 registers a lane need every register of a CU,
+// in whole runs of 128, and a wave that came in beside another kernel's (of
+// another thread's stream) may lie across two of them for as long as it
+// stays.  So the blocks agree before they begin: each one counts itself, the
+// last one lets the launch go, and a block that waits too long for that (2 ms)
+// calls it off.  A launch called off leaves no trace, and its sweeps run one
+// launch each.
+//
+// After that a block waits for running blocks only.  If it waits longer than
+// its bound all the same (2 s unless the call sets another) it sets `abort`
+// and every block leaves at its next wait; the host then reports an error.
+// The update of a site is that of sweep_tile_kernel (or, for
 // double-precision chains, of half_sweep_fp64_kernel), so the results are the
 // same bit for bit.
 struct ResidentCtl {
-    unsigned int *gen;             // most sweeps any chain ran in this launch; zero at launch
+    // gen[0]: most sweeps any chain ran in this launch; gen[kResArrive]: blocks
+    // on the GPU; gen[kResGoes]: 0 at launch, then kResGo or kResOff;
+    // gen[kResStart]: the longest wait for that, in ticks.  (Behind one pointer:
+    // the kernel has no scalar register left, and three more arguments cost up
+    // to 5% of a sweep; as it is, agreeing costs 0.5 to 1.1%: us per sweep in
+    // relaxation 9.91 and 10.01 at 1024^2, 20.7 and 20.9 at 2048^2.)
+    unsigned int *gen;
     unsigned int *abort;           // nonzero: a block timed out
     unsigned long long *sums;      // [sweep parity][block]: energy | accepted << 46 | tag << 60, then
                                    // [block]: 1 once it has read its chain's state; zero at launch
@@ -1502,6 +1517,9 @@ struct ResidentCtl {
     int32_t K;
 };
 constexpr uint64_t kPersistWaitTicks = 200000000ull;  // default wait bound: 2 s
+constexpr uint32_t kPersistStartTicks = 200000u;      // default bound of the wait for the launch to go: 2 ms
+constexpr int kResArrive = 1, kResGoes = 2, kResStart = 3;
+constexpr unsigned int kResGo = 1u, kResOff = 2u;
 constexpr int kResThreads = 512;
 constexpr int kResWaves = kResThreads / 64;
 constexpr int kResMaxBlocks = 512;  // blocks of a launch at most (8 sums words per lane of the reading wave)
@@ -1541,6 +1559,29 @@ struct ResidentShared {
     int n0_inner, n0, n1, ns;
     int fail;
 };
+
+// A block counts itself (one thread); the last one lets the launch go.
+__device__ __forceinline__ void res_arrive(unsigned int *gen)
+{
+    if (atomicAdd(gen + kResArrive, 1u) == gridDim.x - 1u) atomicCAS(gen + kResGoes, 0u, kResGo);
+}
+
+// Waits for the launch to go or calls it off (one thread); true if it goes.
+__device__ __forceinline__ bool res_goes(unsigned int *gen)
+{
+    const uint64_t t0 = wall_clock64(), bound = ld_agent(gen + kResStart);
+    unsigned int g = ld_agent(gen + kResGoes);
+    while (g == 0u) {
+        __builtin_amdgcn_s_sleep(1);
+        if ((uint64_t)(wall_clock64() - t0) > bound) {
+            g = atomicCAS(gen + kResGoes, 0u, kResOff);
+            if (g == 0u) g = kResOff;
+        } else {
+            g = ld_agent(gen + kResGoes);
+        }
+    }
+    return g == kResGo;
+}
 
 // One poll loop's bookkeeping: true when the wait must be given up.
 __device__ __forceinline__ bool res_give_up(const ResidentCtl &rc, uint64_t t0, int n)
@@ -1602,8 +1643,8 @@ __device__ __forceinline__ void res_publish(unsigned long long *p, uint32_t tag,
 // blocks of chain cid.
 template <typename RT, int TH, bool EDGE>
 __device__ __forceinline__ void resident_tile(ResidentShared<RT, TH> &L, ChainState *states, const ChainDesc &d, int cid,
-                                              int slot, int lb, int nblk, const SweepConsts &sc, const CtlParams &cp,
-                                              const ResidentCtl &rc)
+                                              int slot, int lb, int nblk, bool agree, const SweepConsts &sc,
+                                              const CtlParams &cp, const ResidentCtl &rc)
 {
     using RS = ResidentShared<RT, TH>;
     typedef RT v4 __attribute__((ext_vector_type(4)));
@@ -1616,6 +1657,11 @@ __device__ __forceinline__ void resident_tile(ResidentShared<RT, TH> &L, ChainSt
     const int nbx = d.S / kTileH, nby = nblk / nbx;
     const int ty = lb / nbx, tx = lb - ty * nbx;
     const int y0 = ty * TH, hx0 = tx * kTileH;
+    if (agree) {
+        if (tid == 0) L.fail = res_goes(rc.gen) ? 0 : 1;
+        __syncthreads();
+        if (L.fail) return;
+    }
     const bool lead = lb == 0;  // the chain's first block
     RT *const h0p = (RT *)d.h[0], *const h1p = (RT *)d.h[1];
     RT *const acc0p = (RT *)d.acc[0], *const acc1p = (RT *)d.acc[1];
@@ -1878,8 +1924,10 @@ __device__ __forceinline__ void resident_tile(ResidentShared<RT, TH> &L, ChainSt
         unsigned long long e_thread = 0ull;
         uint32_t acc_thread = 0u;
         int n_redo = 0;
-        // segment 0: the colour-0 chunks that need no halo; 1: the others; 2: colour 1
-        for (int seg = 0; seg < 3; ++seg) {
+        // segment 0: the colour-0 chunks that need no halo, where it is still
+        // under way; 1: the others; 2: colour 1
+        const bool early = eq && !have;
+        for (int seg = early ? 0 : 1; seg < 3; ++seg) {
             const int c = seg == 2 ? 1 : 0;
             if (seg == 1 && !have) {
                 wait1(i & 1, rc.epoch | (uint32_t)(i + 1));
@@ -1891,7 +1939,7 @@ __device__ __forceinline__ void resident_tile(ResidentShared<RT, TH> &L, ChainSt
             const int k_end = seg == 0 ? inner_chunks : (n + 63) / 64;
             // wave w takes chunks w, w + kResWaves, ...; segment 1 goes on where 0 stopped
             int k = wid;
-            if (seg == 1) k += (inner_chunks > wid ? (inner_chunks - wid + kResWaves - 1) / kResWaves : 0) * kResWaves;
+            if (seg == 1 && early) k += (inner_chunks > wid ? (inner_chunks - wid + kResWaves - 1) / kResWaves : 0) * kResWaves;
             for (; k < k_end; k += kResWaves) {
                 const int e = k * 64 + lane;
                 bool n64 = false;
@@ -2089,13 +2137,15 @@ __global__ __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(4))
     const int lb = (int)(slot - bm.start[k]), nblk = (int)(bm.start[k + 1] - bm.start[k]);
     const int cid = bm.id[k];
     const ChainDesc d = descs[cid];
+    const bool agree = (uint32_t)bm.n < G;  // a chain of several blocks: some wait for others
+    if (agree && threadIdx.x == 0) res_arrive(rc.gen);
     if (states[cid].phase == PH_DONE) return;  // before this launch: no block of the chain starts
     const int nbx = d.S / kTileH;
     const int ty = lb / nbx, tx = lb - ty * nbx;
     const int y0 = ty * TH, hx0 = tx * kTileH;
     const bool edge = !(ty >= 1 && y0 + TH + 2 <= d.ny && tx >= 1 && hx0 + kTileH + 2 <= (d.nx >> 1));
-    if (edge) resident_tile<RT, TH, true>(L, states, d, cid, (int)slot, lb, nblk, sc, cp, rc);
-    else resident_tile<RT, TH, false>(L, states, d, cid, (int)slot, lb, nblk, sc, cp, rc);
+    if (edge) resident_tile<RT, TH, true>(L, states, d, cid, (int)slot, lb, nblk, agree, sc, cp, rc);
+    else resident_tile<RT, TH, false>(L, states, d, cid, (int)slot, lb, nblk, agree, sc, cp, rc);
 }
 
 // The double-precision sweep: the layout of half_sweep_body (a thread per
@@ -2446,6 +2496,15 @@ __global__ void clear_words_kernel(unsigned int *w0, unsigned int *w1, unsigned 
         if (w2) *w2 = 0u;
     }
     for (int k = t; k < n64; k += (int)blockDim.x) wide[k] = 0ull;
+}
+
+// The control words a resident launch starts from: its four words at gen and
+// n64 zeros at `sums`.
+__global__ void clear_resident_kernel(unsigned int *gen, uint32_t start_ticks, unsigned long long *sums, int n64)
+{
+    const int t = (int)threadIdx.x;
+    if (t < 4) gen[t] = t == kResStart ? start_ticks : 0u;
+    for (int k = t; k < n64; k += (int)blockDim.x) sums[k] = 0ull;
 }
 
 // Zeroes the halo words of the resident sweeps.
@@ -3263,11 +3322,8 @@ int64_t half_grid_bytes(int nx, int ny, int eb = 4) { return (int64_t)ny * half_
 // The work of a call on the context's own stream: after what the caller's
 // stream holds at its start, and done at its end (so that the caller's stream
 // need not wait for it).  The sweeps run there, and not on the caller's stream:
-// graphs cannot be captured on the default one, and a cooperative launch, which
-// the runtime moves to another hardware queue and back, must stay in order
-// with the uploads and clears before it while other threads use the caller's
-// stream (three threads with a context each on the default stream: a launch's
-// blocks waited for each other until their bound).
+// graphs cannot be captured on the default one, and calls of several threads
+// that share it would wait for each other.
 struct OwnStream {
     mpr_ctx *ctx;
     hipError_t err;
@@ -3830,7 +3886,7 @@ int64_t persist_capacity(mpr_ctx *ctx, int rows, bool fp64)
 // Up to rc.count fused sweeps of every listed chain in resident shape v, in
 // one cooperative launch.
 hipError_t launch_resident(mpr_ctx *ctx, hipStream_t st, const ChainSet &cs, int v, const SweepConsts &sc,
-                           const CtlParams &cp, ResidentCtl rc)
+                           const CtlParams &cp, ResidentCtl rc, uint32_t start_ticks)
 {
     if (ctx->halo_epoch == 0 || ctx->halo_epoch + 1 >= kResEpochs) {
         // no word may hold the tag of a later launch
@@ -3838,7 +3894,7 @@ hipError_t launch_resident(mpr_ctx *ctx, hipStream_t st, const ChainSet &cs, int
         ctx->halo_epoch = 0;
     }
     rc.epoch = ++ctx->halo_epoch << kResSweepBits;
-    hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(kBlock), 0, st, rc.gen, nullptr, nullptr, rc.sums,
+    hipLaunchKernelGGL(clear_resident_kernel, dim3(1), dim3(kBlock), 0, st, rc.gen, start_ticks, rc.sums,
                        3 * kResMaxBlocks);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -3968,17 +4024,19 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     // The caller's bound on a block's wait holds where MPR_TILE_PERSIST can be
     // asked for: single-precision chains that record no states, in tiles of at
     // most 32 rows from the call's start.  Elsewhere resident sweeps stand in
-    // for launches that wait for nothing, and a bound below the default must
-    // not end the call.
+    // for launches that wait for nothing: a launch that does not go within the
+    // bound is called off, and no other bound below the default ends the call.
     const uint64_t own_wait = (uint64_t)p->barrier_timeout_us * 100u;
-    const bool bounded = own_wait > 0 && fuse && !table;
     bool tail = false;  // the last chains of a set, made resident on the way
+    auto bounded = [&](int v) { return own_wait > 0 && fuse && !table && !tail && kShapes[v].rows <= 32; };
+    bool called_off = false;  // a resident launch was: one launch per sweep from then on
     hipError_t perr = hipSuccess;
     auto sweeps = [&](int v, int count) {
         if (kShapes[v].persist) {
-            rc0.wait_ticks = bounded && !tail && kShapes[v].rows <= 32 ? own_wait : std::max(own_wait, kPersistWaitTicks);
+            rc0.wait_ticks = bounded(v) ? own_wait : std::max(own_wait, kPersistWaitTicks);
             rc0.count = count;
-            perr = launch_resident(ctx, st, cs, v, sc, cp, rc0);
+            const uint64_t start = own_wait > 0 ? std::min<uint64_t>(own_wait, UINT32_MAX) : kPersistStartTicks;
+            perr = launch_resident(ctx, st, cs, v, sc, cp, rc0, (uint32_t)start);
             return;
         }
         for (int i = 0; i < count; ++i) {
@@ -4019,7 +4077,8 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
                                     hipMemcpyDeviceToHost, st));
         HIP_TRY(ctx, hipStreamSynchronize(st));
         if (kShapes[v].persist) {
-            if (ctx->done_host[kAbortOffset / 4] != 0u)
+            called_off = ctx->done_host[kGenOffset / 4 + kResGoes] == kResOff;
+            if (ctx->done_host[kAbortOffset / 4] != 0u || (called_off && bounded(v)))
                 return fail(ctx, MPR_ERR_HIP,
                             "resident sweeps: a block waited for another one longer than its bound (2 s, or "
                             "params.barrier_timeout_us)");
@@ -4042,6 +4101,7 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     // launch per sweep shapes of table chains are the plain ones, those of
     // double-precision chains every unfused one.
     const int n_shapes = table ? kNumPlainShapes : (cs.fp64 ? kNumUnfusedShapes : kNumShapes);
+    const int per_sweep = table || cs.fp64 ? kDefaultShape : shape_of(32 | MPR_TILE_FUSED);
     int v = p->tile_rows ? shape_of(p->tile_rows) : -1;
     if (v >= n_shapes) v = kDefaultShape;
     // a resident shape asked for whose tiles the device does not hold at once:
@@ -4176,6 +4236,13 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         const int cnt = (int)std::min<int64_t>(spl, max_sweeps - done_sweeps);
         rc = block(v, cnt, cnt == spl ? ge : nullptr, nullptr);
         if (rc) break;
+        if (called_off && kShapes[v].persist) {
+            v = per_sweep;
+            if (!table) ctx->last_tile = tile_code(kShapes[v]);
+            if (p->sweeps_per_launch <= 0) spl = poll_every;
+            capture();
+            continue;
+        }
         const unsigned int done_now = *ctx->done_host + already;
         if (finished || !can_shrink || done_now - done_listed < std::max(1u, (unsigned int)cs.n_active / 8u))
             continue;
@@ -4194,7 +4261,7 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         if (active.empty() || 5 * blocks > 4 * cs.total_blocks[v]) continue;
         rc = set_active(ctx, cs, active, st);
         if (rc) break;
-        if (!p->tile_rows && !kShapes[v].persist) {
+        if (!p->tile_rows && !kShapes[v].persist && !called_off) {
             // the last chains of a set finish in one resident launch once
             // they fit
             const int best = resident_shape();
