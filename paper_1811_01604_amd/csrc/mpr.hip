@@ -1474,7 +1474,7 @@ __global__ __launch_bounds__(kBlock) void sweep_tile_kernel(ChainDesc *__restric
 // between two words by the same argument over the whole chain.
 // Measured, one chain with 100 states, whole fills, against the kernel this
 // replaced (tiles written to memory and a device-wide barrier between
-// sweeps): 64^2 4.4 us per sweep (8.5), 1024^2 8.4 us (18.9); 2048^2 28.7 us,
+// sweeps): 64^2 4.4 us per sweep (8.5), 1024^2 8.5 us (18.9); 2048^2 28.7 us,
 // against 41.3 us with one launch per sweep; four double-precision chains of
 // 512^2 17.3 us, against two half-sweep launches of 12 us; 32 table chains of
 // 256^2 17 us, against 38 us of half-sweeps and deferred redos.
