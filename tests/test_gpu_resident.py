@@ -193,3 +193,26 @@ def test_threads_with_a_context_each(own_streams):
     for t in threads:
         t.join()
     assert not wrong
+
+
+@pytest.mark.parametrize("fp64", [0, 1])
+def test_launches_called_off_and_runs_resumed(ctx, fp64):
+    """A bound of 1 us calls resident launches with recorded states off (their
+    sweeps then run one launch each); runs of 11 sweeps a call, the first two
+    of them so, the others resident, end as one run of half-sweeps does."""
+    imgs, mk, phi = image(ctx, 130, 517)
+    kw = dict(R=3, K=9, spread=1, fp64=fp64)
+    ref = run(ctx, imgs, phi, mk, 0.05, 4, record=True, **kw)
+    prm = mpr.default_params(sweep_limit=11, **kw)
+    ws = torch.empty(ctx.workspace_size(imgs, prm), dtype=torch.uint8, device="cuda")
+    ps, m2 = torch.zeros_like(phi), torch.zeros_like(phi)
+    states = torch.zeros(prm.R * prm.K * phi.numel(), device="cuda")
+    tiles, done = [], False
+    while not done:
+        prm.barrier_timeout_us = 1 if len(tiles) < 2 else 0
+        prm.resume = 1 if tiles else 0
+        done, st = ctx.simulate(imgs, phi, mk, np.array([0.05]), prm, ws, ps, phi_m2=m2, phi_states=states,
+                                allow_incomplete=True)
+        tiles.append(bool(ctx.profile_read()["last_tile"] & mpr.TILE_PERSIST))
+    assert len(tiles) > 3 and not any(tiles[:2]) and all(tiles[2:])
+    assert ([o.cpu().numpy().tobytes() for o in (ps, m2, states)], st) == ref
