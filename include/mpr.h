@@ -25,8 +25,8 @@
  *    managed memory) with MPR_ERR_ARG; it cannot check their extent, which
  *    is the caller's to size as each call states.
  *  - `stream` is a hipStream_t (NULL = the default stream).  Work is
- *    enqueued on it (that of mpr_simulate and of the e(T, L) tables on a
- *    stream of the context, after it) and done before the call returns.
+ *    enqueued on it (sweeps also on a stream of the context, after it) and
+ *    done before the call returns.
  *  - Sampled flags are uint8: nonzero = sampled (fixed), 0 = gap.
  *  - Every call returns MPR_OK (0) or an error code (mpr_simulate also
  *    MPR_INCOMPLETE, see mpr_params.sweep_limit); mpr_last_error gives a

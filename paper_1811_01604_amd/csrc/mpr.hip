@@ -3237,9 +3237,10 @@ struct mpr_ctx {
     // tile rows and angle bytes (0: no cooperative launch on this device)
     std::map<std::pair<int, int>, int64_t> persist_cap;
     uint32_t halo_epoch = 0;          // resident launches since the halo words were cleared; 0: not cleared yet
-    // the stream of the calls with sweeps (OwnStream), after the caller's
+    // sweeps of one launch and less run on a context-owned stream (captured
+    // into HIP graphs), ordered after and before the caller's with two events
     hipStream_t gstream = nullptr;
-    hipEvent_t ev_in = nullptr, ev_t0 = nullptr, ev_t1 = nullptr;
+    hipEvent_t ev_in = nullptr, ev_out = nullptr, ev_t0 = nullptr, ev_t1 = nullptr;
     // tuned block shape by what the cost of a sweep depends on: type and
     // options, chains, largest sides, blocks (all chains together) and share of
     // gaps (shapes before `next` are timed; a run too short to time them all
@@ -3318,26 +3319,6 @@ int half_stride(int nx) { return (int)round_up((nx + 1) / 2, 64); }
 
 // Bytes of one half-grid of `eb`-byte angles.
 int64_t half_grid_bytes(int nx, int ny, int eb = 4) { return (int64_t)ny * half_stride(nx) * eb; }
-
-// The work of a call on the context's own stream: after what the caller's
-// stream holds at its start, and done at its end (so that the caller's stream
-// need not wait for it).  The sweeps run there, and not on the caller's stream:
-// graphs cannot be captured on the default one, and calls of several threads
-// that share it would wait for each other.
-struct OwnStream {
-    mpr_ctx *ctx;
-    hipError_t err;
-    OwnStream(mpr_ctx *c, hipStream_t caller) : ctx(c), err(hipStreamQuery(caller))
-    {
-        if (err == hipSuccess) return;  // nothing to wait for (an event and its wait cost some 15 us of a call)
-        (void)hipGetLastError();
-        err = hipEventRecord(c->ev_in, caller);
-        if (err == hipSuccess) err = hipStreamWaitEvent(c->gstream, c->ev_in, 0);
-    }
-    ~OwnStream() { (void)hipStreamSynchronize(ctx->gstream); }
-    OwnStream(const OwnStream &) = delete;
-    OwnStream &operator=(const OwnStream &) = delete;
-};
 
 // Host memory for a read-back of `bytes`: the context's pinned staging
 // area when it fits, else `spill` (pageable), resized.
@@ -3957,7 +3938,7 @@ int clear_redo(mpr_ctx *ctx, ChainSet &cs, hipStream_t stream)
 // as a captured graph (launched directly when `graphs` is false: instantiating
 // a graph allocates), checking the done-counter after each group.  At most
 // max_sweeps sweeps run; chains still running then are an error, or with
-// `stop_ok` the result MPR_INCOMPLETE.  `stream` is the context's own.
+// `stop_ok` the result MPR_INCOMPLETE.
 int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stream, int64_t max_sweeps,
                int poll_every, bool table, bool graphs = true, bool stop_ok = false)
 {
@@ -3980,7 +3961,7 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     }
     const SweepConsts sc = make_sc(p->q, p->seed);
     const int cblocks = (n + 63) / 64;
-    const hipStream_t st = stream;
+    hipStream_t st = stream;  // the context's own for shapes that are not resident
 
     // the control runs at the end of the colour-1 redo kernel unless
     // something must run between them (the state record) or there is no
@@ -4155,6 +4136,16 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         return best;
     };
     if (v < 0) v = resident_shape();
+    // The resident shapes run on the caller's stream, the others on the
+    // context's own, ordered after and before the caller's with two events (15
+    // to 40 us of a call): half-sweeps are captured into graphs (the caller's
+    // may be the default stream, which cannot be captured, and other threads
+    // may use it), and calls of several threads on the default stream overlap.
+    if (v < 0 || !kShapes[v].persist) {
+        st = ctx->gstream;
+        HIP_TRY(ctx, hipEventRecord(ctx->ev_in, stream));
+        HIP_TRY(ctx, hipStreamWaitEvent(st, ctx->ev_in, 0));
+    }
     float sweep_ms = -1.0f;
     if (v < 0) {
         int maxnx = 0, maxny = 0;
@@ -4212,7 +4203,8 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
         // (a resident launch runs a whole group itself; a fused sweep is one or
         // two launches of 20 us and more, which the host keeps ahead of, and
         // capturing its graph anew whenever the list changes took 60 to 190 us)
-        if (graphs && !kShapes[v].fused && hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) == hipSuccess) {
+        if (graphs && !kShapes[v].fused && st == ctx->gstream &&
+            hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) == hipSuccess) {
             sweeps(v, spl);
             if (hipStreamEndCapture(st, &cap.graph) != hipSuccess ||
                 hipGraphInstantiate(&cap.exec, cap.graph, nullptr, nullptr, 0) != hipSuccess)
@@ -4275,6 +4267,10 @@ int run_chains(mpr_ctx *ctx, ChainSet &cs, const mpr_params *p, hipStream_t stre
     }
     cap.release();
     if (rc) return rc;
+    if (st != stream) {
+        HIP_TRY(ctx, hipEventRecord(ctx->ev_out, st));
+        HIP_TRY(ctx, hipStreamWaitEvent(stream, ctx->ev_out, 0));
+    }
     if (!finished)
         return stop_ok ? MPR_INCOMPLETE
                        : fail(ctx, MPR_ERR_HIP, "chains did not finish within %lld sweeps", (long long)max_sweeps);
@@ -4493,6 +4489,7 @@ int32_t mpr_create(mpr_ctx **out, int32_t device)
         hipHostMalloc((void **)&ctx->done_host, kHostStageBytes, hipHostMallocDefault) != hipSuccess ||
         hipStreamCreateWithFlags(&ctx->gstream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->ev_in, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&ctx->ev_out, hipEventDisableTiming) != hipSuccess ||
         hipEventCreate(&ctx->ev_t0) != hipSuccess || hipEventCreate(&ctx->ev_t1) != hipSuccess) {
         mpr_destroy(ctx);
         return MPR_ERR_HIP;
@@ -4506,7 +4503,7 @@ void mpr_destroy(mpr_ctx *ctx)
     if (!ctx) return;
     (void)hipSetDevice(ctx->device);
     if (ctx->gstream) (void)hipStreamSynchronize(ctx->gstream);
-    for (hipEvent_t ev : {ctx->ev_in, ctx->ev_t0, ctx->ev_t1})
+    for (hipEvent_t ev : {ctx->ev_in, ctx->ev_out, ctx->ev_t0, ctx->ev_t1})
         if (ev) (void)hipEventDestroy(ev);
     if (ctx->gstream) (void)hipStreamDestroy(ctx->gstream);
     if (ctx->scratch) (void)hipFree(ctx->scratch);
@@ -4728,9 +4725,6 @@ int32_t mpr_estimate_temperature(mpr_ctx *ctx, const mpr_image *imgs, int32_t n,
                nT * (int64_t)(sizeof(ChainDesc) + sizeof(ChainState) + 8 + (kNumStarts + 1) * 8) + 4096;
     };
     for (size_t first = 0; first < missing.size();) {
-        const OwnStream own(ctx, stream);
-        HIP_TRY(ctx, own.err);
-        const hipStream_t st = ctx->gstream;
         // as many grid sizes as fit (at least one: the workspace holds the largest)
         size_t last = first;
         int64_t need = 65536 + table_chain_bytes(missing[first]);
@@ -4758,15 +4752,15 @@ int32_t mpr_estimate_temperature(mpr_ctx *ctx, const mpr_image *imgs, int32_t n,
                 cs.offset.push_back(0);
             }
         }
-        int rc = upload_chains(ctx, cs, cv, st, p->q);
+        int rc = upload_chains(ctx, cs, cv, stream, p->q);
         if (rc) return rc;
-        launch_init(st, cs, nullptr, nullptr, nullptr, 0u, 1);
+        launch_init(stream, cs, nullptr, nullptr, nullptr, 0u, 1);
         HIP_TRY(ctx, hipGetLastError());
-        rc = run_chains(ctx, cs, p, st, (int64_t)p->table_burn + p->table_meas, 50, true);
+        rc = run_chains(ctx, cs, p, stream, (int64_t)p->table_burn + p->table_meas, 50, true);
         if (rc) return rc;
         HIP_TRY(ctx, hipMemcpyAsync(cs.state.data(), cs.d_state, cs.state.size() * sizeof(ChainState),
-                                    hipMemcpyDeviceToHost, st));
-        HIP_TRY(ctx, hipStreamSynchronize(st));
+                                    hipMemcpyDeviceToHost, stream));
+        HIP_TRY(ctx, hipStreamSynchronize(stream));
         for (size_t g = first; g <= last; ++g) {
             std::vector<double> ope(nT);
             for (int k = 0; k < nT; ++k) ope[k] = cs.state[(g - first) * nT + k].e_sum / (double)p->table_meas;
@@ -4809,9 +4803,7 @@ static int32_t simulate_call(mpr_ctx *ctx, const mpr_image *imgs, int32_t n, con
         if (!(T_hat[b] > 0.0) || !std::isfinite(T_hat[b])) return fail(ctx, MPR_ERR_ARG, "image %d: bad T_hat", b);
     if (!ws || ws_bytes < sim_bytes(imgs, n, p)) return fail(ctx, MPR_ERR_WORKSPACE, "workspace too small");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    const OwnStream own(ctx, (hipStream_t)stream_);
-    HIP_TRY(ctx, own.err);
-    const hipStream_t stream = ctx->gstream;
+    hipStream_t stream = (hipStream_t)stream_;
     // gap counts (host needs them for the acceptance ratio): from the mask
     // via a device reduction would need scratch; count with the e_s-style
     // partials instead, reusing the map kernel's layout.
